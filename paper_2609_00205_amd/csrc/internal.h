@@ -264,13 +264,10 @@ void decompose_adjoint(bm_plan_s& p, const void* gcoeff, void* gx, hipStream_t s
 void recompose_adjoint(bm_plan_s& p, const void* gx, void* gcoeff, hipStream_t st);
 
 // quantization tables on the device, built from a level-1 block map:
-// per local level s (slot s-1) the per-block Delta and 1/Delta; slot 8 for
-// the coarsest values when M == 0 (level-L blocks); scalar Delta / 1/Delta
+// per local level s (slot s-1) the class tables; slot 8 for the coarsest values when M == 0 (level-L blocks); scalar Delta / 1/Delta
 // per global level (q[2(s-1)], q[2(s-1)+1]) and for the coarsest values
 // (q[2(L+M)], q[2(L+M)+1]).
 struct QTab {
-  const double* del = nullptr;
-  const double* inv = nullptr;
   // per block, per class of node position (first face / interior / last face
   // along z, y, x: 27 classes, index 9 cz + 3 cy + cx) the smallest Delta and
   // the largest 1/Delta over the blocks that contain such a node

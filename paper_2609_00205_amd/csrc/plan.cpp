@@ -399,9 +399,9 @@ bm_plan_s* bm_plan_build(const bm_config* c) {
     }
     p->ws.tol_off[c->L + 1] = tot;
     const int64_t nlastb = c->L > 0 ? prod3(p->lv[c->L - 1].nb) : 0;
-    // propagated taus, Delta, 1/Delta per block; tau_global; coarsest-value
-    // Delta and 1/Delta; then the 27-class Delta and 1/Delta tables
-    plan_alloc(*p, &p->ws.tolbuf, size_t(3 * tot + 8 + 2 * nlastb + 8 + 54 * (tot + nlastb)) * sizeof(double));
+    // propagated taus; tau_global; then the 27-class Delta and 1/Delta tables
+    // of the levels and of the coarsest values
+    plan_alloc(*p, &p->ws.tolbuf, size_t(tot + 8 + 54 * (tot + nlastb)) * sizeof(double));
     plan_alloc(*p, &p->ws.boxbuf, size_t(kMaxBoxes) * 7 * sizeof(double));
     BM_HIP(hipHostMalloc(&p->ws.boxhost, size_t(kMaxBoxes) * 7 * sizeof(double), hipHostMallocDefault));
     plan_alloc(*p, &p->ws.qparam, size_t(4 * (p->nlev + 2)) * sizeof(double));

@@ -42,10 +42,6 @@ __device__ inline void atomic_min_pos(double* p, double v) {
   atomicMin(reinterpret_cast<unsigned long long*>(p), static_cast<unsigned long long>(__double_as_longlong(v)));
 }
 
-__global__ void k_fill_u64(unsigned long long* p) {
-  if (threadIdx.x == 0) *p = 0;
-}
-
 __global__ void k_fill(double* p, int64_t n, double v) {
   for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < n; i += int64_t(gridDim.x) * NT) p[i] = v;
 }
@@ -147,10 +143,11 @@ struct QArgs {
   int D[3];                   // levels each axis coarsens
   int lw;                     // log2(b - 1), b of the first block level
   int nested;                 // nested block schedule: every level's blocks span b - 1 padded cells
-  // per-block Delta and 1/Delta: slot s-1 for the details of local level s;
-  // slot kCoarseSlot for the coarsest values when M == 0 (level-L blocks)
-  const double* bdelta[9];
-  const double* binv[9];
+  // 27-class Delta and 1/Delta tables per block: slot s-1 for the details of
+  // local level s; slot kCoarseSlot for the coarsest values when M == 0
+  // (level-L blocks)
+  const double* cdel[9];
+  const double* cinv[9];
   uint32_t nb[9][3];
   const double* q;            // scalar Delta / inverse per level (index s-1), coarsest at L+M
   int64_t* counters;          // [0] outliers, [1] max |q|, [2] out of range
@@ -176,37 +173,31 @@ constexpr int kCoarseSlot = 8;
 // Delta and 1/Delta of a node whose tolerance comes from the blocks of local
 // level s (grid coordinates q = g >> (s-1)), from table slot `slot`.  Block i
 // spans nodes [i w, (i+1) w]: a node on a shared face lies in two blocks per
-// axis.  In the nested schedule the blocks of every level span the same
+// axis, and the block's class table holds the smallest Delta (largest
+// 1/Delta) of the up to eight: one load per node instead of a walk over them
+// (k_qoi_final at 384 x 384 x 256 FP32: 0.227 -> 0.166 ms, with the share no
+// longer read there).  In the nested schedule the blocks of every level span the same
 // padded-grid regions, so the padded coordinates g index them directly.
 __device__ inline void block_delta(const QArgs& a, int s, int slot, uint32_t g0, uint32_t g1, uint32_t g2,
                                    double& del, double& inv) {
   const int sh = a.nested ? 0 : s - 1;
   const uint32_t q[3] = {g0 >> sh, g1 >> sh, g2 >> sh};
   const uint32_t wm = (1u << a.lw) - 1;
-  uint32_t lo[3], hi[3];
+  uint32_t f[3], cls = 0;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const uint32_t nb = a.nb[slot][d];
-    const uint32_t f = q[d] >> a.lw;
-    lo[d] = ((q[d] & wm) == 0 && q[d] > 0) ? f - 1 : f;
-    hi[d] = f < nb - 1 ? f : nb - 1;
-    if (lo[d] > hi[d]) lo[d] = hi[d];
+    f[d] = q[d] >> a.lw;
+    uint32_t c = 1;                       // inside a block
+    if ((q[d] & wm) == 0) {
+      const bool far = f[d] >= a.nb[slot][d];
+      f[d] = far ? a.nb[slot][d] - 1 : f[d];
+      c = far ? 2 : 0;                    // the far end of the grid, or the face block f starts on
+    }
+    cls = cls * 3 + c;
   }
-  const double* bd = a.bdelta[slot];
-  const double* bi = a.binv[slot];
-  const uint32_t n1 = a.nb[slot][1], n2 = a.nb[slot][2];
-  uint32_t k = (lo[0] * n1 + lo[1]) * n2 + lo[2];
-  del = bd[k];
-  inv = bi[k];
-  if (lo[0] != hi[0] || lo[1] != hi[1] || lo[2] != hi[2]) {
-    for (uint32_t z = lo[0]; z <= hi[0]; ++z)
-      for (uint32_t y = lo[1]; y <= hi[1]; ++y)
-        for (uint32_t x = lo[2]; x <= hi[2]; ++x) {
-          k = (z * n1 + y) * n2 + x;
-          del = fmin(del, bd[k]);
-          inv = fmax(inv, bi[k]);
-        }
-  }
+  const uint32_t k = ((f[0] * a.nb[slot][1] + f[1]) * a.nb[slot][2] + f[2]) * 27u + cls;
+  del = a.cdel[slot][k];
+  inv = a.cinv[slot][k];
 }
 
 __device__ inline void node_delta(const QArgs& a, uint32_t z, uint32_t y, uint32_t x, double& del, double& inv) {
@@ -367,15 +358,44 @@ int64_t prod3(const int64_t n[3]) { return n[0] * n[1] * n[2]; }
 // s = R^T g, quantization moves Q by at most sum |s_i| Delta_i / 2.  Each
 // coefficient's share |s_i| Delta_i / 2 is one level lambda, except where the
 // node's L-inf width cap_i is smaller: share = min(a_i, lambda) with
-// a_i = |s_i| cap_i / 2, and lambda the root of sum_i min(a_i, lambda) =
-// (1 - eta) tol_q.  Sums are reduced per workgroup in a fixed order, then by
-// one workgroup (deterministic).
+// a_i = |s_i| cap_i / 2, and lambda the root of f(lambda) =
+// sum_i min(a_i, lambda) = (1 - eta) tol_q.  f is concave and piecewise
+// linear; a pass evaluates it at kQoiK candidates and keeps the bracket
+// f(lo) <= target < f(hi).
+//
+// HBM reads bound a pass, so a pass drops the shares that no later pass
+// needs one by one: a share <= lo adds itself to every later sum, one >= hi
+// adds the candidate.  Each wavefront compacts the others, in order, over the
+// chunks it has read already (in place, no atomics, the same result on every
+// run), so only the first pass goes over all nodes.  The next candidates lie
+// between the bounds that concavity gives (chords from outside the bracket
+// below, the bracket's own chord above), which closes in quadratically where
+// an even split of the bracket gains a factor 16; the steps run on the device,
+// so passes follow each other without a host round trip.  384 x 384 x 256
+// FP32: shares 0.309 -> 0.184 ms (152 MB read, the shares above lo written),
+// search 1.88 ms (15 passes over 306 MB and their folds) -> 0.17 ms.
+// Sums are reduced per workgroup in a fixed order, then by one workgroup
+// (deterministic).
 constexpr int kQoiK = 15;           // candidate levels per pass
-constexpr int kQoiGroups = 1024;    // workgroups of a pass (partials: kQoiK per group)
+constexpr int kQoiGroups = 1024;    // workgroups of a pass
+constexpr int kQoiPasses = 10;      // passes launched before the host looks whether the search has ended
+constexpr int kQoiU = 4;            // chunks in flight per wavefront
 
-struct Cand {
-  double v[kQoiK];
+// the search's state in the plan's statistics scratch
+struct QoiState {
+  double target, lo, hi, flo, fhi;  // f at lo and hi (NaN while unknown)
+  double c[kQoiK];                  // the next pass's candidates, ascending
+  double lambda;
+  int done, passes;
 };
+struct QoiScratch {
+  QoiState st;
+  double sum[kQoiGroups], max[kQoiGroups];            // of all shares, per workgroup
+  double f[kQoiGroups * kQoiK];                       // candidates' sums over the kept shares
+  double low[kQoiGroups], high[kQoiGroups];           // dropped: sum of the low ones, count of the high ones
+  int kept[kQoiGroups * (NT / 64)];                   // kept shares per wavefront
+};
+static_assert(sizeof(QoiScratch) <= 3 * 8192 * sizeof(double), "QoI scratch exceeds the statistics scratch");
 
 __device__ inline double block_sum(double v, double* red) {
   red[threadIdx.x] = v;
@@ -401,76 +421,308 @@ __device__ inline double block_max(double v, double* red) {
   return r;
 }
 
-// a_i = |s_i| cap_i / 2 into share[i]; partials[2 g] = sum, [2 g + 1] = max
-template <typename T>
-__global__ __launch_bounds__(NT) void k_qoi_shares(QArgs a, const T* s, double* share, double* partials) {
-  __shared__ double red[NT];
-  double sum = 0.0, mx = 0.0;
-  for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < a.tot; i += gridDim.x * NT) {
-    uint32_t z, y, x;
-    a.uf(i, z, y, x);
-    double del, inv;
-    node_delta(a, z, y, x, del, inv);
-    const double v = fabs(double(s[i])) * del * 0.5;
-    share[i] = v;
-    sum += v;
-    mx = fmax(mx, v);
+// The 64-share chunks of wavefront w (of W) in the share array: chunk k at
+// (k W + w) 64.  Keeps v (where `keep`) at position `at` of the wavefront's
+// compacted list and advances it; a list never overtakes the chunks read.
+__device__ inline void qoi_keep(double* share, uint32_t W, uint32_t w, int lane, bool keep, double v, uint32_t& at) {
+  const unsigned long long m = __ballot(keep);
+  if (keep) {
+    const uint32_t p = at + __popcll(m & ((1ull << lane) - 1));
+    share[(uint64_t(p >> 6) * W + w) * 64 + (p & 63)] = v;
   }
-  sum = block_sum(sum, red);
-  mx = block_max(mx, red);
-  if (threadIdx.x == 0) {
-    partials[2 * blockIdx.x] = sum;
-    partials[2 * blockIdx.x + 1] = mx;
-  }
+  at += __popcll(m);
 }
 
-// f(c_j) = sum_i min(a_i, c_j) for the kQoiK candidates: partials[g kQoiK + j]
-__global__ __launch_bounds__(NT) void k_qoi_eval(const double* share, uint32_t n, Cand c, double* partials) {
+// a_i = |s_i| cap_i / 2 of every node: their sum and max, f at the first
+// candidates, and the ones above lo kept in share.
+template <typename T>
+__global__ __launch_bounds__(NT) void k_qoi_shares(QArgs a, const T* s, double* share, QoiScratch* q) {
   __shared__ double red[NT];
-  double acc[kQoiK];
+  const int lane = threadIdx.x & 63;
+  const uint32_t W = gridDim.x * (NT / 64), w = blockIdx.x * (NT / 64) + (threadIdx.x >> 6);
+  const uint32_t nchunk = uint32_t((uint64_t(a.tot) + 63) / 64);
+  const double lo = q->st.lo;
+  double c[kQoiK], acc[kQoiK];
 #pragma unroll
-  for (int j = 0; j < kQoiK; ++j) acc[j] = 0.0;
-  for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < n; i += gridDim.x * NT) {
-    const double v = share[i];
+  for (int j = 0; j < kQoiK; ++j) {
+    c[j] = q->st.c[j];
+    acc[j] = 0.0;
+  }
+  double sum = 0.0, mx = 0.0, low = 0.0;
+  uint32_t at = 0;
+  for (uint32_t k0 = w; k0 < nchunk; k0 += kQoiU * W) {
+    double v[kQoiU];
 #pragma unroll
-    for (int j = 0; j < kQoiK; ++j) acc[j] += fmin(v, c.v[j]);
+    for (int u = 0; u < kQoiU; ++u) {
+      const uint64_t i = (uint64_t(k0) + uint64_t(u) * W) * 64 + lane;
+      v[u] = 0.0;
+      if (i < a.tot) {
+        uint32_t z, y, x;
+        a.uf(uint32_t(i), z, y, x);
+        double del, inv;
+        node_delta(a, z, y, x, del, inv);
+        v[u] = fabs(double(s[i])) * del * 0.5;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kQoiU; ++u) {
+      sum += v[u];
+      mx = fmax(mx, v[u]);
+      const bool keep = !(v[u] <= lo);
+      if (!keep) low += v[u];
+      qoi_keep(share, W, w, lane, keep, v[u], at);
+      if (keep) {
+#pragma unroll
+        for (int j = 0; j < kQoiK; ++j) acc[j] += fmin(v[u], c[j]);
+      }
+    }
+  }
+  if (lane == 0) q->kept[w] = int(at);
+  sum = block_sum(sum, red);
+  mx = block_max(mx, red);
+  low = block_sum(low, red);
+  if (threadIdx.x == 0) {
+    q->sum[blockIdx.x] = sum;
+    q->max[blockIdx.x] = mx;
+    q->low[blockIdx.x] = low;
+    q->high[blockIdx.x] = 0.0;
   }
   for (int j = 0; j < kQoiK; ++j) {
     const double r = block_sum(acc[j], red);
-    if (threadIdx.x == 0) partials[blockIdx.x * kQoiK + j] = r;
+    if (threadIdx.x == 0) q->f[blockIdx.x * kQoiK + j] = r;
   }
 }
 
-// out[j] = sum (or max, for odd j when max_odd) over ng groups of partials[g k + j]
-__global__ __launch_bounds__(NT) void k_qoi_fold(const double* partials, int ng, int k, int max_odd, double* out) {
+// one later pass over the kept shares (same grid as k_qoi_shares)
+__global__ __launch_bounds__(NT) void k_qoi_eval(double* share, QoiScratch* q) {
   __shared__ double red[NT];
-  for (int j = 0; j < k; ++j) {
-    const bool mx = max_odd && (j & 1);
-    double v = 0.0;
-    for (int g = threadIdx.x; g < ng; g += NT) v = mx ? fmax(v, partials[g * k + j]) : v + partials[g * k + j];
-    v = mx ? block_max(v, red) : block_sum(v, red);
-    if (threadIdx.x == 0) out[j] = v;
+  if (q->st.done) return;
+  const int lane = threadIdx.x & 63;
+  const uint32_t W = gridDim.x * (NT / 64), w = blockIdx.x * (NT / 64) + (threadIdx.x >> 6);
+  const double lo = q->st.lo, hi = q->st.hi;
+  double c[kQoiK], acc[kQoiK];
+#pragma unroll
+  for (int j = 0; j < kQoiK; ++j) {
+    c[j] = q->st.c[j];
+    acc[j] = 0.0;
   }
+  const uint32_t n = uint32_t(q->kept[w]);
+  double low = 0.0, high = 0.0;
+  uint32_t at = 0;
+  for (uint32_t p0 = 0; p0 < n; p0 += 64 * kQoiU) {
+    double v[kQoiU];
+    bool in[kQoiU];
+#pragma unroll
+    for (int u = 0; u < kQoiU; ++u) {
+      const uint32_t p = p0 + 64 * u + lane;
+      in[u] = p < n;
+      v[u] = in[u] ? share[(uint64_t(p >> 6) * W + w) * 64 + lane] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kQoiU; ++u) {
+      const bool dl = v[u] <= lo, dh = v[u] >= hi;
+      const bool keep = in[u] && !dl && !dh;
+      if (in[u] && dl) low += v[u];
+      if (in[u] && dh) high += 1.0;
+      qoi_keep(share, W, w, lane, keep, v[u], at);
+      if (keep) {
+#pragma unroll
+        for (int j = 0; j < kQoiK; ++j) acc[j] += fmin(v[u], c[j]);
+      }
+    }
+  }
+  if (lane == 0) q->kept[w] = int(at);
+  low = block_sum(low, red);
+  high = block_sum(high, red);
+  if (threadIdx.x == 0) {
+    q->low[blockIdx.x] += low;
+    q->high[blockIdx.x] += high;
+  }
+  for (int j = 0; j < kQoiK; ++j) {
+    const double r = block_sum(acc[j], red);
+    if (threadIdx.x == 0) q->f[blockIdx.x * kQoiK + j] = r;
+  }
+}
+
+// The search starts at lo = target / n (f(lo) <= n lo) with candidates a
+// factor 4 apart; the largest share, hi, is known after the first pass.
+__global__ void k_qoi_begin(QoiScratch* q, double target, double n, unsigned long long* count) {
+  if (threadIdx.x != 0) return;
+  *count = 0;
+  QoiState& t = q->st;
+  t.target = target;
+  t.lo = target / n;
+  t.hi = INFINITY;
+  t.flo = t.fhi = NAN;
+  t.lambda = 0.0;
+  t.done = t.passes = 0;
+  double c = t.lo;
+  for (int j = 0; j < kQoiK; ++j) t.c[j] = c *= 4.0;
+}
+
+__device__ inline double from_bits(long long b) { return __longlong_as_double(b); }
+
+// The new bracket [lo, hi] from the candidates' sums f, and the next
+// candidates (or the end: no double strictly inside, lambda = lo).
+__device__ inline void qoi_narrow(QoiState& t, const double* f) {
+  double lo = t.lo, hi = t.hi, flo = t.flo, fhi = t.fhi;
+  // the points around the bracket's ends, outside it (NaN: none)
+  double plo = NAN, pflo = NAN, phi = NAN, pfhi = NAN;
+  for (int j = 0; j < kQoiK; ++j) {       // the largest candidate with f <= target
+    const double c = t.c[j];
+    if (c > t.lo && c < t.hi && f[j] <= t.target && c > lo) {
+      plo = lo;
+      pflo = flo;
+      lo = c;
+      flo = f[j];
+    }
+  }
+  for (int j = kQoiK - 1; j >= 0; --j) {  // the smallest with f > target
+    const double c = t.c[j];
+    if (c > t.lo && c < t.hi && !(f[j] <= t.target) && c < hi) {
+      phi = hi;
+      pfhi = fhi;
+      hi = c;
+      fhi = f[j];
+    }
+  }
+  t.passes += 1;
+  if (lo >= hi) {                         // sums not monotone at rounding level
+    t.lambda = lo;
+    t.done = 1;
+    return;
+  }
+  t.lo = lo;
+  t.hi = hi;
+  t.flo = flo;
+  t.fhi = fhi;
+  const long long blo = __double_as_longlong(lo), bhi = __double_as_longlong(hi);   // positive: ordered like the values
+  if (bhi - blo <= 1 || t.passes >= 80) {
+    t.lambda = lo;
+    t.done = 1;
+    return;
+  }
+  // where the root can lie
+  double L = lo, U = hi;
+  const double slope = (fhi - flo) / (hi - lo);
+  if (slope > 0 && isfinite(slope)) {
+    // sums carry a few roundings of the target, candidates one of their own
+    const double slack = 2e-15 * t.target / slope + 4e-16 * lo;
+    U = fmin(U, lo + (t.target - flo) / slope + slack);
+    const double sl = (flo - pflo) / (lo - plo), sh = (pfhi - fhi) / (phi - hi);
+    if (sl > 0 && isfinite(sl)) L = fmax(L, lo + (t.target - flo) / sl - slack);
+    if (sh > 0 && isfinite(sh)) L = fmax(L, hi - (fhi - t.target) / sh - slack);
+  }
+  if (!(L >= lo && L < U && U <= hi)) {
+    L = lo;
+    U = hi;
+  }
+  const long long bL = __double_as_longlong(L), bU = __double_as_longlong(U);
+  if (bU - bL <= kQoiK - 3) {             // every double there, and one on either side
+    for (int j = 0; j < kQoiK; ++j) t.c[j] = from_bits(bL - 1 + j);
+  } else if (L == lo && U == hi) {        // nothing known: geometric steps, then even ones
+    for (int j = 0; j < kQoiK; ++j) {
+      const double u = double(j + 1) / double(kQoiK + 1);
+      t.c[j] = hi > 2.0 * lo ? lo * pow(hi / lo, u) : lo + (hi - lo) * u;
+    }
+  } else {                                // even steps over [L, U], and one point on either side of it
+    t.c[0] = lo + 0.5 * (L - lo);
+    for (int j = 0; j < kQoiK - 2; ++j) t.c[j + 1] = L + (U - L) * (double(j) / double(kQoiK - 3));
+    t.c[kQoiK - 1] = U + 0.5 * (hi - U);
+  }
+}
+
+// Folds a pass's sums (wavefront j: candidate j) and takes the next step of
+// the search; after the first pass also the sum and the largest share.
+__global__ __launch_bounds__(1024) void k_qoi_step(QoiScratch* q, int ng, int first) {
+  __shared__ double f[16], red[4][16];
+  if (!first && q->st.done) return;
+  const int lane = threadIdx.x & 63, j = threadIdx.x >> 6;
+  // sums over the workgroups, 16 wavefronts each a 16th of them
+  double v[4] = {0.0, 0.0, 0.0, 0.0};     // low, high, sum, max
+  for (int g = threadIdx.x; g < ng; g += 1024) {
+    v[0] += q->low[g];
+    v[1] += q->high[g];
+    if (first) {
+      v[2] += q->sum[g];
+      v[3] = fmax(v[3], q->max[g]);
+    }
+  }
+  double s = 0.0;
+  if (j < kQoiK)
+    for (int g = lane; g < ng; g += 64) s += q->f[g * kQoiK + j];
+  for (int off = 32; off > 0; off >>= 1) {
+    s += __shfl_down(s, off, 64);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] += __shfl_down(v[k], off, 64);
+    v[3] = fmax(v[3], __shfl_down(v[3], off, 64));
+  }
+  if (lane == 0) {
+    f[j] = s;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[k][j] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  double low = 0.0, high = 0.0, sum = 0.0, mx = 0.0;
+  for (int k = 0; k < 16; ++k) {
+    low += red[0][k];
+    high += red[1][k];
+    sum += red[2][k];
+    mx = fmax(mx, red[3][k]);
+  }
+  QoiState& t = q->st;
+  if (first) {
+    t.hi = mx;
+    if (!(sum > t.target)) {              // every cap fits: no width is set by the quantity
+      t.lambda = INFINITY;
+      t.done = 1;
+      return;
+    }
+    if (isinf(mx) || !(mx > t.lo)) {      // (no bracket to search)
+      t.lambda = t.lo;
+      t.done = 1;
+      return;
+    }
+    t.fhi = sum;
+  }
+  for (int k = 0; k < kQoiK; ++k) f[k] = f[k] + low + high * t.c[k];
+  qoi_narrow(t, f);
 }
 
 // Delta_i = 2 lambda / |s_i| where a_i > lambda (the quantity sets the
-// width), else the node's L-inf width; counts the former
+// width), else the node's L-inf width; counts the former.  Nothing is
+// written while the search has not ended.
 template <typename T>
-__global__ __launch_bounds__(NT) void k_qoi_final(QArgs a, const T* s, double lambda, double* delta,
+__global__ __launch_bounds__(NT) void k_qoi_final(QArgs a, const T* s, const QoiScratch* q, double* delta,
                                                   unsigned long long* count) {
   __shared__ double red[NT];
+  if (!q->st.done) return;
+  const double lambda = q->st.lambda;
   double c = 0.0;
-  for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < a.tot; i += gridDim.x * NT) {
-    const double ai = delta[i];
-    uint32_t z, y, x;
-    a.uf(i, z, y, x);
-    double del, inv;
-    node_delta(a, z, y, x, del, inv);
-    if (ai > lambda) {
-      delta[i] = 2.0 * lambda / fabs(double(s[i]));
-      c += 1.0;
-    } else {
-      delta[i] = del;
+  const uint32_t ntiles = (a.tot + NT * QU - 1) / (NT * QU);
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint32_t base = tile * (NT * QU) + threadIdx.x;
+    double sv[QU], del[QU];
+#pragma unroll
+    for (int k = 0; k < QU; ++k) {
+      const uint32_t i = base + k * NT;
+      sv[k] = del[k] = 0.0;
+      if (i < a.tot) {
+        uint32_t z, y, x;
+        a.uf(i, z, y, x);
+        double inv;
+        node_delta(a, z, y, x, del[k], inv);
+        sv[k] = fabs(double(s[i]));
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < QU; ++k) {
+      const uint32_t i = base + k * NT;
+      if (i >= a.tot) continue;
+      const bool set = sv[k] * del[k] * 0.5 > lambda;
+      delta[i] = set ? 2.0 * lambda / sv[k] : del[k];
+      if (set) c += 1.0;
     }
   }
   c = block_sum(c, red);
@@ -483,17 +735,13 @@ QPrep qprep_layout(bm_plan_s& p, const double* block_tol) {
   QPrep a{};
   a.flag = p.ws.counters + 2;
   const int64_t tot = p.ws.tol_off[p.L + 1];
-  double* bdel = p.ws.tolbuf + tot;
-  double* binv = p.ws.tolbuf + 2 * tot;
-  double* tg = p.ws.tolbuf + 3 * tot;     // tau_global
+  double* tg = p.ws.tolbuf + tot;         // tau_global
   const int64_t nlastb = p.L > 0 ? prod3(p.lv[p.L - 1].nb) : 0;
-  double* cls = tg + 8 + 2 * nlastb + 8;  // 27-class tables: level s at 54 tol_off[s], coarsest at 54 tot
+  double* cls = tg + 8;                   // 27-class tables: level s at 54 tol_off[s], coarsest at 54 tot
   for (int s = 1; s <= p.L; ++s) {
     const int64_t nbs = prod3(p.lv[s - 1].nb);
     const int64_t off = p.ws.tol_off[s];
     QTab& t = a.lv[s - 1];
-    t.del = bdel + off;
-    t.inv = binv + off;
     t.cdel = cls + 54 * off;
     t.cinv = cls + 54 * off + 27 * nbs;
     for (int d = 0; d < 3; ++d) t.nb[d] = p.lv[s - 1].nb[d];
@@ -501,8 +749,6 @@ QPrep qprep_layout(bm_plan_s& p, const double* block_tol) {
   if (p.L > 0 && p.M == 0) {
     // coarsest values (no gain), over the level-L blocks
     QTab& t = a.lv[kCoarseSlotHost];
-    t.del = tg + 8;
-    t.inv = tg + 8 + nlastb;
     t.cdel = cls + 54 * tot;
     t.cinv = cls + 54 * tot + 27 * nlastb;
     for (int d = 0; d < 3; ++d) t.nb[d] = p.lv[p.L - 1].nb[d];
@@ -601,12 +847,11 @@ __global__ void k_batch_propagate(const PrepField* F, const int64_t* first, int 
   }
 }
 
-// Per-block Delta, 1/Delta and 27-class tables of local level s (s = 0: the
+// The 27-class Delta and 1/Delta tables of local level s (s = 0: the
 // coarsest values of a field with M == 0) straight from the taus: rounding
 // of tau * kappa is monotone, so the smallest Delta over a set of blocks is
 // the smallest tau times kappa, and its reciprocal is the largest 1/Delta.
-// Task = (block, class), consecutive tasks write consecutive entries; class
-// 13 (interior) also writes the block's own entry.  Along an axis, class 0
+// Task = (block, class), consecutive tasks write consecutive entries.  Along an axis, class 0
 // (first face) takes the block and the one before, 1 the block alone, 2
 // (last face) the block and the one after.  32-bit index arithmetic (a
 // level has fewer than 2^32 / 27 blocks).
@@ -639,10 +884,6 @@ __device__ inline void table_task(const PrepField& P, int s, uint32_t i) {
   const double d = m * kap, iv = 1.0 / d;
   const_cast<double*>(T.cdel)[i] = d;
   const_cast<double*>(T.cinv)[i] = iv;
-  if (c == 13) {
-    const_cast<double*>(T.del)[blk] = d;
-    const_cast<double*>(T.inv)[blk] = iv;
-  }
 }
 
 __global__ void k_batch_tables(const PrepField* F, const int64_t* first, int nf, int64_t ntot, int s) {
@@ -720,7 +961,7 @@ PrepField prep_field(bm_plan_s& p, const double* block_tol, const QPrep& q) {
   if (p.L == 0) f.tau[0] = block_tol;
   f.kapc = (2.0 * (1.0 - eta)) * w[p.nlev];
   f.tab[kCoarseSlotHost] = q.lv[kCoarseSlotHost];
-  f.tg = p.ws.tolbuf + 3 * p.ws.tol_off[p.L + 1];
+  f.tg = p.ws.tolbuf + p.ws.tol_off[p.L + 1];
   f.q = p.ws.qparam;
   for (int s = 1; s <= p.nlev; ++s) f.kq[s - 1] = (2.0 * (1.0 - eta)) * w[s - 1] / p.lv[s - 1].gain;
   f.kq[p.nlev] = (2.0 * (1.0 - eta)) * w[p.nlev];
@@ -763,8 +1004,8 @@ QArgs prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool tables
   a.nested = p.cfg.nested;
   a.counters = p.ws.counters;
   for (int k = 0; k < 9; ++k) {
-    a.bdelta[k] = qp.lv[k].del;
-    a.binv[k] = qp.lv[k].inv;
+    a.cdel[k] = qp.lv[k].cdel;
+    a.cinv[k] = qp.lv[k].cinv;
     for (int d = 0; d < 3; ++d) a.nb[k][d] = uint32_t(qp.lv[k].nb[d]);
   }
   a.q = qp.q;
@@ -856,77 +1097,39 @@ int64_t qoi_deltas(bm_plan_s& p, const void* g, double tol_q, const double* bloc
   recompose_adjoint(p, g, p.ws.coeff, st);
   QArgs a = prepare(p, block_tol, st);
   const bool f32 = p.cfg.dtype == BM_F32;
-  // partial sums live in the plan's statistics scratch (3 x 8192 slots after
-  // the 16 counters): up to kQoiGroups x kQoiK partials, then 16 folded values
-  double* part = reinterpret_cast<double*>(p.ws.counters + 16);
-  double* fold = part + kQoiGroups * kQoiK;
-  static_assert(kQoiGroups * kQoiK + 16 <= 3 * 8192, "QoI partials exceed the statistics scratch");
+  auto* q = reinterpret_cast<QoiScratch*>(p.ws.counters + 16);
+  auto* cnt = reinterpret_cast<unsigned long long*>(p.ws.counters + 3);
   const unsigned gs = std::min<unsigned>(grid_for(int64_t(a.tot)), unsigned(kQoiGroups));
-  // a_i = |s_i| cap_i / 2 (held in delta until the last pass), their sum and max
+  hipLaunchKernelGGL(k_qoi_begin, dim3(1), dim3(64), 0, st, q, (1.0 - p.cfg.eta) * tol_q, double(a.tot), cnt);
+  // (the kept shares wait in delta until the last pass)
   if (f32)
     hipLaunchKernelGGL(k_qoi_shares<float>, dim3(gs), dim3(NT), 0, st, a, static_cast<const float*>(p.ws.coeff),
-                       delta, part);
+                       delta, q);
   else
     hipLaunchKernelGGL(k_qoi_shares<double>, dim3(gs), dim3(NT), 0, st, a, static_cast<const double*>(p.ws.coeff),
-                       delta, part);
-  hipLaunchKernelGGL(k_qoi_fold, dim3(1), dim3(NT), 0, st, part, int(gs), 2, 1, fold);
+                       delta, q);
+  hipLaunchKernelGGL(k_qoi_step, dim3(1), dim3(1024), 0, st, q, int(gs), 1);
   BM_HIP(hipGetLastError());
-  double sm[2];
-  BM_HIP(hipMemcpyAsync(sm, fold, sizeof(sm), hipMemcpyDeviceToHost, st));
-  BM_HIP(hipStreamSynchronize(st));
-  const double target = (1.0 - p.cfg.eta) * tol_q;
-  double lambda = INFINITY;   // every cap fits: no width is set by the quantity
-  if (sm[0] > target) {
-    // f(lambda) = sum min(a_i, lambda) rises from f(lo) <= tot lo = target to
-    // f(max a) = sum a > target; kQoiK candidates per pass narrow [lo, hi]
-    // (geometric steps while hi > 2 lo, then even steps) until no double lies
-    // between; lambda = lo keeps f(lambda) <= target, so the quantity's bound holds
-    double lo = target / double(a.tot), hi = sm[1];
-    for (int pass = 0; pass < 80 && hi > lo; ++pass) {
-      Cand c;
-      for (int j = 0; j < kQoiK; ++j) {
-        const double t = double(j + 1) / double(kQoiK + 1);
-        c.v[j] = hi > 2.0 * lo ? lo * std::pow(hi / lo, t) : lo + (hi - lo) * t;
-      }
-      hipLaunchKernelGGL(k_qoi_eval, dim3(unsigned(kQoiGroups)), dim3(NT), 0, st, static_cast<const double*>(delta),
-                         a.tot, c, part);
-      hipLaunchKernelGGL(k_qoi_fold, dim3(1), dim3(NT), 0, st, part, kQoiGroups, kQoiK, 0, fold);
-      BM_HIP(hipGetLastError());
-      double f[kQoiK];
-      BM_HIP(hipMemcpyAsync(f, fold, sizeof(f), hipMemcpyDeviceToHost, st));
-      BM_HIP(hipStreamSynchronize(st));
-      double nlo = lo, nhi = hi;
-      for (int j = 0; j < kQoiK; ++j) {
-        if (!(c.v[j] > lo && c.v[j] < hi)) continue;
-        if (f[j] <= target)
-          nlo = std::max(nlo, c.v[j]);
-        else
-          nhi = std::min(nhi, c.v[j]);
-      }
-      if (nlo == lo && nhi == hi) break;   // no candidate strictly inside: converged
-      if (nlo >= nhi) {                    // sums not monotone at rounding level
-        lo = nlo;
-        break;
-      }
-      lo = nlo;
-      hi = nhi;
+  const unsigned gq = qgroups(a.tot);
+  for (;;) {   // (a search that has not ended after its passes leaves delta to more of them)
+    for (int pass = 0; pass < kQoiPasses; ++pass) {
+      hipLaunchKernelGGL(k_qoi_eval, dim3(gs), dim3(NT), 0, st, delta, q);
+      hipLaunchKernelGGL(k_qoi_step, dim3(1), dim3(1024), 0, st, q, int(gs), 0);
     }
-    lambda = lo;
+    if (f32)
+      hipLaunchKernelGGL(k_qoi_final<float>, dim3(gq), dim3(NT), 0, st, a, static_cast<const float*>(p.ws.coeff), q,
+                         delta, cnt);
+    else
+      hipLaunchKernelGGL(k_qoi_final<double>, dim3(gq), dim3(NT), 0, st, a, static_cast<const double*>(p.ws.coeff), q,
+                         delta, cnt);
+    BM_HIP(hipGetLastError());
+    unsigned long long nset = 0;
+    int done = 0;
+    BM_HIP(hipMemcpyAsync(&nset, cnt, sizeof(nset), hipMemcpyDeviceToHost, st));
+    BM_HIP(hipMemcpyAsync(&done, &q->st.done, sizeof(done), hipMemcpyDeviceToHost, st));
+    BM_HIP(hipStreamSynchronize(st));
+    if (done) return int64_t(nset);
   }
-  auto* cnt = reinterpret_cast<unsigned long long*>(p.ws.counters + 3);
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, st, cnt);
-  const unsigned gq = grid_for(int64_t(a.tot));
-  if (f32)
-    hipLaunchKernelGGL(k_qoi_final<float>, dim3(gq), dim3(NT), 0, st, a, static_cast<const float*>(p.ws.coeff),
-                       lambda, delta, cnt);
-  else
-    hipLaunchKernelGGL(k_qoi_final<double>, dim3(gq), dim3(NT), 0, st, a, static_cast<const double*>(p.ws.coeff),
-                       lambda, delta, cnt);
-  BM_HIP(hipGetLastError());
-  unsigned long long nset = 0;
-  BM_HIP(hipMemcpyAsync(&nset, cnt, sizeof(nset), hipMemcpyDeviceToHost, st));
-  BM_HIP(hipStreamSynchronize(st));
-  return int64_t(nset);
 }
 
 void quantize_delta(bm_plan_s& p, const void* coeff, const double* delta, int32_t* codes, bm_qstats* stats,
@@ -940,9 +1143,10 @@ void quantize_delta(bm_plan_s& p, const void* coeff, const double* delta, int32_
   else
     hipLaunchKernelGGL(k_quantize<double>, dim3(g), dim3(NT), 0, st, a, static_cast<const double*>(coeff), codes,
                        partials);
-  hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(NT), 0, st, partials, int(g), p.ws.counters);
   BM_HIP(hipGetLastError());
   if (stats) {
+    hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(NT), 0, st, partials, int(g), p.ws.counters);
+    BM_HIP(hipGetLastError());
     int64_t h[4];
     BM_HIP(hipMemcpyAsync(h, p.ws.counters, sizeof(h), hipMemcpyDeviceToHost, st));
     BM_HIP(hipStreamSynchronize(st));
