@@ -18,12 +18,19 @@
 //
 // Block levels (Sec. IV-A, face-fixed): every block applies the transpose of
 // its own level to the values of the nodes it owns and adds the result into
-// every node it covers, shared faces included.  Blocks run in 8 passes by
-// the parity of their block coordinates: two blocks of one parity class never
-// share a node, so a pass needs no atomics, and the order in which shared
-// nodes are summed is fixed (the first class that covers a node writes it,
-// later classes add).  The transpose of the clamp padding adds the gradient
-// of every padded node into the node it copied.
+// every node it covers, shared faces included.  The order in which the up to
+// eight contributions of a shared node are summed is fixed: by the parity
+// class of the contributing block, even before odd, z slowest.  The blocks of
+// a slab (a few layers along z) leave their contributions, b^3 values each,
+// in a scratch array; a second launch sums them node by node in that order.
+// HBM traffic is what bounds a level, and a slab's scratch is kept small
+// enough to stay in the 256 MB Infinity Cache between its two launches.
+// (As 8 launches, one per parity class, that added into the grid in place,
+// every line was fetched and written several times: 384 x 384 x 256 FP32
+// 0.324 ms, now 0.18 ms.)  The transpose of the clamp padding adds the
+// gradient of every padded node into the node it copied.
+
+#include <algorithm>
 
 #include "block.h"
 #include "internal.h"
@@ -46,8 +53,17 @@ inline unsigned grid_for(int64_t tot) {
 // K_D^T on one line of a face-fixed block: s = Mc_I^{-1} y on the MI interior
 // coarse nodes (3 Mc_I = tridiag(1, 4, 1)), then the transposed interior rows
 // of P^T M ({1/12, 1/2, 5/6, 1/2, 1/12} around node 2J+2) spread s over the B
-// nodes of the line.
-template <typename T, int B>
+// nodes of the line.  SPLIT: the last term of a coarse node's sum is a product
+// rounded on its own (else contracted): the z spread of a recomposition's
+// transpose, whose bits set the widths of a quantity of interest and with
+// them its codes, has that rounding.
+template <typename T>
+__device__ inline T add_product(T acc, T a, T b) {
+#pragma clang fp contract(off)
+  return acc + a * b;
+}
+
+template <typename T, int B, bool SPLIT = false>
 __device__ inline void solve_spread(const T (&yv)[Geo<B>::MI], T (&out)[B]) {
   constexpr int MI = Geo<B>::MI;
   constexpr Pivots<MI> P{};
@@ -63,42 +79,15 @@ __device__ inline void solve_spread(const T (&yv)[Geo<B>::MI], T (&out)[B]) {
 #pragma unroll
   for (int J = 0; J < MI; ++J) {
     const int c = 2 * J + 2;
-    out[c - 2] += C2 * s[J];
+    if (SPLIT)
+      out[c - 2] = add_product(out[c - 2], C2, s[J]);
+    else
+      out[c - 2] += C2 * s[J];
     out[c - 1] += C1 * s[J];
     out[c] += C0 * s[J];
     out[c + 1] += C1 * s[J];
     out[c + 2] += C2 * s[J];
   }
-}
-
-// Blocks of one parity class: block coordinates b_k = 2 i_k + bit_k.
-struct ColorSet {
-  int64_t nb[3];          // blocks per axis
-  int bit[3];             // parity of this pass
-  int64_t nbc[3];         // blocks of this parity per axis
-  int64_t nblocks, nwg, per;
-};
-
-__device__ inline void color_block(const ColorSet& c, int64_t k, int64_t& bz, int64_t& by, int64_t& bx) {
-  const int64_t kx = k % c.nbc[2];
-  const int64_t t = k / c.nbc[2];
-  bx = 2 * kx + c.bit[2];
-  by = 2 * (t % c.nbc[1]) + c.bit[1];
-  bz = 2 * (t / c.nbc[1]) + c.bit[0];
-}
-
-// Is this block the first (lowest parity class) of the blocks covering a
-// node at local coordinate loc along one axis?  The only other candidate is
-// the neighbour across a face, whose parity differs.
-template <int B>
-__device__ inline bool first_on_axis(int loc, int64_t bk, int64_t nbk) {
-  const bool other = (loc == 0 && bk > 0) || (loc == B - 1 && bk + 1 < nbk);
-  return !other || (bk & 1) == 0;
-}
-
-template <typename T>
-__device__ inline void put(T* dst, T v, bool first) {
-  *dst = first ? v : *dst + v;
 }
 
 // Transposed passes x, y (LDS lines) and z (registers) of K_D^T:
@@ -128,12 +117,13 @@ __device__ inline void kd_transpose_xy(const T* Z, T* T2, T* T1, int tb, bool ac
 }
 
 // z part of P3^T at the even planes of one column: R[j] = v[2j] + (v[2j-1] + v[2j+1]) / 2
+// (skip: with v[2j] taken as zero)
 template <typename T, int B>
-__device__ inline void restrict_z(const T (&v)[B], T* R, int tb) {
+__device__ inline void restrict_z(const T (&v)[B], T* R, int tb, bool skip) {
   constexpr int MC = Geo<B>::MC, BB = Geo<B>::BB;
 #pragma unroll
   for (int j = 0; j < MC; ++j) {
-    T r = v[2 * j];
+    T r = skip ? T(0) : v[2 * j];
     if (j > 0 && j < MC - 1)
       r += T(0.5) * (v[2 * j - 1] + v[2 * j + 1]);
     else if (j > 0)
@@ -162,129 +152,158 @@ __device__ inline T gather_yx(const T* R, int j, int y, int x) {
   return acc + T(0.5) * side + T(0.25) * corner;
 }
 
+// One slab of block layers [k0, k1) of a level and its scratch: block
+// (bz, by, bx) leaves its B^3 contributions in slot (bz mod ring, by, bx).
+struct Slab {
+  int64_t nb[3];          // blocks per axis of the level
+  int64_t k0, nblocks;    // first layer, blocks of the slab
+  int64_t nwg, per;
+  uint32_t ring;
+  FastDiv fnb2, fnb1, fring;
+  __device__ inline int64_t slot(int64_t bz, int64_t by, int64_t bx) const {
+    const uint32_t r = uint32_t(bz) - fring.div(uint32_t(bz)) * ring;
+    return (int64_t(r) * nb[1] + by) * nb[2] + bx;
+  }
+};
+
 template <typename T>
-struct DecTArgs {
-  const T* gc;            // gradient of the coefficients, this level's view (strides cs)
+struct BlockTArgs {
+  // decomposition: gradient of the coefficients, this level's view, and of
+  // the coarse grid G^s (compact, dims cn)
+  const T* gc;
   int64_t cs[3];
-  const T* gcur;          // gradient of the coarse grid G^s (compact, dims cn)
+  const T* gcur;
   int64_t cn[3];
-  T* out;                 // gradient of G^{s-1} (dense, dims on)
-  int64_t on[3];
-  ColorSet c;
+  // recomposition: gradient of G^{s-1} (dense, dims in; zero at or beyond lim)
+  const T* gin;
+  int64_t in[3], lim[3];
+  T* part;                // contributions [slot][B][B][B]
+  Slab sl;
+};
+
+// The element `lane` past a base that all lanes of a workgroup share: the
+// base stays in scalar registers and every access of a column takes the same
+// 32-bit lane offset, where a pointer per lane and plane costs two vector
+// registers each.
+template <typename T>
+__device__ inline T* lane_at(T* base, uint32_t lane) {
+  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(base) + lane * uint32_t(sizeof(T)));
+}
+
+// A workgroup's block for this lane (several 9^3 blocks share a workgroup).
+template <int B>
+struct BlockLane {
+  static constexpr int NB = Geo<B>::NB1, BB = B * B, NT = (NB * BB + 63) / 64 * 64;
+  int bl, tb, y, x;
+  bool act, ecol;
+  int64_t bz, by, bx;
+  __device__ inline BlockLane(const Slab& sl, int64_t g) {
+    const int tid = threadIdx.x;
+    bl = NB == 1 ? 0 : tid / BB;          // (one block: its coordinates are scalars)
+    tb = tid - bl * BB;
+    act = NB == 1 ? tid < BB : bl < NB && g * NB + bl < sl.nblocks;
+    const int64_t blk = NB == 1 || act ? g * NB + bl : 0;
+    block_coords(uint32_t(blk), sl.fnb2, sl.fnb1, sl.nb, bz, by, bx);
+    bz += sl.k0;
+    if (NB > 1 && bl >= NB) bl = 0;
+    y = tb / B;
+    x = tb - (tb / B) * B;
+    ecol = ((y | x) & 1) == 0;
+  }
 };
 
 template <typename T, int B>
-__global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) void k_local_decompose_T(DecTArgs<T> a) {
+__global__ __launch_bounds__(BlockLane<B>::NT) void k_local_decompose_T(BlockTArgs<T> a) {
   using G = Geo<B, sizeof(T)>;
-  constexpr int BB = G::BB, MC = G::MC, MI = G::MI, NB = G::NB;
-  __shared__ T lds[NB * G::ADJ_LDS];
-  const int64_t g = xcd_group(blockIdx.x, a.c.per);
-  if (g >= a.c.nwg) return;
-  const int tid = threadIdx.x;
-  const int bl = tid / BB;
-  const int tb = tid - bl * BB;
-  const int64_t blk = g * NB + bl;
-  const bool act = bl < NB && blk < a.c.nblocks;
-  T* T1 = lds + (bl < NB ? bl : 0) * G::ADJ_LDS;     // [MI][B][B]
+  constexpr int BB = G::BB, MC = G::MC, MI = G::MI;
+  __shared__ T lds[BlockLane<B>::NB * G::ADJ_LDS];
+  const int64_t g = xcd_group(blockIdx.x, a.sl.per);
+  if (g >= a.sl.nwg) return;
+  const BlockLane<B> k(a.sl, g);
+  const int tb = k.tb, y = k.y, x = k.x;
+  const bool act = k.act, ecol = k.ecol;
+  T* T1 = lds + k.bl * G::ADJ_LDS;                   // [MI][B][B]
   T* T2 = T1 + MI * BB;                              // [MI][MI][B]
   T* Z = T2 + MI * MI * B;                           // [MI][MI][MI]
   T* R = T1;                                         // [MC][B][B], once T1 and T2 are dead
-  const int y = tb / B, x = tb - (tb / B) * B;
-  const bool ecol = ((y | x) & 1) == 0;
-  int64_t bz = 0, by = 0, bx = 0;
-  if (act) color_block(a.c, blk, bz, by, bx);
-  const int64_t oz = bz * (B - 1), gy = by * (B - 1) + y, gx = bx * (B - 1) + x;
+  const int64_t oz = k.bz * (B - 1), oy = k.by * (B - 1), ox = k.bx * (B - 1);
   // the gradient on the nodes this block owns (zero elsewhere)
-  T gv[B];
+  T v[B];
   if (act) {
-    const bool own_yx = (y < B - 1 || by == a.c.nb[1] - 1) && (x < B - 1 || bx == a.c.nb[2] - 1);
-    const bool lastz = bz == a.c.nb[0] - 1;
-    const T* col = a.gc + gy * a.cs[1] + gx * a.cs[2];
-    const T* ccol = a.gcur + (gy >> 1) * a.cn[2] + (gx >> 1);
+    const bool own_yx = (y < B - 1 || k.by == a.sl.nb[1] - 1) && (x < B - 1 || k.bx == a.sl.nb[2] - 1);
+    const bool lastz = k.bz == a.sl.nb[0] - 1;
     const int64_t cpl = a.cn[1] * a.cn[2];
+    const T* col = a.gc + oz * a.cs[0] + oy * a.cs[1] + ox * a.cs[2];
+    const T* ccol = a.gcur + (oz >> 1) * cpl + (oy >> 1) * a.cn[2] + (ox >> 1);
+    const uint32_t l = uint32_t(y * a.cs[1]) + uint32_t(x * a.cs[2]);
+    const uint32_t cl = uint32_t((y >> 1) * a.cn[2]) + uint32_t(x >> 1);
 #pragma unroll
     for (int z = 0; z < B; ++z) {
-      T v = T(0);
+      T w = T(0);
       if (own_yx && (z < B - 1 || lastz))
-        v = (ecol && !(z & 1)) ? ccol[((oz >> 1) + (z >> 1)) * cpl] : col[(oz + z) * a.cs[0]];
-      gv[z] = v;
+        w = (ecol && !(z & 1)) ? *lane_at(ccol + (z >> 1) * cpl, cl) : *lane_at(col + z * a.cs[0], l);
+      v[z] = w;
     }
     if (ecol && y >= 2 && y <= B - 3 && x >= 2 && x <= B - 3) {
       const int I = (y - 2) >> 1, K = (x - 2) >> 1;
 #pragma unroll
-      for (int J = 0; J < MI; ++J) Z[(J * MI + I) * MI + K] = gv[2 * J + 2];
+      for (int J = 0; J < MI; ++J) Z[(J * MI + I) * MI + K] = v[2 * J + 2];
     }
   }
   __syncthreads();
   kd_transpose_xy<T, B>(Z, T2, T1, tb, act);
-  T v[B];
   if (act) {
     T l[MI], t[B];
 #pragma unroll
     for (int J = 0; J < MI; ++J) l[J] = T1[J * BB + tb];
     solve_spread<T, B>(l, t);
+    // v = g + t on the fine nodes; the coarse ones keep cbar, which P3^T
+    // leaves out
 #pragma unroll
-    for (int z = 0; z < B; ++z) v[z] = (ecol && !(z & 1)) ? T(0) : gv[z] + t[z];
+    for (int z = 0; z < B; ++z)
+      if (!(ecol && !(z & 1))) v[z] = v[z] + t[z];
     // R aliases T1 (this column only, read above) and the dead T2 / Z
-    restrict_z<T, B>(v, R, tb);
+    restrict_z<T, B>(v, R, tb, ecol);
   }
   __syncthreads();
   if (act) {
     if (ecol) {
 #pragma unroll
-      for (int j = 0; j < MC; ++j) v[2 * j] = gv[2 * j] - gather_yx<T, B>(R, j, y, x);
+      for (int j = 0; j < MC; ++j) v[2 * j] = v[2 * j] - gather_yx<T, B>(R, j, y, x);
     }
-    const bool fy = first_on_axis<B>(y, by, a.c.nb[1]), fx = first_on_axis<B>(x, bx, a.c.nb[2]);
-    T* dst = a.out + gy * a.on[2] + gx;
-    const int64_t pl = a.on[1] * a.on[2];
+    T* dst = a.part + a.sl.slot(k.bz, k.by, k.bx) * (B * BB);
 #pragma unroll
-    for (int z = 0; z < B; ++z) put(dst + (oz + z) * pl, v[z], fy && fx && first_on_axis<B>(z, bz, a.c.nb[0]));
+    for (int z = 0; z < B; ++z) *lane_at(dst + z * BB, uint32_t(tb)) = v[z];
   }
 }
 
-template <typename T>
-struct RecTArgs {
-  const T* gin;           // gradient of G^{s-1} (dense, dims in); zero at or beyond lim
-  int64_t in[3], lim[3];
-  T* gc;                  // gradient of the coefficients, this level's view (strides cs)
-  int64_t cs[3];
-  T* gcur;                // gradient of the coarse grid G^s (compact, dims cn)
-  int64_t cn[3];
-  ColorSet c;
-};
-
 template <typename T, int B>
-__global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) void k_local_recompose_T(RecTArgs<T> a) {
+__global__ __launch_bounds__(BlockLane<B>::NT) void k_local_recompose_T(BlockTArgs<T> a) {
   using G = Geo<B, sizeof(T)>;
-  constexpr int BB = G::BB, MC = G::MC, MI = G::MI, NB = G::NB;
-  __shared__ T lds[NB * G::ADJ_LDS];
-  const int64_t g = xcd_group(blockIdx.x, a.c.per);
-  if (g >= a.c.nwg) return;
-  const int tid = threadIdx.x;
-  const int bl = tid / BB;
-  const int tb = tid - bl * BB;
-  const int64_t blk = g * NB + bl;
-  const bool act = bl < NB && blk < a.c.nblocks;
-  T* T1 = lds + (bl < NB ? bl : 0) * G::ADJ_LDS;
+  constexpr int BB = G::BB, MC = G::MC, MI = G::MI;
+  __shared__ T lds[BlockLane<B>::NB * G::ADJ_LDS];
+  const int64_t g = xcd_group(blockIdx.x, a.sl.per);
+  if (g >= a.sl.nwg) return;
+  const BlockLane<B> k(a.sl, g);
+  const int tb = k.tb, y = k.y, x = k.x;
+  const bool act = k.act, ecol = k.ecol;
+  T* T1 = lds + k.bl * G::ADJ_LDS;
   T* T2 = T1 + MI * BB;
   T* Z = T2 + MI * MI * B;
   T* R = T1;
-  const int y = tb / B, x = tb - (tb / B) * B;
-  const bool ecol = ((y | x) & 1) == 0;
-  int64_t bz = 0, by = 0, bx = 0;
-  if (act) color_block(a.c, blk, bz, by, bx);
-  const int64_t oz = bz * (B - 1), gy = by * (B - 1) + y, gx = bx * (B - 1) + x;
+  const int64_t oz = k.bz * (B - 1), oy = k.by * (B - 1), ox = k.bx * (B - 1);
   T gv[B];
   if (act) {
-    const bool own_yx = (y < B - 1 || by == a.c.nb[1] - 1) && (x < B - 1 || bx == a.c.nb[2] - 1) &&
-                        gy < a.lim[1] && gx < a.lim[2];
-    const bool lastz = bz == a.c.nb[0] - 1;
-    const T* col = a.gin + gy * a.in[2] + gx;
+    const bool own_yx = (y < B - 1 || k.by == a.sl.nb[1] - 1) && (x < B - 1 || k.bx == a.sl.nb[2] - 1) &&
+                        oy + y < a.lim[1] && ox + x < a.lim[2];
+    const bool lastz = k.bz == a.sl.nb[0] - 1;
     const int64_t pl = a.in[1] * a.in[2];
+    const T* col = a.gin + oz * pl + oy * a.in[2] + ox;
+    const uint32_t l = uint32_t(y * a.in[2]) + uint32_t(x);
 #pragma unroll
     for (int z = 0; z < B; ++z)
-      gv[z] = (own_yx && (z < B - 1 || lastz) && oz + z < a.lim[0]) ? col[(oz + z) * pl] : T(0);
-    restrict_z<T, B>(gv, R, tb);
+      gv[z] = (own_yx && (z < B - 1 || lastz) && oz + z < a.lim[0]) ? *lane_at(col + z * pl, l) : T(0);
+    restrict_z<T, B>(gv, R, tb, false);
   }
   __syncthreads();
   T rc[MC];
@@ -304,80 +323,246 @@ __global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) void k_local_recompose_T(R
     T l[MI], t[B];
 #pragma unroll
     for (int J = 0; J < MI; ++J) l[J] = T1[J * BB + tb];
-    solve_spread<T, B>(l, t);
-    const bool fy = first_on_axis<B>(y, by, a.c.nb[1]), fx = first_on_axis<B>(x, bx, a.c.nb[2]);
-    T* dst = a.gc + gy * a.cs[1] + gx * a.cs[2];
-    T* cdst = a.gcur + (gy >> 1) * a.cn[2] + (gx >> 1);
-    const int64_t cpl = a.cn[1] * a.cn[2];
+    solve_spread<T, B, true>(l, t);
+    T* dst = a.part + a.sl.slot(k.bz, k.by, k.bx) * (B * BB);
 #pragma unroll
-    for (int z = 0; z < B; ++z) {
-      const bool first = fy && fx && first_on_axis<B>(z, bz, a.c.nb[0]);
-      if (ecol && !(z & 1))
-        put(cdst + ((oz >> 1) + (z >> 1)) * cpl, rc[z >> 1], first);
+    for (int z = 0; z < B; ++z)
+      *lane_at(dst + z * BB, uint32_t(tb)) = (ecol && !(z & 1)) ? rc[z >> 1] : gv[z] - t[z];
+  }
+}
+
+// Where a node's summed gradient goes.  REC (coefficients of a recomposition
+// level): coarse nodes (every coordinate even) into the compact coarse grid
+// b, the others into the level view a.  Otherwise (gradient of G^{s-1}):
+// nodes below lim on every axis into a, the others into b (the padded grid,
+// at the padded strides; null: dropped).
+template <typename T>
+struct NodeOut {
+  T* a;
+  int64_t as[3];
+  T* b;
+  int64_t bs[3];
+  int64_t lim[3];
+};
+
+template <typename T>
+struct SumArgs {
+  const T* part;
+  Slab sl;
+  NodeOut<T> out;
+  uint32_t z0;            // first plane of the slab
+  uint32_t n1, n2;        // rows per plane, nodes per row
+  uint32_t ntask;         // wavefront tasks: kSumR rows of one plane, 64 nodes of each
+  Unflat32 uf;            // task -> (plane, group of rows, 64 nodes)
+};
+
+// the blocks along one axis that cover node c, even block first: block and
+// local coordinate; returns how many
+template <int B>
+__device__ inline int cover(uint32_t c, int64_t nb, int (&blk)[2], int (&loc)[2]) {
+  const uint32_t f = c / (B - 1);
+  const int l = int(c - f * (B - 1));
+  blk[0] = int(f);
+  loc[0] = l;
+  blk[1] = loc[1] = 0;
+  if (l != 0 || f == 0) return 1;
+  if (f == uint32_t(nb)) {
+    blk[0] = int(f) - 1;
+    loc[0] = B - 1;
+    return 1;
+  }
+  const bool odd = f & 1;                // block f is odd: block f-1 comes first
+  blk[0] = int(f) - odd;
+  loc[0] = odd ? B - 1 : 0;
+  blk[1] = int(f) - !odd;
+  loc[1] = odd ? 0 : B - 1;
+  return 2;
+}
+
+// A wavefront sums 64 nodes of kSumR neighbouring rows: what depends on z and
+// y (the blocks of a row, its place in the output) is scalar, what depends on
+// x is formed once for all rows, and the first contributions of all rows are
+// fetched before any other.  One lane per node with all of that per node was
+// bound by its index arithmetic: the 15 M nodes of a slab of 113 x 513 x 513
+// 53 us, 37 to 41 us this way.
+constexpr int kSumR = 4;
+
+template <typename T, int B, bool REC>
+__global__ __launch_bounds__(NT) void k_block_sum(SumArgs<T> a) {
+  constexpr int64_t B3 = int64_t(B) * B * B;
+  const uint32_t nwg = (a.ntask + NT / 64 - 1) / (NT / 64);
+  const uint32_t g = uint32_t(xcd_group(blockIdx.x, (nwg + 7) / 8));
+  const uint32_t w = __builtin_amdgcn_readfirstlane(g * (NT / 64) + (threadIdx.x >> 6));
+  if (w >= a.ntask) return;
+  uint32_t z, yg, seg;
+  a.uf(w, z, yg, seg);
+  z += a.z0;
+  const uint32_t x = seg * 64 + (threadIdx.x & 63);
+  const bool in = x < a.n2;
+  int bx[2], lx[2], by[2], ly[2], bz[2], lz[2];
+  const bool two = cover<B>(in ? x : 0, a.sl.nb[2], bx, lx) > 1;
+  const int64_t o0 = bx[0] * B3 + lx[0], o1 = bx[1] * B3 + lx[1];
+  const int nz = cover<B>(z, a.sl.nb[0], bz, lz);
+  // a row of a block row's contributions at node (0, iz-th z, iy-th y)
+  auto row = [&](int iz, int iy) {
+    return a.part + a.sl.slot(bz[iz], by[iy], 0) * B3 + (lz[iz] * B + ly[iy]) * B;
+  };
+  const uint32_t y0 = yg * kSumR;
+  T acc[kSumR], v1[kSumR];
+#pragma unroll
+  for (int r = 0; r < kSumR; ++r) {
+    acc[r] = v1[r] = T(0);
+    if (y0 + r >= a.n1) continue;
+    cover<B>(y0 + r, a.sl.nb[1], by, ly);
+    const T* p = row(0, 0);
+    if (in) acc[r] = p[o0];
+    if (in && two) v1[r] = p[o1];
+  }
+#pragma unroll
+  for (int r = 0; r < kSumR; ++r) {
+    const uint32_t y = y0 + r;
+    if (y >= a.n1) continue;
+    const int ny = cover<B>(y, a.sl.nb[1], by, ly);
+    if (two) acc[r] += v1[r];
+    auto add = [&](int iz, int iy) {
+      const T* p = row(iz, iy);
+      if (in) {
+        acc[r] += p[o0];
+        if (two) acc[r] += p[o1];
+      }
+    };
+    if (ny > 1) add(0, 1);
+    if (nz > 1) {
+      add(1, 0);
+      if (ny > 1) add(1, 1);
+    }
+    if (!in) continue;
+    const NodeOut<T>& o = a.out;
+    if (REC) {
+      if (((z | y) & 1) == 0 && (x & 1) == 0)
+        o.b[(z >> 1) * o.bs[0] + (y >> 1) * o.bs[1] + (x >> 1)] = acc[r];
       else
-        put(dst + (oz + z) * a.cs[0], gv[z] - t[z], first);
+        o.a[z * o.as[0] + y * o.as[1] + x * o.as[2]] = acc[r];
+    } else if (z < o.lim[0] && y < o.lim[1] && x < o.lim[2]) {
+      o.a[z * o.as[0] + y * o.as[1] + x] = acc[r];
+    } else if (o.b) {
+      o.b[z * o.bs[0] + y * o.bs[1] + x] = acc[r];
     }
   }
 }
 
-ColorSet color_set(const Level& L, int color, int nb_per_wg) {
-  ColorSet c{};
-  c.nblocks = 1;
-  for (int k = 0; k < 3; ++k) {
-    c.nb[k] = L.nb[k];
-    c.bit[k] = (color >> (2 - k)) & 1;
-    c.nbc[k] = (L.nb[k] - c.bit[k] + 1) / 2;
-    c.nblocks *= c.nbc[k];
+// Bytes of scratch per slab: half the Infinity Cache, so that the second
+// launch finds it there (and the plan's memory does not grow with the grid).
+constexpr size_t kSlabBytes = size_t(128) << 20;
+
+// Layers per slab and layers in the scratch (one more than a slab, for the
+// last plane of the slab before, unless one slab takes the whole level).
+void slab_layers(const Level& L, size_t esize, int64_t& layers, int64_t& ring) {
+  const size_t layer = size_t(L.nb[1]) * L.nb[2] * L.b * L.b * L.b * esize;
+  int64_t fit = int64_t(kSlabBytes / layer);
+  if (fit >= L.nb[0]) {
+    layers = ring = L.nb[0];
+    return;
   }
-  c.nwg = (c.nblocks + nb_per_wg - 1) / nb_per_wg;
-  c.per = (c.nwg + 7) / 8;
-  return c;
+  fit = std::max<int64_t>(fit - 1, 1);
+  const int64_t slabs = (L.nb[0] + fit - 1) / fit;
+  layers = (L.nb[0] + slabs - 1) / slabs;
+  ring = layers + 1;
+}
+
+// Runs a level slab by slab: blocks(slab) launches what leaves the
+// contributions of the slab's blocks in the plan's scratch (kept; sized for
+// the largest level on first use), then its nodes are summed.
+template <typename T, int B, bool REC, typename F>
+void run_slabs(bm_plan_s& p, int s, const NodeOut<T>& out, int per_wg, hipStream_t st, F blocks) {
+  const Level& L = p.lv[s - 1];
+  if (!p.ws.contrib) {
+    size_t need = 0;
+    for (const Level& l : p.lv)
+      if (l.local) {
+        int64_t n, r;
+        slab_layers(l, p.esize, n, r);
+        need = std::max(need, size_t(r) * l.nb[1] * l.nb[2] * l.b * l.b * l.b * p.esize);
+      }
+    plan_alloc_late(p, &p.ws.contrib, need);
+  }
+  T* part = static_cast<T*>(p.ws.contrib);
+  int64_t layers, ring;
+  slab_layers(L, p.esize, layers, ring);
+  if (ring * L.nb[1] * L.nb[2] >= (int64_t(1) << 31)) fail(BM_EUNSUPPORTED, "too many blocks");
+  for (int64_t k0 = 0; k0 < L.nb[0]; k0 += layers) {
+    const int64_t k1 = std::min(L.nb[0], k0 + layers);
+    Slab sl{};
+    for (int k = 0; k < 3; ++k) sl.nb[k] = L.nb[k];
+    sl.k0 = k0;
+    sl.nblocks = (k1 - k0) * L.nb[1] * L.nb[2];
+    sl.nwg = (sl.nblocks + per_wg - 1) / per_wg;
+    sl.per = (sl.nwg + 7) / 8;
+    sl.ring = uint32_t(ring);
+    sl.fring = FastDiv(uint32_t(ring));
+    sl.fnb2 = FastDiv(uint32_t(L.nb[2]));
+    sl.fnb1 = FastDiv(uint32_t(L.nb[1]));
+    blocks(sl, part);
+    BM_HIP(hipGetLastError());
+    // planes of the slab; the far face goes with the last one
+    const int64_t z0 = k0 * (B - 1), z1 = k1 == L.nb[0] ? L.n[0] : k1 * (B - 1);
+    const int64_t ngy = (L.n[1] + kSumR - 1) / kSumR, nseg = (L.n[2] + 63) / 64, ntask = (z1 - z0) * ngy * nseg;
+    if (ntask >= (int64_t(1) << 31)) fail(BM_EUNSUPPORTED, "grid planes too large");
+    SumArgs<T> a{part, sl, out, uint32_t(z0), uint32_t(L.n[1]), uint32_t(L.n[2]), uint32_t(ntask),
+                 Unflat32(ngy, nseg)};
+    const int64_t nwg = (ntask + NT / 64 - 1) / (NT / 64);
+    hipLaunchKernelGGL((k_block_sum<T, B, REC>), dim3(unsigned((nwg + 7) / 8 * 8)), dim3(NT), 0, st, a);
+    BM_HIP(hipGetLastError());
+  }
+}
+
+// the outputs of a recomposition level's transpose
+template <typename T>
+NodeOut<T> rec_out(bm_plan_s& p, int s, void* gcoeff) {
+  const Level& L = p.lv[s - 1];
+  const View3 cv = level_view(p, s, gcoeff);
+  NodeOut<T> o{};
+  o.a = static_cast<T*>(cv.ptr);
+  o.b = static_cast<T*>(p.ws.grid[s]);
+  for (int k = 0; k < 3; ++k) o.as[k] = cv.s[k];
+  o.bs[0] = L.m[1] * L.m[2];
+  o.bs[1] = L.m[2];
+  o.bs[2] = 1;
+  return o;
 }
 
 template <typename T, int B>
-void launch_local_dec_T(const bm_plan_s& p, int s, const void* gcoeff, void* out, hipStream_t st) {
-  using G = Geo<B, sizeof(T)>;
+void launch_local_dec_T(bm_plan_s& p, int s, const void* gcoeff, const NodeOut<T>& out, hipStream_t st) {
   const Level& L = p.lv[s - 1];
-  DecTArgs<T> a{};
+  BlockTArgs<T> a{};
   const View3 cv = level_view(p, s, const_cast<void*>(gcoeff));
   a.gc = static_cast<const T*>(cv.ptr);
   a.gcur = static_cast<const T*>(p.ws.grid[s]);
-  a.out = static_cast<T*>(out);
   for (int k = 0; k < 3; ++k) {
     a.cs[k] = cv.s[k];
     a.cn[k] = L.m[k];
-    a.on[k] = L.n[k];
   }
-  for (int color = 0; color < 8; ++color) {
-    a.c = color_set(L, color, G::NB);
-    if (a.c.nblocks == 0) continue;
-    hipLaunchKernelGGL((k_local_decompose_T<T, B>), dim3(unsigned(8 * a.c.per)), dim3(G::NT), 0, st, a);
-    BM_HIP(hipGetLastError());
-  }
+  run_slabs<T, B, false>(p, s, out, BlockLane<B>::NB, st, [&](const Slab& sl, T* part) {
+    a.sl = sl;
+    a.part = part;
+    hipLaunchKernelGGL((k_local_decompose_T<T, B>), dim3(unsigned(8 * sl.per)), dim3(BlockLane<B>::NT), 0, st, a);
+  });
 }
 
 template <typename T, int B>
-void launch_local_rec_T(const bm_plan_s& p, int s, const void* gin, const int64_t in[3], const int64_t lim[3],
+void launch_local_rec_T(bm_plan_s& p, int s, const void* gin, const int64_t in[3], const int64_t lim[3],
                         void* gcoeff, hipStream_t st) {
-  using G = Geo<B, sizeof(T)>;
-  const Level& L = p.lv[s - 1];
-  RecTArgs<T> a{};
-  const View3 cv = level_view(p, s, gcoeff);
+  BlockTArgs<T> a{};
   a.gin = static_cast<const T*>(gin);
-  a.gc = static_cast<T*>(cv.ptr);
-  a.gcur = static_cast<T*>(p.ws.grid[s]);
   for (int k = 0; k < 3; ++k) {
     a.in[k] = in[k];
     a.lim[k] = lim[k];
-    a.cs[k] = cv.s[k];
-    a.cn[k] = L.m[k];
   }
-  for (int color = 0; color < 8; ++color) {
-    a.c = color_set(L, color, G::NB);
-    if (a.c.nblocks == 0) continue;
-    hipLaunchKernelGGL((k_local_recompose_T<T, B>), dim3(unsigned(8 * a.c.per)), dim3(G::NT), 0, st, a);
-    BM_HIP(hipGetLastError());
-  }
+  run_slabs<T, B, true>(p, s, rec_out<T>(p, s, gcoeff), BlockLane<B>::NB, st, [&](const Slab& sl, T* part) {
+    a.sl = sl;
+    a.part = part;
+    hipLaunchKernelGGL((k_local_recompose_T<T, B>), dim3(unsigned(8 * sl.per)), dim3(BlockLane<B>::NT), 0, st, a);
+  });
 }
 
 // ------------------------------------------------------- 33^3 block levels
@@ -387,8 +572,7 @@ void launch_local_rec_T(const bm_plan_s& p, int s, const void* gin, const int64_
 // columns next to the cut (16 and 18) has both neighbours; the first half
 // stores x <= 16, the second x >= 17.  The transposed correction runs as an
 // x spread per block into a scratch array (the plan's line-pass buffer),
-// then the y and z spreads per half.  Halves of one colour class write
-// disjoint nodes, so the colour passes keep the summation order fixed.
+// then the y and z spreads per half.  Halves of a block store disjoint nodes.
 namespace w33 {
 constexpr int B = 33, MC = 17, MI = 15, HW = 18, NCOL = B * HW, NT = 640, T2B = MI * MI * B, ZB = MI * MI * MI;
 __device__ inline int x0(int h) { return h ? 15 : 0; }
@@ -397,19 +581,25 @@ __device__ inline bool stores(int h, int x) { return h ? x >= 17 : x <= 16; }
 
 template <typename T>
 struct W33Args {
-  const T* gc;            // decompose: gradient of the coefficients (level view); recompose: output
+  const T* gc;            // decompose: gradient of the coefficients (level view)
   int64_t cs[3];
-  const T* gcur;          // gradient of the coarse grid G^s (compact, dims cn); recompose: output
+  const T* gcur;          // decompose: gradient of the coarse grid G^s (compact, dims cn)
   int64_t cn[3];
-  T* out;                 // decompose: gradient of G^{s-1} (dense, dims on)
-  int64_t on[3];
   const T* gin;           // recompose: gradient of G^{s-1} (dense, dims in, zero at or beyond lim)
   int64_t in[3], lim[3];
   T* zs;                  // recompose: interior coarse gradients per block [ZB]
   T* t2;                  // x-spread result per block [MI][MI][B]
   int64_t nb[3];
-  ColorSet c;
+  T* part;                // contributions [slot][B][B][B]
+  Slab sl;
 };
+
+// block (bz, by, bx) of index k in the slab
+template <typename T>
+__device__ inline void slab_block(const W33Args<T>& a, int64_t k, int64_t& bz, int64_t& by, int64_t& bx) {
+  block_coords(uint32_t(k), a.sl.fnb2, a.sl.fnb1, a.nb, bz, by, bx);
+  bz += a.sl.k0;
+}
 
 // z part of P3^T at the even planes of a column of 33 values
 template <typename T>
@@ -450,7 +640,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_w33_spread_x(W33Args<T> a, int from_zs) {
   using namespace w33;
   __shared__ T Z[ZB];
-  const int64_t blk = blockIdx.x;
+  const int64_t blk = blockIdx.x + (from_zs ? a.sl.k0 * a.nb[1] * a.nb[2] : 0);   // zs: the slab's blocks
   const int64_t bx = blk % a.nb[2], t = blk / a.nb[2], by = t % a.nb[1], bz = t / a.nb[1];
   const int64_t c0 = bz * (MC - 1), c1 = by * (MC - 1), c2 = bx * (MC - 1), cpl = a.cn[1] * a.cn[2];
   for (int i = threadIdx.x; i < ZB; i += 256) {
@@ -487,16 +677,16 @@ __device__ inline void w33_spread_y(const W33Args<T>& a, int64_t blk, int h, T* 
 }
 
 // Transpose of a decomposition level, per half: v = g + K^T cbar on the
-// fine nodes, then cbar - P3^T v on the coarse nodes, added into G^{s-1}.
+// fine nodes, then cbar - P3^T v on the coarse nodes.
 template <typename T>
 __global__ __launch_bounds__(w33::NT) void k_w33_dec_T(W33Args<T> a) {
   using namespace w33;
   __shared__ T lds[MC * B * HW];       // T1 [MI][B][HW], then R [MC][B][HW]
   const int64_t g = blockIdx.x;
-  if (g >= 2 * a.c.nblocks) return;
+  if (g >= 2 * a.sl.nblocks) return;
   const int h = int(g & 1);
   int64_t bz, by, bx;
-  color_block(a.c, g >> 1, bz, by, bx);
+  slab_block(a, g >> 1, bz, by, bx);
   const int64_t blk = (bz * a.nb[1] + by) * a.nb[2] + bx;
   w33_spread_y(a, blk, h, lds);
   __syncthreads();
@@ -537,11 +727,9 @@ __global__ __launch_bounds__(w33::NT) void k_w33_dec_T(W33Args<T> a) {
 #pragma unroll
       for (int j = 0; j < MC; ++j) v[2 * j] = gv[2 * j] - gather33<T>(lds, j, y, xl, x);
     }
-    const bool fy = first_on_axis<B>(y, by, a.c.nb[1]), fx = first_on_axis<B>(x, bx, a.c.nb[2]);
-    T* dst = a.out + gy * a.on[2] + gx;
-    const int64_t pl = a.on[1] * a.on[2];
+    T* dst = a.part + a.sl.slot(bz, by, bx) * (B * B * B) + y * B + x;
 #pragma unroll
-    for (int z = 0; z < B; ++z) put(dst + (oz + z) * pl, v[z], fy && fx && first_on_axis<B>(z, bz, a.c.nb[0]));
+    for (int z = 0; z < B; ++z) dst[z * B * B] = v[z];
   }
 }
 
@@ -562,17 +750,17 @@ __device__ inline void w33_owned_column(const W33Args<T>& a, int64_t bz, int64_t
 }
 
 // Transpose of a recomposition level, first part per half: r = P3^T g at
-// the coarse nodes, added into the coarse grid's gradient; the interior ones
+// the coarse nodes, part of the block's contributions; the interior ones
 // also go to zs for the transposed correction.
 template <typename T>
 __global__ __launch_bounds__(w33::NT) void k_w33_rec_T_coarse(W33Args<T> a) {
   using namespace w33;
   __shared__ T R[MC * B * HW];
   const int64_t g = blockIdx.x;
-  if (g >= 2 * a.c.nblocks) return;
+  if (g >= 2 * a.sl.nblocks) return;
   const int h = int(g & 1);
   int64_t bz, by, bx;
-  color_block(a.c, g >> 1, bz, by, bx);
+  slab_block(a, g >> 1, bz, by, bx);
   const int64_t blk = (bz * a.nb[1] + by) * a.nb[2] + bx;
   const int tid = threadIdx.x;
   const bool act = tid < NCOL;
@@ -586,15 +774,12 @@ __global__ __launch_bounds__(w33::NT) void k_w33_rec_T_coarse(W33Args<T> a) {
   }
   __syncthreads();
   if (act && ecol && stores(h, x)) {
-    const bool fy = first_on_axis<B>(y, by, a.c.nb[1]), fx = first_on_axis<B>(x, bx, a.c.nb[2]);
-    const int64_t oz = bz * (B - 1), gy = by * (B - 1) + y, gx = bx * (B - 1) + x;
-    T* cdst = const_cast<T*>(a.gcur) + (gy >> 1) * a.cn[2] + (gx >> 1);
-    const int64_t cpl = a.cn[1] * a.cn[2];
+    T* dst = a.part + a.sl.slot(bz, by, bx) * (B * B * B) + y * B + x;
     const bool icol = y >= 2 && y <= B - 3 && x >= 2 && x <= B - 3;
 #pragma unroll
     for (int j = 0; j < MC; ++j) {
       const T rc = gather33<T>(R, j, y, xl, x);
-      put(cdst + ((oz >> 1) + j) * cpl, rc, fy && fx && first_on_axis<B>(2 * j, bz, a.c.nb[0]));
+      dst[2 * j * B * B] = rc;
       if (icol && j >= 1 && j <= MC - 2) a.zs[blk * ZB + ((j - 1) * MI + ((y - 2) >> 1)) * MI + ((x - 2) >> 1)] = rc;
     }
   }
@@ -607,10 +792,10 @@ __global__ __launch_bounds__(w33::NT) void k_w33_rec_T_fine(W33Args<T> a) {
   using namespace w33;
   __shared__ T T1[MI * B * HW];
   const int64_t g = blockIdx.x;
-  if (g >= 2 * a.c.nblocks) return;
+  if (g >= 2 * a.sl.nblocks) return;
   const int h = int(g & 1);
   int64_t bz, by, bx;
-  color_block(a.c, g >> 1, bz, by, bx);
+  slab_block(a, g >> 1, bz, by, bx);
   const int64_t blk = (bz * a.nb[1] + by) * a.nb[2] + bx;
   w33_spread_y(a, blk, h, T1);
   __syncthreads();
@@ -624,14 +809,10 @@ __global__ __launch_bounds__(w33::NT) void k_w33_rec_T_fine(W33Args<T> a) {
 #pragma unroll
   for (int J = 0; J < MI; ++J) l[J] = T1[(J * B + y) * HW + xl];
   solve_spread<T, B>(l, t);
-  const bool fy = first_on_axis<B>(y, by, a.c.nb[1]), fx = first_on_axis<B>(x, bx, a.c.nb[2]);
-  const int64_t oz = bz * (B - 1), gy = by * (B - 1) + y, gx = bx * (B - 1) + x;
-  T* dst = const_cast<T*>(a.gc) + gy * a.cs[1] + gx * a.cs[2];
+  T* dst = a.part + a.sl.slot(bz, by, bx) * (B * B * B) + y * B + x;
 #pragma unroll
-  for (int z = 0; z < B; ++z) {
-    if (ecol && !(z & 1)) continue;    // coarse nodes: the coarse part above
-    put(dst + (oz + z) * a.cs[0], gv[z] - t[z], fy && fx && first_on_axis<B>(z, bz, a.c.nb[0]));
-  }
+  for (int z = 0; z < B; ++z)
+    if (!(ecol && !(z & 1))) dst[z * B * B] = gv[z] - t[z];   // coarse nodes: the coarse part above
 }
 
 template <typename T>
@@ -650,61 +831,42 @@ W33Args<T> w33_args(const bm_plan_s& p, int s) {
 }
 
 template <typename T>
-void launch_w33_dec_T(const bm_plan_s& p, int s, const void* gcoeff, void* out, hipStream_t st) {
+void launch_w33_dec_T(bm_plan_s& p, int s, const void* gcoeff, const NodeOut<T>& out, hipStream_t st) {
   const Level& L = p.lv[s - 1];
   W33Args<T> a = w33_args<T>(p, s);
   const View3 cv = level_view(p, s, const_cast<void*>(gcoeff));
   a.gc = static_cast<const T*>(cv.ptr);
   a.gcur = static_cast<const T*>(p.ws.grid[s]);
-  a.out = static_cast<T*>(out);
-  for (int k = 0; k < 3; ++k) {
-    a.cs[k] = cv.s[k];
-    a.on[k] = L.n[k];
-  }
-  const int64_t nblocks = L.nb[0] * L.nb[1] * L.nb[2];
-  hipLaunchKernelGGL(k_w33_spread_x<T>, dim3(unsigned(nblocks)), dim3(256), 0, st, a, 0);
+  for (int k = 0; k < 3; ++k) a.cs[k] = cv.s[k];
+  hipLaunchKernelGGL(k_w33_spread_x<T>, dim3(unsigned(L.nb[0] * L.nb[1] * L.nb[2])), dim3(256), 0, st, a, 0);
   BM_HIP(hipGetLastError());
-  for (int color = 0; color < 8; ++color) {
-    a.c = color_set(L, color, 1);
-    if (a.c.nblocks == 0) continue;
-    hipLaunchKernelGGL(k_w33_dec_T<T>, dim3(unsigned(2 * a.c.nblocks)), dim3(w33::NT), 0, st, a);
-    BM_HIP(hipGetLastError());
-  }
+  run_slabs<T, w33::B, false>(p, s, out, 1, st, [&](const Slab& sl, T* part) {
+    a.sl = sl;
+    a.part = part;
+    hipLaunchKernelGGL(k_w33_dec_T<T>, dim3(unsigned(2 * sl.nblocks)), dim3(w33::NT), 0, st, a);
+  });
 }
 
 template <typename T>
-void launch_w33_rec_T(const bm_plan_s& p, int s, const void* gin, const int64_t in[3], const int64_t lim[3],
+void launch_w33_rec_T(bm_plan_s& p, int s, const void* gin, const int64_t in[3], const int64_t lim[3],
                       void* gcoeff, hipStream_t st) {
-  const Level& L = p.lv[s - 1];
   W33Args<T> a = w33_args<T>(p, s);
-  const View3 cv = level_view(p, s, gcoeff);
-  a.gc = static_cast<const T*>(cv.ptr);
-  a.gcur = static_cast<const T*>(p.ws.grid[s]);
   a.gin = static_cast<const T*>(gin);
   for (int k = 0; k < 3; ++k) {
-    a.cs[k] = cv.s[k];
     a.in[k] = in[k];
     a.lim[k] = lim[k];
   }
-  const int64_t nblocks = L.nb[0] * L.nb[1] * L.nb[2];
-  for (int color = 0; color < 8; ++color) {
-    a.c = color_set(L, color, 1);
-    if (a.c.nblocks == 0) continue;
-    hipLaunchKernelGGL(k_w33_rec_T_coarse<T>, dim3(unsigned(2 * a.c.nblocks)), dim3(w33::NT), 0, st, a);
-    BM_HIP(hipGetLastError());
-  }
-  hipLaunchKernelGGL(k_w33_spread_x<T>, dim3(unsigned(nblocks)), dim3(256), 0, st, a, 1);
-  BM_HIP(hipGetLastError());
-  for (int color = 0; color < 8; ++color) {
-    a.c = color_set(L, color, 1);
-    if (a.c.nblocks == 0) continue;
-    hipLaunchKernelGGL(k_w33_rec_T_fine<T>, dim3(unsigned(2 * a.c.nblocks)), dim3(w33::NT), 0, st, a);
-    BM_HIP(hipGetLastError());
-  }
+  run_slabs<T, w33::B, true>(p, s, rec_out<T>(p, s, gcoeff), 1, st, [&](const Slab& sl, T* part) {
+    a.sl = sl;
+    a.part = part;
+    hipLaunchKernelGGL(k_w33_rec_T_coarse<T>, dim3(unsigned(2 * sl.nblocks)), dim3(w33::NT), 0, st, a);
+    hipLaunchKernelGGL(k_w33_spread_x<T>, dim3(unsigned(sl.nblocks)), dim3(256), 0, st, a, 1);
+    hipLaunchKernelGGL(k_w33_rec_T_fine<T>, dim3(unsigned(2 * sl.nblocks)), dim3(w33::NT), 0, st, a);
+  });
 }
 
 template <typename T>
-void local_dec_T(const bm_plan_s& p, int s, const void* gcoeff, void* out, hipStream_t st) {
+void local_dec_T(bm_plan_s& p, int s, const void* gcoeff, const NodeOut<T>& out, hipStream_t st) {
   if (p.lv[s - 1].b == 33)
     launch_w33_dec_T<T>(p, s, gcoeff, out, st);
   else if (p.lv[s - 1].b == 9)
@@ -714,7 +876,7 @@ void local_dec_T(const bm_plan_s& p, int s, const void* gcoeff, void* out, hipSt
 }
 
 template <typename T>
-void local_rec_T(const bm_plan_s& p, int s, const void* gin, const int64_t in[3], const int64_t lim[3], void* gcoeff,
+void local_rec_T(bm_plan_s& p, int s, const void* gin, const int64_t in[3], const int64_t lim[3], void* gcoeff,
                  hipStream_t st) {
   if (p.lv[s - 1].b == 33)
     launch_w33_rec_T<T>(p, s, gin, in, lim, gcoeff, st);
@@ -880,23 +1042,27 @@ __global__ __launch_bounds__(NT) void k_restrict_T(RestrArgs<T> a) {
     a.uf(uint32_t(i), uz, uy, ux);
     const int64_t cz = uz, cy = uy, cx = ux;
     const int64_t fz = a.cm[0] ? 2 * cz : cz, fy = a.cm[1] ? 2 * cy : cy, fx = a.cm[2] ? 2 * cx : cx;
-    T acc = T(0);
-    for (int dz = -a.cm[0]; dz <= a.cm[0]; ++dz) {
-      const int64_t zz = fz + dz;
-      if (zz < 0 || zz >= a.n[0]) continue;
-      for (int dy = -a.cm[1]; dy <= a.cm[1]; ++dy) {
-        const int64_t yy = fy + dy;
-        if (yy < 0 || yy >= a.n[1]) continue;
-        for (int dx = -a.cm[2]; dx <= a.cm[2]; ++dx) {
-          const int64_t xx = fx + dx;
-          if (xx < 0 || xx >= a.n[2]) continue;
-          if (!a.self && dz == 0 && dy == 0 && dx == 0) continue;
-          const T w = T((dz ? 0.5 : 1.0) * (dy ? 0.5 : 1.0) * (dx ? 0.5 : 1.0));
-          acc += w * a.src[(zz * a.n[1] + yy) * a.n[2] + xx];
-        }
-      }
+    // all (up to 27) neighbours are fetched before the sum, which takes them
+    // in the order z, y, x (weights are powers of two: exact products; an
+    // absent neighbour adds +0, which changes nothing)
+    T v[27];
+#pragma unroll
+    for (int t = 0; t < 27; ++t) {
+      const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
+      const int64_t zz = fz + dz, yy = fy + dy, xx = fx + dx;
+      const bool in = (dz == 0 || (a.cm[0] && zz >= 0 && zz < a.n[0])) &&
+                      (dy == 0 || (a.cm[1] && yy >= 0 && yy < a.n[1])) &&
+                      (dx == 0 || (a.cm[2] && xx >= 0 && xx < a.n[2])) && (t != 13 || a.self);
+      v[t] = in ? a.src[(zz * a.n[1] + yy) * a.n[2] + xx] : T(0);
     }
-    a.out[cz * a.os[0] + cy * a.os[1] + cx * a.os[2]] = a.cbar ? a.cbar[i] - acc : acc;
+    const T cb = a.cbar ? a.cbar[i] : T(0);
+    T acc = T(0);
+#pragma unroll
+    for (int t = 0; t < 27; ++t) {
+      const int d = (t / 9 != 1) + ((t / 3) % 3 != 1) + (t % 3 != 1);
+      acc += T(d == 0 ? 1.0 : d == 1 ? 0.5 : d == 2 ? 0.25 : 0.125) * v[t];
+    }
+    a.out[cz * a.os[0] + cy * a.os[1] + cx * a.os[2]] = a.cbar ? cb - acc : acc;
   }
 }
 
@@ -971,25 +1137,119 @@ void global_rec_T(bm_plan_s& p, int s, const void* gin, void* gcoeff, hipStream_
   apply_K3_T<T>(p, s, level_view(p, s, gcoeff), &base, T(-1), false, st);
 }
 
-// transpose of the padding: gx = sum of the padded gradient over the padded
-// nodes that read each logical node (clamp), or the crop (zero fill)
+// Transpose of the clamp padding at the end nodes of the padded axes: gx =
+// sum of the padded gradient over the padded nodes that copied the node.
+// One lane per node on a face (its terms along one axis), one wavefront per
+// node on an edge or the corner (up to the product of three axes' terms: as
+// one lane's loop the corner of 100 x 500 x 500 took 0.32 ms by itself).
+constexpr int kUT = 8;    // loads in flight per lane
+
 template <typename T>
-__global__ __launch_bounds__(NT) void k_unpad_T(const T* gp, int64_t p0, int64_t p1, int64_t p2, T* gx, int64_t n0,
-                                                int64_t n1, int64_t n2, Unflat32 uf, int zero) {
-  const int64_t tot = n0 * n1 * n2;
-  for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < tot; i += int64_t(gridDim.x) * NT) {
-    uint32_t uz, uy, ux;
-    uf(uint32_t(i), uz, uy, ux);
-    const int64_t z = uz, y = uy, x = ux;
-    const int64_t ze = (!zero && z == n0 - 1) ? p0 : z + 1;
-    const int64_t ye = (!zero && y == n1 - 1) ? p1 : y + 1;
-    const int64_t xe = (!zero && x == n2 - 1) ? p2 : x + 1;
-    T acc = T(0);
-    for (int64_t zz = z; zz < ze; ++zz)
-      for (int64_t yy = y; yy < ye; ++yy)
-        for (int64_t xx = x; xx < xe; ++xx) acc += gp[(zz * p1 + yy) * p2 + xx];
-    gx[i] = acc;
+struct UnpadArgs {
+  const T* gp;
+  int64_t p[3];           // padded dims
+  T* gx;
+  int64_t n[3];           // logical dims
+  int64_t e[3];           // logical dims without the end node of a padded axis
+  Unflat32 uf[3];         // face tasks of axis k -> the other two coordinates
+  uint64_t tf[3];         // face tasks per axis
+  uint64_t te[3];         // edge tasks (the axis the edge runs along); then one corner
+  uint64_t ngf;           // workgroups of the face tasks
+};
+
+template <typename T>
+__global__ __launch_bounds__(NT) void k_unpad_ends(UnpadArgs<T> a) {
+  const int64_t ps[3] = {a.p[1] * a.p[2], a.p[2], 1}, ns[3] = {a.n[1] * a.n[2], a.n[2], 1};
+  if (blockIdx.x < a.ngf) {
+    uint64_t i = uint64_t(blockIdx.x) * NT + threadIdx.x;
+    for (int k = 0; k < 3; ++k) {
+      if (i >= a.tf[k]) {
+        i -= a.tf[k];
+        continue;
+      }
+      const int u = k == 0 ? 1 : 0, v = k == 2 ? 1 : 2;
+      uint32_t z, cu, cv;
+      a.uf[k](uint32_t(i), z, cu, cv);
+      const T* src = a.gp + int64_t(cu) * ps[u] + int64_t(cv) * ps[v] + (a.n[k] - 1) * ps[k];
+      const int64_t cnt = a.p[k] - a.n[k] + 1;
+      T acc = T(0);
+      int64_t j = 0;
+      for (; j < cnt; j += kUT) {
+        T t[kUT];
+#pragma unroll
+        for (int q = 0; q < kUT; ++q) t[q] = j + q < cnt ? src[(j + q) * ps[k]] : T(0);
+#pragma unroll
+        for (int q = 0; q < kUT; ++q) acc += t[q];
+      }
+      a.gx[int64_t(cu) * ns[u] + int64_t(cv) * ns[v] + (a.n[k] - 1) * ns[k]] = acc;
+      return;
+    }
+    return;
   }
+  uint64_t i = (uint64_t(blockIdx.x) - a.ngf) * (NT / 64) + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  int64_t c[3] = {a.n[0] - 1, a.n[1] - 1, a.n[2] - 1};
+  int64_t cnt[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) cnt[k] = a.p[k] - a.n[k] + 1;
+  bool found = false;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (found) continue;
+    if (i < a.te[k]) {
+      c[k] = int64_t(i);
+      cnt[k] = 1;
+      found = true;
+    } else {
+      i -= a.te[k];
+    }
+  }
+  if (!found && i > 0) return;           // (i == 0: the corner)
+  const T* src = a.gp + c[0] * ps[0] + c[1] * ps[1] + c[2];
+  const uint32_t c1 = uint32_t(cnt[1]), c2 = uint32_t(cnt[2]), tot = uint32_t(cnt[0]) * c1 * c2;
+  T acc = T(0);
+  for (uint32_t t0 = lane; t0 < tot; t0 += 64 * kUT) {
+    T v[kUT];
+#pragma unroll
+    for (int u = 0; u < kUT; ++u) {
+      const uint32_t t = t0 + 64 * u, r = t / c2, x = t - r * c2, z = r / c1, y = r - z * c1;
+      v[u] = t < tot ? src[z * ps[0] + y * ps[1] + x] : T(0);
+    }
+#pragma unroll
+    for (int u = 0; u < kUT; ++u) acc += v[u];
+  }
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+  if (lane == 0) a.gx[c[0] * ns[0] + c[1] * ns[1] + c[2]] = acc;
+}
+
+template <typename T>
+void launch_unpad_ends(const bm_plan_s& p, const void* gp, void* gx, hipStream_t st) {
+  UnpadArgs<T> a{};
+  a.gp = static_cast<const T*>(gp);
+  a.gx = static_cast<T*>(gx);
+  bool pad[3];
+  for (int k = 0; k < 3; ++k) {
+    a.p[k] = p.pdims[k];
+    a.n[k] = p.dims[k];
+    pad[k] = a.p[k] > a.n[k];
+    a.e[k] = a.n[k] - (pad[k] ? 1 : 0);
+  }
+  uint64_t nf = 0, ne = 0;
+  for (int k = 0; k < 3; ++k) {
+    const int u = k == 0 ? 1 : 0, v = k == 2 ? 1 : 2;
+    a.tf[k] = pad[k] ? uint64_t(a.e[u]) * a.e[v] : 0;
+    a.te[k] = pad[u] && pad[v] ? uint64_t(a.e[k]) : 0;
+    if (a.tf[k] >= (uint64_t(1) << 32)) fail(BM_EUNSUPPORTED, "grid too large for the pad transpose");
+    a.uf[k] = Unflat32(std::max<int64_t>(a.e[u], 1), std::max<int64_t>(a.e[v], 1));
+    nf += a.tf[k];
+    ne += a.te[k];
+  }
+  if (pad[0] && pad[1] && pad[2]) ne += 1;
+  a.ngf = (nf + NT - 1) / NT;
+  const uint64_t g = a.ngf + (ne + NT / 64 - 1) / (NT / 64);
+  if (g == 0) return;
+  hipLaunchKernelGGL(k_unpad_ends<T>, dim3(unsigned(g)), dim3(NT), 0, st, a);
+  BM_HIP(hipGetLastError());
 }
 
 template <typename T>
@@ -997,31 +1257,49 @@ void decompose_adjoint_t(bm_plan_s& p, const void* gcoeff, void* gx, hipStream_t
   const Level& last = p.lv[p.nlev - 1];
   strided_copy(p.esize, coarsest_view(p, const_cast<void*>(gcoeff)), dense_view(p.ws.grid[p.nlev], last.m), st);
   const bool padded = p.dims[0] != p.pdims[0] || p.dims[1] != p.pdims[1] || p.dims[2] != p.pdims[2];
+  const bool clamp = p.cfg.pad_mode != 1;
+  // a level-1 block level writes nodes below the end of a padded axis straight
+  // into gx; only the others go through the padded grid
   void* top = gx;
-  if (padded) {
-    if (p.L == 0) {
-      top = p.ws.grid[0];
-    } else {
-      if (!p.ws.gpad) plan_alloc(p, &p.ws.gpad, size_t(p.pdims[0] * p.pdims[1] * p.pdims[2]) * p.esize);
-      top = p.ws.gpad;
-    }
+  if (padded && p.L == 0) {
+    top = p.ws.grid[0];
+  } else if (padded && clamp) {
+    if (!p.ws.gpad) plan_alloc_late(p, &p.ws.gpad, size_t(p.pdims[0] * p.pdims[1] * p.pdims[2]) * p.esize);
+    top = p.ws.gpad;
   }
   for (int s = p.nlev; s >= 1; --s) {
     const Level& L = p.lv[s - 1];
-    void* out = s > 1 ? p.ws.grid[s - 1] : top;
-    if (L.local)
-      local_dec_T<T>(p, s, gcoeff, out, st);
-    else
-      global_dec_T<T>(p, s, gcoeff, out, st);
+    if (!L.local) {
+      global_dec_T<T>(p, s, gcoeff, s > 1 ? p.ws.grid[s - 1] : top, st);
+      continue;
+    }
+    NodeOut<T> out{};
+    out.a = static_cast<T*>(s > 1 ? p.ws.grid[s - 1] : top);
+    for (int k = 0; k < 3; ++k) out.lim[k] = L.n[k];
+    const int64_t* d = L.n;
+    if (s == 1 && padded) {
+      out.a = static_cast<T*>(gx);
+      d = p.dims;
+      for (int k = 0; k < 3; ++k) out.lim[k] = p.dims[k] - (clamp && p.dims[k] != p.pdims[k] ? 1 : 0);
+      if (clamp) {
+        out.b = static_cast<T*>(p.ws.gpad);
+        out.bs[0] = p.pdims[1] * p.pdims[2];
+        out.bs[1] = p.pdims[2];
+        out.bs[2] = 1;
+      }
+    }
+    out.as[0] = d[1] * d[2];
+    out.as[1] = d[2];
+    out.as[2] = 1;
+    local_dec_T<T>(p, s, gcoeff, out, st);
   }
-  if (padded) {
-    const int64_t tot = p.dims[0] * p.dims[1] * p.dims[2];
-    if (tot >= (int64_t(1) << 32)) fail(BM_EUNSUPPORTED, "grid too large for the pad transpose");
-    hipLaunchKernelGGL(k_unpad_T<T>, dim3(grid_for(tot)), dim3(NT), 0, st, static_cast<const T*>(top), p.pdims[0],
-                       p.pdims[1], p.pdims[2], static_cast<T*>(gx), p.dims[0], p.dims[1], p.dims[2],
-                       Unflat32(p.dims[1], p.dims[2]), p.cfg.pad_mode == 1 ? 1 : 0);
-    BM_HIP(hipGetLastError());
+  if (!padded) return;
+  if (p.L == 0) {
+    View3 src = dense_view(top, p.pdims);
+    for (int k = 0; k < 3; ++k) src.n[k] = p.dims[k];
+    strided_copy(p.esize, src, dense_view(gx, p.dims), st);
   }
+  if (clamp) launch_unpad_ends<T>(p, top, gx, st);
 }
 
 template <typename T>

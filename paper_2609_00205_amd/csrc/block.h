@@ -25,6 +25,7 @@ struct Geo {
   static constexpr int MI = MC - 2;             // interior coarse nodes per axis
   static constexpr int NB = B <= 9 ? 3 : ((ES == 4 && DEC) ? 2 : 1);
   static constexpr int NT = ((NB * BB + 63) / 64) * 64;
+  static constexpr int NB1 = B <= 9 ? 3 : 1;    // blocks per workgroup in the transposes
   // LDS per block: decompose UE[MC][B][B] + T1[MI][B][B] (T2 aliases UE, Z aliases T1)
   static constexpr int DEC_LDS = MC * BB + MI * BB;
   // recompose: UC[MC][MC][MC] + T1[MI][B][B] + T2[MI][MI][B] (Z aliases T1)

@@ -143,6 +143,7 @@ struct Workspace {
   double* boxbuf = nullptr;      // device copy of an ROI box list (kMaxBoxes x 7)
   double* boxhost = nullptr;     // pinned staging for the box list
   void* gpad = nullptr;          // dtype, padded grid: level-1 gradient before the pad transpose
+  void* contrib = nullptr;       // dtype: a slab of blocks' contributions in the transposes of the block levels
   void* prep_dev = nullptr;      // quantizer preparation of this plan: field record + task prefixes (device)
   void* part = nullptr;          // double: per-block partial load vectors of the first global level (fused)
   std::vector<uint8_t> prep_key; // field record last uploaded
@@ -200,6 +201,19 @@ namespace bm {
 template <typename P>
 void plan_alloc(bm_plan_s& p, P** ptr, size_t bytes) {
   BM_HIP(hipMalloc(reinterpret_cast<void**>(ptr), bytes));
+  p.dev_bytes += bytes;
+}
+
+// The same for buffers that a first call adds, which the caller may be
+// capturing into a graph: the allocation itself is no stream operation, so it
+// runs in the relaxed capture mode.
+template <typename P>
+void plan_alloc_late(bm_plan_s& p, P** ptr, size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  BM_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+  const hipError_t e = hipMalloc(reinterpret_cast<void**>(ptr), bytes);
+  BM_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+  BM_HIP(e);
   p.dev_bytes += bytes;
 }
 
