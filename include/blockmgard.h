@@ -409,6 +409,15 @@ bm_status bm_compressed_config(const void* in, size_t in_bytes, bm_config* cfg);
  * and finite). */
 bm_status bm_decompress(const void* in, size_t in_bytes, void* x, hipStream_t stream);
 
+/* Give back the memory that the synchronous calls on containers and streams
+ * (bm_compress*, bm_decompress, bm_batch_compress, bm_p8_compress,
+ * bm_huffman_*) keep for the next such call: at most 2 GiB of device memory
+ * per GPU and 64 MiB of pinned host memory per process, none of it in use
+ * between calls.  Such a call also gives back by itself what none took for
+ * five seconds, and an allocation of theirs that fails gives back everything
+ * first.  Any thread may call this at any time. */
+bm_status bm_release_memory(void);
+
 /* ---- many fields (the paper's batched multi-field workloads, Sec. V) ------- */
 
 /* A batch of independent fields sharing dtype and block size (each its own

@@ -90,6 +90,7 @@ _SIGS = {
     "bm_compress": [P, P, P, P, C.c_size_t, C.POINTER(C.c_size_t), P],
     "bm_compressed_config": [P, C.c_size_t, C.POINTER(BMConfig)],
     "bm_decompress": [P, C.c_size_t, P, P],
+    "bm_release_memory": [],
     "bm_decompose_quantize": [P, P, P, P, C.POINTER(BMQStats), P],
     "bm_dequantize_recompose": [P, P, P, P, P],
     "bm_qoi_deltas": [P, P, C.c_double, P, P, C.POINTER(C.c_int64), P],

@@ -357,6 +357,12 @@ def decompress(buf, device=None, stream=None) -> torch.Tensor:
     return out
 
 
+def release_memory() -> None:
+    """Give back the memory that the container and stream calls keep for the
+    next such call (bm_release_memory)."""
+    call("bm_release_memory")
+
+
 def huffman_encode(codes: torch.Tensor, stream=None) -> bytearray:
     """The Huffman stream of int32 device codes (bm_huffman_plan, then
     bm_huffman_write into a buffer of the stream's exact size)."""

@@ -12,7 +12,7 @@
 
 #include "internal.h"
 
-bm_plan_s* bm_plan_build(const bm_config* c);
+bm_plan_s* bm_plan_build(const bm_config* c, bool pooled = false);
 void bm_plan_free(bm_plan_s* p);
 
 namespace {
@@ -209,14 +209,12 @@ void ensure_code_buffer(bm_plan_s& p) {
   if (!p.ws.codes) plan_alloc(p, &p.ws.codes, n * sizeof(int32_t));
 }
 
-void check_block_tol(bm_plan_s& p, const double* block_tol, hipStream_t st) {
-  const int64_t ntol = p.nb1[0] * p.nb1[1] * p.nb1[2];
-  std::vector<double> tol(ntol);
-  BM_HIP(hipMemcpyAsync(tol.data(), block_tol, ntol * sizeof(double), hipMemcpyDeviceToHost, st));
-  BM_HIP(hipStreamSynchronize(st));
-  for (double t : tol)
-    if (!(t > 0) || !std::isfinite(t)) fail(BM_ENONFINITE, "block tolerances must be positive and finite");
+namespace {
+void check_tols(const double* t, int64_t n) {
+  for (int64_t i = 0; i < n; ++i)
+    if (!(t[i] > 0) || !std::isfinite(t[i])) fail(BM_ENONFINITE, "block tolerances must be positive and finite");
 }
+}  // namespace
 
 struct PendingContainer {
   std::vector<uint8_t> head;   // the header, CRC not set
@@ -229,20 +227,16 @@ struct PendingContainer {
 
 size_t pending_bytes(const PendingContainer& c) { return c.total; }
 
-std::shared_ptr<PendingContainer> plan_container(bm_plan_s& p, const void* x, const double* block_tol, bool too_fine,
-                                                 hipStream_t st) {
-  const int64_t npad = p.pdims[0] * p.pdims[1] * p.pdims[2];
+// The container of x with the map tol; enc: the planned stream of its codes,
+// or null (codes beyond 32 bits: the raw data is stored).
+std::shared_ptr<PendingContainer> plan_container(bm_plan_s& p, const void* x, std::vector<double> tol,
+                                                 std::unique_ptr<HuffmanEncoder> enc, hipStream_t st) {
   const int64_t nlog = p.dims[0] * p.dims[1] * p.dims[2];
   const int64_t ntol = p.nb1[0] * p.nb1[1] * p.nb1[2];
   auto c = std::make_shared<PendingContainer>();
-  c->tol.resize(ntol);
-  BM_HIP(hipMemcpyAsync(c->tol.data(), block_tol, ntol * sizeof(double), hipMemcpyDeviceToHost, st));
-  // the stream is planned once (histogram, code table, chunk sizes); it is
-  // encoded when the container is written, straight into the caller's buffer
-  const int32_t* codes = static_cast<const int32_t*>(p.ws.codes);
-  if (!too_fine) c->enc = std::make_unique<HuffmanEncoder>(codes, npad, st);
+  c->tol = std::move(tol);
+  c->enc = std::move(enc);
   const size_t sb = c->enc ? c->enc->bytes() : 0;
-  BM_HIP(hipStreamSynchronize(st));
   CHeader h{};
   h.magic = kMagic;
   h.version = 1;
@@ -258,7 +252,7 @@ std::shared_ptr<PendingContainer> plan_container(bm_plan_s& p, const void* x, co
   h.ntol = ntol;
   const size_t coded = size_t(ntol) * 8 + sb;
   const size_t raw = size_t(nlog) * p.esize;
-  h.flags = (too_fine || coded >= raw) ? 1u : 0u;
+  h.flags = (!c->enc || coded >= raw) ? 1u : 0u;
   h.payload = h.flags ? raw : coded;
   if (h.flags) c->enc.reset();
   c->head.assign(reinterpret_cast<const uint8_t*>(&h), reinterpret_cast<const uint8_t*>(&h) + sizeof(h));
@@ -268,17 +262,45 @@ std::shared_ptr<PendingContainer> plan_container(bm_plan_s& p, const void* x, co
   return c;
 }
 
+// The codes of x quantized under block_tol and the plan of their stream.
+// The map, the overflow flag and the histogram come back in one wait.
+std::shared_ptr<PendingContainer> plan_compress(bm_plan_s& p, const void* x, const double* block_tol, hipStream_t st) {
+  ensure_code_buffer(p);
+  const int64_t ntol = p.nb1[0] * p.nb1[1] * p.nb1[2];
+  int32_t* codes = static_cast<int32_t*>(p.ws.codes);
+  HostBuf<double> tol(ntol);
+  HostBuf<int64_t> flag(1);
+  IdleOnError idle(st);
+  BM_HIP(hipMemcpyAsync(tol.p, block_tol, ntol * sizeof(double), hipMemcpyDeviceToHost, st));
+  decompose_quantize(p, x, block_tol, codes, nullptr, st);
+  BM_HIP(hipMemcpyAsync(flag.p, p.ws.counters + 2, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+  auto enc = std::make_unique<HuffmanEncoder>(codes, p.pdims[0] * p.pdims[1] * p.pdims[2], st);
+  BM_HIP(hipStreamSynchronize(st));
+  check_tols(tol.p, ntol);
+  try {
+    check_code_flag(flag[0], "tolerance too small for the data");
+    enc->plan();
+  } catch (const Error& e) {
+    if (e.code != BM_ERANGE) throw;
+    enc.reset();   // codes beyond 32 bits: store the raw data
+  }
+  return plan_container(p, x, std::vector<double>(tol.p, tol.p + ntol), std::move(enc), st);
+}
+
 void write_pending(PendingContainer& c, void* out) {
   CHeader h;
   std::memcpy(&h, c.head.data(), sizeof(h));
   const size_t ntol = size_t(h.ntol);
   uint8_t* o = static_cast<uint8_t*>(out) + sizeof(CHeader);
+  uint32_t tcrc = 0;           // CRC-32 of the map
   if (h.flags & 1u) {
     BM_HIP(hipMemcpyAsync(o, c.x, size_t(h.payload), hipMemcpyDeviceToHost, c.st));
     BM_HIP(hipStreamSynchronize(c.st));
   } else {
-    std::memcpy(o, c.tol.data(), ntol * 8);
-    c.enc->write(o + ntol * 8, size_t(h.payload) - ntol * 8);
+    c.enc->write(o + ntol * 8, size_t(h.payload) - ntol * 8, [&] {
+      std::memcpy(o, c.tol.data(), ntol * 8);
+      tcrc = crc32(o, ntol * 8);
+    });
   }
   h.crc = 0;
   const auto t0 = std::chrono::steady_clock::now();
@@ -286,7 +308,7 @@ void write_pending(PendingContainer& c, void* out) {
   if (h.flags & 1u) {
     crc = crc32_parallel(o, size_t(h.payload), crc);
   } else {
-    crc = crc32(o, ntol * 8, crc);
+    crc = crc32_shift(crc, ntol * 8) ^ tcrc;
     crc = stream_crc(*c.enc, o + ntol * 8, size_t(h.payload) - ntol * 8, crc);
   }
   h.crc = crc;
@@ -295,9 +317,17 @@ void write_pending(PendingContainer& c, void* out) {
   std::memcpy(out, &h, sizeof(h));
 }
 
-bool write_container(bm_plan_s& p, const void* x, const double* block_tol, bool too_fine, void* out,
-                     size_t capacity, size_t* needed, hipStream_t st) {
-  std::shared_ptr<PendingContainer> c = plan_container(p, x, block_tol, too_fine, st);
+// one field of a batch, its codes in the plan's code array (false: capacity
+// too small, *needed holds the size)
+bool write_container(bm_plan_s& p, const void* x, std::vector<double> tol, bool too_fine, void* out, size_t capacity,
+                     size_t* needed, hipStream_t st) {
+  std::unique_ptr<HuffmanEncoder> enc;
+  if (!too_fine) {
+    enc = std::make_unique<HuffmanEncoder>(static_cast<const int32_t*>(p.ws.codes),
+                                           p.pdims[0] * p.pdims[1] * p.pdims[2], st);
+    enc->plan();
+  }
+  std::shared_ptr<PendingContainer> c = plan_container(p, x, std::move(tol), std::move(enc), st);
   *needed = c->total;
   if (!out || capacity < c->total) return false;
   write_pending(*c, out);
@@ -323,7 +353,10 @@ bool write_container_p8(bm_p8_s& p, const void* x, const double* block_tol, doub
   const int32_t* codes = p8_codes(p);
   const int64_t ncodes = p8_coeff_size(p);
   std::unique_ptr<HuffmanEncoder> enc;
-  if (!too_fine) enc = std::make_unique<HuffmanEncoder>(codes, ncodes, st);
+  if (!too_fine) {
+    enc = std::make_unique<HuffmanEncoder>(codes, ncodes, st);
+    enc->plan();
+  }
   const size_t sb = enc ? enc->bytes() : 0;
   BM_HIP(hipStreamSynchronize(st));
   CHeader h{};
@@ -515,6 +548,7 @@ bm_status bm_huffman_encode(const int32_t* codes, int64_t n, void* out, size_t c
     need(out_bytes != nullptr, "null out_bytes");
     need(codes || n == 0, "null codes");
     bm::HuffmanEncoder enc(codes, n, st);
+    enc.plan();
     const size_t bytes = enc.bytes();
     *out_bytes = bytes;
     if (!out || capacity < bytes) bm::fail(BM_ECAPACITY, "output buffer too small");
@@ -535,6 +569,7 @@ bm_status bm_huffman_plan(const int32_t* codes, int64_t n, bm_huffman* out, size
     auto h = std::make_unique<bm_huffman_s>();
     BM_HIP(hipGetDevice(&h->device));
     h->enc = std::make_unique<bm::HuffmanEncoder>(codes, n, st);
+    h->enc->plan();
     *out_bytes = h->enc->bytes();
     *out = h.release();
   });
@@ -592,18 +627,10 @@ bm_status bm_compress(bm_plan p, const void* x, const double* block_tol, void* o
     need(p && x && block_tol && out_bytes, "null argument");
     check_device(p);
     p->pending.reset();
-    bm::ensure_code_buffer(*p);
-    bool too_fine = false;   // codes beyond 32 bits: store the raw data
-    bm::check_block_tol(*p, block_tol, st);
-    try {
-      bm_qstats qs;
-      bm::decompose_quantize(*p, x, block_tol, static_cast<int32_t*>(p->ws.codes), &qs, st);
-    } catch (const bm::Error& e) {
-      if (e.code != BM_ERANGE) throw;
-      too_fine = true;
-    }
-    if (!bm::write_container(*p, x, block_tol, too_fine, out, capacity, out_bytes, st))
-      bm::fail(BM_ECAPACITY, "output buffer too small");
+    std::shared_ptr<bm::PendingContainer> c = bm::plan_compress(*p, x, block_tol, st);
+    *out_bytes = bm::pending_bytes(*c);
+    if (!out || capacity < *out_bytes) bm::fail(BM_ECAPACITY, "output buffer too small");
+    bm::write_pending(*c, out);
   });
 }
 
@@ -612,17 +639,7 @@ bm_status bm_compress_plan(bm_plan p, const void* x, const double* block_tol, si
     need(p && x && block_tol && out_bytes, "null argument");
     check_device(p);
     p->pending.reset();
-    bm::ensure_code_buffer(*p);
-    bool too_fine = false;   // codes beyond 32 bits: store the raw data
-    bm::check_block_tol(*p, block_tol, st);
-    try {
-      bm_qstats qs;
-      bm::decompose_quantize(*p, x, block_tol, static_cast<int32_t*>(p->ws.codes), &qs, st);
-    } catch (const bm::Error& e) {
-      if (e.code != BM_ERANGE) throw;
-      too_fine = true;
-    }
-    p->pending = bm::plan_container(*p, x, block_tol, too_fine, st);
+    p->pending = bm::plan_compress(*p, x, block_tol, st);
     *out_bytes = bm::pending_bytes(*p->pending);
   });
 }
@@ -866,11 +883,16 @@ bm_status bm_batch_compress(bm_batch b, const void* const* x, const double* cons
     need(b && x && block_tol && out && capacity && out_bytes, "null argument");
     const int nf = bm::batch_size(*b);
     std::vector<int32_t*> codes(nf);
+    std::vector<std::vector<double>> tol(nf);
     for (int f = 0; f < nf; ++f) {
       need(x[f] && block_tol[f], "null field pointer");
       bm_plan_s& p = *bm::batch_plan(*b, f);
       check_device(&p);
-      bm::check_block_tol(p, block_tol[f], st);
+      const int64_t ntol = p.nb1[0] * p.nb1[1] * p.nb1[2];
+      tol[f].resize(ntol);
+      BM_HIP(hipMemcpyAsync(tol[f].data(), block_tol[f], ntol * sizeof(double), hipMemcpyDeviceToHost, st));
+      BM_HIP(hipStreamSynchronize(st));
+      bm::check_tols(tol[f].data(), ntol);
       bm::ensure_code_buffer(p);
       codes[f] = static_cast<int32_t*>(p.ws.codes);
     }
@@ -879,7 +901,8 @@ bm_status bm_batch_compress(bm_batch b, const void* const* x, const double* cons
     bm::batch_overflows(*b, bad, st);
     bool short_buf = false;
     for (int f = 0; f < nf; ++f)
-      if (!bm::write_container(*bm::batch_plan(*b, f), x[f], block_tol[f], bad[f] != 0, out[f], capacity[f], &out_bytes[f], st))
+      if (!bm::write_container(*bm::batch_plan(*b, f), x[f], std::move(tol[f]), bad[f] != 0, out[f], capacity[f],
+                               &out_bytes[f], st))
         short_buf = true;
     if (short_buf) bm::fail(BM_ECAPACITY, "an output buffer is too small (out_bytes holds the sizes needed)");
   });
@@ -948,17 +971,14 @@ bm_status bm_decompress(const void* in, size_t in_bytes, void* x, hipStream_t st
       return;
     }
     const bm_config c = header_config(h);
-    bm_plan_s* p = bm_plan_build(&c);
+    bm_plan_s* p = bm_plan_build(&c, true);
     struct Guard {
       bm_plan_s* p;
-      double* d = nullptr;
-      ~Guard() {
-        if (d) (void)hipFree(d);
-        bm_plan_free(p);
-      }
+      ~Guard() { bm_plan_free(p); }
     } g{p};
     const uint8_t* pl = static_cast<const uint8_t*>(in) + sizeof(CHeader);
     const int64_t nlog = p->dims[0] * p->dims[1] * p->dims[2];
+    bm::IdleOnError idle0(st);
     if (h.flags & 1u) {
       if (h.payload != uint64_t(nlog) * p->esize) bm::fail(BM_ECORRUPT, "raw payload size mismatch");
       BM_HIP(hipMemcpyAsync(x, pl, size_t(h.payload), hipMemcpyHostToDevice, st));
@@ -967,14 +987,19 @@ bm_status bm_decompress(const void* in, size_t in_bytes, void* x, hipStream_t st
     }
     const int64_t ntol = p->nb1[0] * p->nb1[1] * p->nb1[2];
     if (h.ntol != ntol || h.payload < uint64_t(ntol) * 8) bm::fail(BM_ECORRUPT, "tolerance map size mismatch");
-    bm::ensure_code_buffer(*p);
-    BM_HIP(hipMalloc(&g.d, size_t(ntol) * sizeof(double)));
-    BM_HIP(hipMemcpyAsync(g.d, pl, size_t(ntol) * 8, hipMemcpyHostToDevice, st));
     const int64_t npad = p->pdims[0] * p->pdims[1] * p->pdims[2];
-    dec->decode(static_cast<int32_t*>(p->ws.codes), npad);
-    bm::dequantize_recompose(*p, static_cast<const int32_t*>(p->ws.codes), g.d, x, st);
+    bm::DevBuf<int32_t> codes(npad);
+    bm::DevBuf<double> tol(ntol);
+    bm::IdleOnError idle(st);
+    BM_HIP(hipMemcpyAsync(tol.p, pl, size_t(ntol) * 8, hipMemcpyHostToDevice, st));
+    dec->decode(codes.p, npad);
+    bm::dequantize_recompose(*p, codes.p, tol.p, x, st);
     BM_HIP(hipStreamSynchronize(st));
   });
+}
+
+bm_status bm_release_memory(void) {
+  return guarded([] { bm::pool_release(); });
 }
 
 extern "C++" {
@@ -998,7 +1023,8 @@ void crc32_shift_matrix(uint64_t bytes, uint32_t out[32]) {
   for (int i = 0; i < 32; ++i) out[i] = crc32_shift(1u << i, bytes);
 }
 
-uint32_t crc_with_spans(const uint8_t* buf, size_t n, uint32_t crc, const CrcSpan* spans, int nspans) {
+uint32_t crc_with_spans(const uint8_t* buf, size_t n, uint32_t crc, uint32_t head, const CrcSpan* spans,
+                        int nspans) {
   // the shift over one block as four byte tables: Z(v) = T0[v & 255] ^ T1[..] ^ T2[..] ^ T3[v >> 24]
   static const std::vector<uint32_t> zt = [] {
     uint32_t m[32];
@@ -1011,14 +1037,16 @@ uint32_t crc_with_spans(const uint8_t* buf, size_t n, uint32_t crc, const CrcSpa
   size_t at = 0;
   for (int i = 0; i < nspans; ++i) {
     const CrcSpan& d = spans[i];
-    const size_t done = d.block_crc.size() * kCrcBlock;
+    const size_t done = d.nblk * kCrcBlock;
     if (d.offset < at || d.offset + d.bytes > n || done > d.bytes)
       fail(BM_EINVAL, "stream CRC: the device parts do not match the stream");
-    crc = crc32_parallel(buf + at, d.offset - at, crc);    // host bytes before the span
+    // host bytes before the span
+    crc = i == 0 ? crc32_shift(crc, d.offset) ^ head : crc32_parallel(buf + at, d.offset - at, crc);
     // the span: the device's block CRCs in order, then its last partial block
     uint32_t w = 0;
-    for (uint32_t b : d.block_crc)
-      w = (zt[w & 255u] ^ zt[256 + ((w >> 8) & 255u)] ^ zt[512 + ((w >> 16) & 255u)] ^ zt[768 + (w >> 24)]) ^ b;
+    for (size_t k = 0; k < d.nblk; ++k)
+      w = (zt[w & 255u] ^ zt[256 + ((w >> 8) & 255u)] ^ zt[512 + ((w >> 16) & 255u)] ^ zt[768 + (w >> 24)]) ^
+          d.block_crc[k];
     w = crc32_parallel(buf + d.offset + done, d.bytes - done, w);
     crc = crc32_shift(crc, d.bytes) ^ w;
     at = d.offset + d.bytes;
@@ -1027,7 +1055,7 @@ uint32_t crc_with_spans(const uint8_t* buf, size_t n, uint32_t crc, const CrcSpa
 }
 
 uint32_t stream_crc(const HuffmanEncoder& e, const uint8_t* stream, size_t n, uint32_t crc) {
-  return crc_with_spans(stream, n, crc, e.device_spans(), 2);
+  return crc_with_spans(stream, n, crc, e.head_crc(), e.device_spans(), 2);
 }
 }  // namespace bm
 }  // extern "C++"

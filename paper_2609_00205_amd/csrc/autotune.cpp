@@ -21,7 +21,7 @@
 
 #include "internal.h"
 
-bm_plan_s* bm_plan_build(const bm_config* c);
+bm_plan_s* bm_plan_build(const bm_config* c, bool pooled = false);
 void bm_plan_free(bm_plan_s* p);
 
 namespace bm {
@@ -102,9 +102,10 @@ void measure(const bm_config& cfg, const void* x, const double* voxel_tol, int r
   if (c.status == BM_OK) {
     // one encode into pinned host memory gives the coded size and the
     // lossless stage's time (histogram, code table, chunk sizes, encode, copy
-    // out; its work buffers are allocated per encode, as in compress)
+    // out; its work buffers come from the pool, as in compress)
     const auto t0 = std::chrono::steady_clock::now();
     HuffmanEncoder enc(codes, npad, st);
+    enc.plan();
     const size_t bytes = enc.bytes();
     enc.write(pin.get(bytes), bytes);
     c.lossless_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();

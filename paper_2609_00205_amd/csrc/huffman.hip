@@ -32,6 +32,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <mutex>
 
@@ -60,24 +61,57 @@ __device__ inline uint32_t sym_of(int32_t q) { return (q > -R && q < R) ? uint32
 
 // LDS bins: [0, 2 HW) for symbols R-HW .. R+HW-1, bin 2 HW for the escape
 // symbol; everything else (rare) goes straight to the global histogram.
-__global__ __launch_bounds__(256) void k_hist(const int32_t* codes, int64_t n, unsigned long long* hist) {
-  __shared__ uint32_t h[2 * HW + 1];
-  for (int i = threadIdx.x; i < 2 * HW + 1; i += 256) h[i] = 0;
+// Atomics bound it: in LDS, where neighbouring codes often share a bin (even
+// and odd lanes count apart), and at the end, when every workgroup adds its
+// bins to the same global ones (so two workgroups of 1024 lanes per CU
+// instead of eight of 256).  Codes are read 16 bytes a lane (VEC: the array
+// is 16-byte aligned).  135 M codes of the 512^3 ROI field: 0.340 -> 0.144 ms.
+constexpr int kHistNT = 1024, kHistGroups = 512;
+
+template <bool VEC>
+__global__ __launch_bounds__(kHistNT) void k_hist(const int32_t* codes, int64_t n, unsigned long long* hist) {
+  __shared__ uint32_t h[2][2 * HW + 1];
+  for (int i = threadIdx.x; i < 2 * (2 * HW + 1); i += kHistNT) (&h[0][0])[i] = 0;
   __syncthreads();
-  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
-    const uint32_t s = sym_of(codes[i]);
-    const int64_t k = int64_t(s) - (R - HW);
+  uint32_t* const mine = h[threadIdx.x & 1];
+  auto count = [&](int32_t q) {
+    const uint32_t s = sym_of(q);
+    const uint32_t k = s - uint32_t(R - HW);
     if (s == 0)
-      atomicAdd(&h[2 * HW], 1u);
-    else if (k >= 0 && k < 2 * HW)
-      atomicAdd(&h[k], 1u);
+      atomicAdd(&mine[2 * HW], 1u);
+    else if (k < 2 * HW)
+      atomicAdd(&mine[k], 1u);
     else
       atomicAdd(&hist[s], 1ull);
+  };
+  const int64_t t = int64_t(blockIdx.x) * kHistNT + threadIdx.x, nt = int64_t(gridDim.x) * kHistNT;
+  const int64_t n4 = VEC ? n / 4 : 0;
+  const int4* v = reinterpret_cast<const int4*>(codes);
+  int64_t i = t;
+  for (; i + nt < n4; i += 2 * nt) {
+    const int4 a = v[i], b = v[i + nt];
+    count(a.x);
+    count(a.y);
+    count(a.z);
+    count(a.w);
+    count(b.x);
+    count(b.y);
+    count(b.z);
+    count(b.w);
   }
+  for (; i < n4; i += nt) {
+    const int4 a = v[i];
+    count(a.x);
+    count(a.y);
+    count(a.z);
+    count(a.w);
+  }
+  for (i = 4 * n4 + t; i < n; i += nt) count(codes[i]);
   __syncthreads();
-  for (int i = threadIdx.x; i < 2 * HW; i += 256)
-    if (h[i]) atomicAdd(&hist[R - HW + i], (unsigned long long)h[i]);
-  if (threadIdx.x == 0 && h[2 * HW]) atomicAdd(&hist[0], (unsigned long long)h[2 * HW]);
+  for (int k = threadIdx.x; k <= 2 * HW; k += kHistNT) {
+    const uint32_t c = h[0][k] + h[1][k];
+    if (c) atomicAdd(&hist[k == 2 * HW ? 0 : R - HW + k], (unsigned long long)c);
+  }
 }
 
 __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
@@ -479,21 +513,50 @@ __global__ __launch_bounds__(256) void k_outliers(const uint64_t* ooff, const ui
 // The codebook is built in fixed arrays (no allocation), so the same code
 // serves the entry point that may not allocate.
 
-// Work arrays of the code-length construction: the leaves sorted by key
-// (weight, symbol), the merged nodes in the order they are made, parents and
-// depths of the merge tree.
-struct HNode {
-  uint64_t w;     // weight
-  uint32_t m;     // smallest symbol in the subtree
-  uint32_t id;    // node: a symbol, or NSYM + merge number
-};
-struct LenWork {
-  HNode leaf[NSYM], tmp[NSYM], node[NSYM];
-  uint32_t digit[2048];
+// Work arrays of the code-length construction: keys (weight << 16 | smallest
+// symbol in the subtree) of the leaves in order and of the merged nodes in the
+// order they are made, parents and depths of the merge tree.  Node ids: a
+// leaf's symbol, NSYM + merge number.
+template <typename K>
+struct LenWorkOf {
+  K leaf[NSYM + 1], tmp[NSYM + 1], node[NSYM + 1];
+  uint32_t digit[4][2048];
   int32_t parent[2 * NSYM], depth[2 * NSYM], L[NSYM], present[NSYM];
 };
+using LenWork = LenWorkOf<uint64_t>;
 
-inline bool key_less(const HNode& a, const HNode& b) { return a.w != b.w ? a.w < b.w : a.m < b.m; }
+// Stable sort by weight of np keys in symbol order, 11 bits a pass; wmax: the
+// largest weight.  Each pass runs over the four quarters side by side with
+// bucket positions of their own: neighbouring symbols have similar counts, so
+// one run would wait at almost every key for the position it just moved.
+template <typename K>
+K* sort_leaves(LenWorkOf<K>& w, int np, uint64_t wmax) {
+  K *A = w.leaf, *T = w.tmp;
+  int q[5];
+  for (int k = 0; k <= 4; ++k) q[k] = int(int64_t(np) * k / 4);
+  const int run = q[1] - q[0];                          // (quarters differ by at most one)
+  for (int sh = 0; sh < 64 && (wmax >> sh) != 0; sh += 11) {
+    auto dig = [&](K k) { return uint32_t(uint64_t(k >> 16) >> sh) & 2047u; };
+    std::memset(w.digit, 0, sizeof(w.digit));
+    for (int k = 0; k < run; ++k)
+      for (int j = 0; j < 4; ++j) ++w.digit[j][dig(A[q[j] + k])];
+    for (int j = 0; j < 4; ++j)
+      for (int k = q[j] + run; k < q[j + 1]; ++k) ++w.digit[j][dig(A[k])];
+    uint32_t sum = 0;
+    for (int d = 0; d < 2048; ++d)
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t c = w.digit[j][d];
+        w.digit[j][d] = sum;
+        sum += c;
+      }
+    for (int k = 0; k < run; ++k)
+      for (int j = 0; j < 4; ++j) T[w.digit[j][dig(A[q[j] + k])]++] = A[q[j] + k];
+    for (int j = 0; j < 4; ++j)
+      for (int k = q[j] + run; k < q[j + 1]; ++k) T[w.digit[j][dig(A[k])]++] = A[k];
+    std::swap(A, T);
+  }
+  return A;
+}
 
 // Huffman code lengths of the symbols with hist[s] > 0 (len[s] = 0 for the
 // others): merge the two smallest (weight, smallest symbol in the subtree)
@@ -505,48 +568,31 @@ inline bool key_less(const HNode& a, const HNode& b) { return a.w != b.w ? a.w <
 // order they are made, which is key order too: merges take keys in
 // increasing order, so merged weights do not decrease, and two merged nodes
 // of one weight 2w both come from pairs of weight-w nodes taken in
-// increasing symbol order, so their smallest symbols increase.
-void code_lengths(const uint64_t* hist, uint8_t* len, LenWork& w) {
-  std::memset(len, 0, NSYM);
-  int np = 0;
-  uint64_t wmax = 0;
-  for (int s = 0; s < NSYM; ++s)
-    if (hist[s]) {
-      w.present[np++] = s;
-      wmax = std::max(wmax, hist[s]);
-    }
-  if (np == 0) return;
-  if (np == 1) {
-    len[w.present[0]] = 1;
-    return;
-  }
-  HNode* A = w.leaf;
-  HNode* T = w.tmp;
-  for (int k = 0; k < np; ++k) A[k] = HNode{hist[w.present[k]], uint32_t(w.present[k]), uint32_t(w.present[k])};
-  for (int sh = 0; sh < 64 && (wmax >> sh) != 0; sh += 11) {   // stable LSD passes of 11 bits
-    std::memset(w.digit, 0, sizeof(w.digit));
-    for (int k = 0; k < np; ++k) ++w.digit[(A[k].w >> sh) & 2047u];
-    uint32_t sum = 0;
-    for (int d = 0; d < 2048; ++d) {
-      const uint32_t c = w.digit[d];
-      w.digit[d] = sum;
-      sum += c;
-    }
-    for (int k = 0; k < np; ++k) T[w.digit[(A[k].w >> sh) & 2047u]++] = A[k];
-    std::swap(A, T);
-  }
-  HNode* B = w.node;
-  int ai = 0, bi = 0, bn = 0;
-  auto pop = [&]() -> HNode {
-    if (ai < np && (bi >= bn || key_less(A[ai], B[bi]))) return A[ai++];
-    return B[bi++];
+// increasing symbol order, so their smallest symbols increase.  A queue's head
+// is taken by conditional moves (which one it is cannot be predicted), an
+// entry above every key behind each queue's end.
+template <typename K>
+void code_lengths_of(const uint64_t* hist, uint8_t* len, LenWorkOf<K>& w, int np, uint64_t wmax) {
+  for (int k = 0; k < np; ++k) w.leaf[k] = K(hist[w.present[k]]) << 16 | K(w.present[k]);
+  K* const A = sort_leaves(w, np, wmax);
+  K* const B = w.node;
+  A[np] = B[0] = ~K(0);
+  int ai = 0, bi = 0, next = NSYM;
+  auto pop = [&](K& key) -> int {
+    const K a = A[ai], b = B[bi];
+    const bool leaf = a < b;
+    key = leaf ? a : b;
+    const int id = leaf ? int(a & 0xFFFFu) : NSYM + bi;
+    ai += leaf;
+    bi += !leaf;
+    return id;
   };
-  int next = NSYM;
   for (int k = 0; k < np - 1; ++k) {
-    const HNode a = pop(), b = pop();
-    w.parent[a.id] = next;
-    w.parent[b.id] = next;
-    B[bn++] = HNode{a.w + b.w, std::min(a.m, b.m), uint32_t(next)};
+    K a, b;
+    w.parent[pop(a)] = next;
+    w.parent[pop(b)] = next;
+    B[k] = ((a >> 16) + (b >> 16)) << 16 | std::min(a & 0xFFFFu, b & 0xFFFFu);
+    B[k + 1] = ~K(0);
     ++next;
   }
   w.depth[next - 1] = 0;
@@ -575,6 +621,30 @@ void code_lengths(const uint64_t* hist, uint8_t* len, LenWork& w) {
     }
   }
   for (int k = 0; k < np; ++k) len[w.present[k]] = uint8_t(w.L[w.present[k]]);
+}
+
+void code_lengths(const uint64_t* hist, uint8_t* len, LenWork& w) {
+  std::memset(len, 0, NSYM);
+  int np = 0;
+  uint64_t wmax = 0;
+  for (int s = 0; s < NSYM; ++s)
+    if (hist[s]) {
+      w.present[np++] = s;
+      wmax = std::max(wmax, hist[s]);
+    }
+  if (np == 0) return;
+  if (np == 1) {
+    len[w.present[0]] = 1;
+    return;
+  }
+  if (wmax < (uint64_t(1) << 47) / uint64_t(np)) {      // every sum of weights fits above the symbol
+    code_lengths_of(hist, len, w, np, wmax);
+  } else {                                              // (counts of more codes than a call can hold)
+    using K = unsigned __int128;
+    std::unique_ptr<LenWorkOf<K>> big{new LenWorkOf<K>};
+    std::copy(w.present, w.present + np, big->present);
+    code_lengths_of(hist, len, *big, np, wmax);
+  }
 }
 
 // Canonical codes in (length, symbol) order; sorted receives the coded
@@ -607,19 +677,6 @@ struct HuffHeader {
 };
 constexpr uint32_t kHuffMagic = 0x46484D42u;   // "BMHF"
 
-template <typename T>
-struct DevBuf {
-  T* p = nullptr;
-  explicit DevBuf(size_t n) {
-    if (n) BM_HIP(hipMalloc(&p, n * sizeof(T)));
-  }
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
-  }
-  DevBuf(const DevBuf&) = delete;
-  DevBuf& operator=(const DevBuf&) = delete;
-};
-
 struct EventPair {
   hipEvent_t a = nullptr, b = nullptr;
   EventPair() {
@@ -641,6 +698,18 @@ struct EventPair {
 thread_local bm_lossless_times g_times{};
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+void launch_hist(const int32_t* codes, int64_t n, unsigned long long* hist, hipStream_t st) {
+  hipLaunchKernelGGL(k_zero_u64, dim3(64), dim3(256), 0, st, hist, int64_t(NSYM));
+  if (n) {
+    const dim3 g{unsigned(std::min<int64_t>(kHistGroups, (n + 8 * kHistNT - 1) / (8 * kHistNT)))};
+    if (aligned16(codes))
+      hipLaunchKernelGGL(k_hist<true>, g, dim3(kHistNT), 0, st, codes, n, hist);
+    else
+      hipLaunchKernelGGL(k_hist<false>, g, dim3(kHistNT), 0, st, codes, n, hist);
+  }
+  BM_HIP(hipGetLastError());
+}
 
 void launch_chunk_bits(const int32_t* codes, int64_t n, int64_t nch, const uint8_t* len, uint32_t* bits,
                        uint32_t* esc, hipStream_t st) {
@@ -751,22 +820,45 @@ __global__ __launch_bounds__(256) void k_crc_blocks(const uint4* words, CrcTree 
 // ------------------------------------------------------------------ encoder
 // One plan per code array: histogram (device), code lengths and canonical
 // codes (host), per-chunk bit and escape counts (device), word and outlier
-// offsets (host).  write() encodes with that plan.
+// offsets (host).  write() encodes with that plan.  Every copy between the
+// host and the device goes through pinned memory, so a call waits for its
+// stream three times (counts, sizes, stream) and not at each copy.
+namespace {
+// The calling thread's work arrays (4 MiB of ordinary memory, freed with the
+// thread: clearing and first touching them cost as much as the construction,
+// and pinned memory may lie on another node than the thread)
+struct TableWork {
+  LenWork lw;
+  uint64_t hist[NSYM];
+  uint8_t len[NSYM];
+  uint32_t cw[NSYM], sorted[NSYM];
+};
+TableWork& table_work() {
+  thread_local std::unique_ptr<TableWork> w{new TableWork};
+  return *w;
+}
+}  // namespace
+
 struct HuffmanEncoder::Impl {
   const int32_t* codes;
   int64_t n, nch;
   hipStream_t st;
-  std::vector<uint8_t> len;
-  std::vector<uint32_t> cw, sorted;
-  std::vector<uint64_t> woff, ooff;
-  std::vector<uint16_t> psym;
-  std::vector<uint8_t> plen;
+  HostBuf<uint64_t> hist{NSYM}, woff, ooff;
+  HostBuf<uint8_t> len{NSYM}, plen{NSYM};
+  HostBuf<uint32_t> cw{NSYM}, sizes, crc;
+  HostBuf<uint16_t> psym{NSYM};
+  int64_t np = 0;
   uint64_t wmax = 0;
   size_t bytes = 0;
   CrcSpan span[2];      // the last write's words and outlier values
+  uint32_t head = 0;    // CRC-32 of its bytes before them
+  DevBuf<unsigned long long> dhist{NSYM};
   DevBuf<uint8_t> dlen{NSYM};
   DevBuf<uint32_t> dcw{NSYM};
-  Impl(const int32_t* c, int64_t n_, hipStream_t s) : codes(c), n(n_), nch((n_ + CHUNK - 1) / CHUNK), st(s) {}
+  EventPair eh;
+  IdleOnError idle;
+  Impl(const int32_t* c, int64_t n_, hipStream_t s)
+      : codes(c), n(n_), nch((n_ + CHUNK - 1) / CHUNK), st(s), woff(size_t(nch + 1)), ooff(size_t(nch + 1)), idle(s) {}
 };
 
 HuffmanEncoder::HuffmanEncoder(const int32_t* codes, int64_t n, hipStream_t st) {
@@ -776,61 +868,58 @@ HuffmanEncoder::HuffmanEncoder(const int32_t* codes, int64_t n, hipStream_t st) 
   bm_lossless_times& T = g_times;
   T.enc_n = n;
   T.enc_hist_ms = T.enc_table_ms = T.enc_sizes_ms = T.enc_encode_ms = T.enc_copy_ms = T.enc_crc_ms = 0.0;
+  BM_HIP(hipEventRecord(I.eh.a, st));
+  launch_hist(codes, n, I.dhist.p, st);
+  BM_HIP(hipEventRecord(I.eh.b, st));
+  BM_HIP(hipMemcpyAsync(I.hist.p, I.dhist.p, NSYM * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+}
+
+void HuffmanEncoder::plan() {
+  Impl& I = *d_;
+  bm_lossless_times& T = g_times;
   const int64_t nch = I.nch;
-  DevBuf<unsigned long long> hist(NSYM);
-  EventPair eh, eb;
-  BM_HIP(hipEventRecord(eh.a, st));
-  hipLaunchKernelGGL(k_zero_u64, dim3(64), dim3(256), 0, st, hist.p, int64_t(NSYM));
-  if (n) {
-    const int64_t g = std::min<int64_t>(2048, (n + 255) / 256);
-    hipLaunchKernelGGL(k_hist, dim3(unsigned(g)), dim3(256), 0, st, codes, n, hist.p);
-  }
-  BM_HIP(hipGetLastError());
-  BM_HIP(hipEventRecord(eh.b, st));
-  std::vector<uint64_t> h(NSYM);
-  BM_HIP(hipMemcpyAsync(h.data(), hist.p, NSYM * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+  const hipStream_t st = I.st;
   BM_HIP(hipStreamSynchronize(st));
-  T.enc_hist_ms = eh.ms();
+  T.enc_hist_ms = I.eh.ms();
   const auto t1 = clk::now();
   {
-    auto work = std::make_unique<LenWork>();
-    I.len.assign(NSYM, 0);
-    code_lengths(h.data(), I.len.data(), *work);
+    TableWork& W = table_work();
+    std::memcpy(W.hist, I.hist.p, sizeof(W.hist));
+    code_lengths(W.hist, W.len, W.lw);
+    int ns = 0;
+    canonical(W.len, W.cw, W.sorted, &ns);
+    std::memcpy(I.len.p, W.len, sizeof(W.len));
+    std::memcpy(I.cw.p, W.cw, sizeof(W.cw));
+    uint16_t* const psym = I.psym.p;
+    uint8_t* const plen = I.plen.p;
+    int64_t np = 0;
+    for (int s = 0; s < NSYM; ++s)
+      if (W.len[s]) {
+        psym[np] = uint16_t(s);
+        plen[np++] = W.len[s];
+      }
+    I.np = np;
   }
-  I.cw.assign(NSYM, 0);
-  I.sorted.assign(NSYM, 0);
-  int ns = 0;
-  canonical(I.len.data(), I.cw.data(), I.sorted.data(), &ns);
-  I.sorted.resize(ns);
-  for (int s = 0; s < NSYM; ++s)
-    if (I.len[s]) {
-      I.psym.push_back(uint16_t(s));
-      I.plen.push_back(I.len[s]);
-    }
   T.enc_table_ms = ms_since(t1);
   const auto t2 = clk::now();
-  BM_HIP(hipMemcpyAsync(I.dlen.p, I.len.data(), NSYM, hipMemcpyHostToDevice, st));
-  BM_HIP(hipMemcpyAsync(I.dcw.p, I.cw.data(), NSYM * sizeof(uint32_t), hipMemcpyHostToDevice, st));
-  DevBuf<uint32_t> bits(size_t(std::max<int64_t>(nch, 1))), esc(size_t(std::max<int64_t>(nch, 1)));
-  BM_HIP(hipEventRecord(eb.a, st));
-  launch_chunk_bits(codes, n, nch, I.dlen.p, bits.p, esc.p, st);
-  BM_HIP(hipEventRecord(eb.b, st));
-  std::vector<uint32_t> hb(nch), he(nch);
-  if (nch) {
-    BM_HIP(hipMemcpyAsync(hb.data(), bits.p, nch * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    BM_HIP(hipMemcpyAsync(he.data(), esc.p, nch * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  }
+  const size_t nc = size_t(std::max<int64_t>(nch, 1));
+  I.sizes.reset(2 * nc);
+  DevBuf<uint32_t> dsizes(2 * nc);
+  IdleOnError idle(st);
+  BM_HIP(hipMemcpyAsync(I.dlen.p, I.len.p, NSYM, hipMemcpyHostToDevice, st));
+  BM_HIP(hipMemcpyAsync(I.dcw.p, I.cw.p, NSYM * sizeof(uint32_t), hipMemcpyHostToDevice, st));
+  launch_chunk_bits(I.codes, I.n, nch, I.dlen.p, dsizes.p, dsizes.p + nc, st);
+  if (nch) BM_HIP(hipMemcpyAsync(I.sizes.p, dsizes.p, 2 * nc * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
   BM_HIP(hipStreamSynchronize(st));
-  I.woff.assign(nch + 1, 0);
-  I.ooff.assign(nch + 1, 0);
+  I.woff[0] = I.ooff[0] = 0;
   for (int64_t c = 0; c < nch; ++c) {
-    const uint64_t w = (uint64_t(hb[c]) + 31) / 32;
+    const uint64_t w = (uint64_t(I.sizes[c]) + 31) / 32;
     I.wmax = std::max(I.wmax, w);
     I.woff[c + 1] = I.woff[c] + w;
-    I.ooff[c + 1] = I.ooff[c] + he[c];
+    I.ooff[c + 1] = I.ooff[c] + I.sizes[nc + c];
   }
   T.enc_sizes_ms = ms_since(t2);
-  I.bytes = sizeof(HuffHeader) + I.psym.size() * 3 + size_t(nch + 1) * 16 + size_t(I.woff[nch]) * 4 +
+  I.bytes = sizeof(HuffHeader) + size_t(I.np) * 3 + size_t(nch + 1) * 16 + size_t(I.woff[nch]) * 4 +
             size_t(I.ooff[nch]) * 4;
 }
 
@@ -838,6 +927,7 @@ HuffmanEncoder::~HuffmanEncoder() = default;
 
 size_t HuffmanEncoder::bytes() const { return d_->bytes; }
 const CrcSpan (&HuffmanEncoder::device_spans() const)[2] { return d_->span; }
+uint32_t HuffmanEncoder::head_crc() const { return d_->head; }
 
 namespace {
 // the columns of the tree's shifts over 64, 128, ..., 8192 zero bytes
@@ -849,71 +939,87 @@ const CrcTree& crc_tree() {
   }();
   return t;
 }
+
+// Launches the CRC-32 of every whole kCrcBlock of the spans' device copies
+// and its copy to host (pinned): stream-ordered.
+void launch_span_crcs(CrcSpan (&span)[2], const void* const (&src)[2], DevBuf<uint32_t>& dev, HostBuf<uint32_t>& host,
+                      hipStream_t st) {
+  for (CrcSpan& c : span) {
+    c.nblk = c.bytes / kCrcBlock;
+    if (c.nblk >= (size_t(1) << 31)) fail(BM_EUNSUPPORTED, "Huffman stream too large");
+  }
+  const size_t tot = span[0].nblk + span[1].nblk;
+  if (!tot) return;
+  dev.reset(tot);
+  host.reset(tot);
+  size_t at = 0;
+  for (int k = 0; k < 2; ++k) {
+    span[k].block_crc = host.p + at;
+    if (span[k].nblk)
+      hipLaunchKernelGGL(k_crc_blocks, dim3(unsigned(span[k].nblk)), dim3(256), 0, st,
+                         static_cast<const uint4*>(src[k]), crc_tree(), dev.p + at);
+    BM_HIP(hipGetLastError());
+    at += span[k].nblk;
+  }
+  BM_HIP(hipMemcpyAsync(host.p, dev.p, tot * 4, hipMemcpyDeviceToHost, st));
+}
 }  // namespace
 
-void HuffmanEncoder::write(uint8_t* dst, size_t capacity) {
+void HuffmanEncoder::write(uint8_t* dst, size_t capacity, const std::function<void()>& meanwhile) {
   Impl& I = *d_;
   bm_lossless_times& T = g_times;
   if (I.bytes > capacity) fail(BM_ECAPACITY, "Huffman stream larger than its buffer");
   const int64_t nch = I.nch, nw = int64_t(I.woff[nch]), nout = int64_t(I.ooff[nch]);
-  const int64_t np = int64_t(I.psym.size());
-  DevBuf<uint64_t> dwoff(nch + 1), dooff(nch + 1);
-  DevBuf<uint32_t> dwords(size_t(std::max<int64_t>(nw, 1)));
+  const int64_t np = I.np;
+  DevBuf<uint64_t> doff(size_t(2 * (nch + 1)));
+  uint64_t *const dwoff = doff.p, *const dooff = doff.p + nch + 1;
+  DevBuf<uint32_t> dwords(size_t(std::max<int64_t>(nw, 1))), dcrc;
   DevBuf<int32_t> doval(size_t(std::max<int64_t>(nout, 1)));
-  BM_HIP(hipMemcpyAsync(dwoff.p, I.woff.data(), (nch + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, I.st));
-  BM_HIP(hipMemcpyAsync(dooff.p, I.ooff.data(), (nch + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, I.st));
   EventPair ee, ec;
+  IdleOnError idle(I.st);
+  BM_HIP(hipMemcpyAsync(dwoff, I.woff.p, (nch + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, I.st));
+  BM_HIP(hipMemcpyAsync(dooff, I.ooff.p, (nch + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, I.st));
   BM_HIP(hipEventRecord(ee.a, I.st));
-  launch_encode(I.codes, I.n, nch, I.dlen.p, I.dcw.p, dwoff.p, dooff.p, I.wmax, dwords.p, doval.p, I.st);
+  launch_encode(I.codes, I.n, nch, I.dlen.p, I.dcw.p, dwoff, dooff, I.wmax, dwords.p, doval.p, I.st);
+  uint8_t* o = dst + sizeof(HuffHeader) + size_t(np) * 3 + size_t(nch + 1) * 16;
+  I.span[0] = CrcSpan{size_t(o - dst), size_t(nw) * 4};
+  I.span[1] = CrcSpan{I.span[0].offset + I.span[0].bytes, size_t(nout) * 4};
   // the CRC-32 of every whole 16 KiB block of the words and of the outlier
   // values, while they are on the device
-  const void* dsrc[2] = {dwords.p, doval.p};
-  const size_t dbytes[2] = {size_t(nw) * 4, size_t(nout) * 4};
-  size_t nblk[2];
-  for (int k = 0; k < 2; ++k) nblk[k] = dbytes[k] / kCrcBlock;
-  DevBuf<uint32_t> dcrc(std::max<size_t>(nblk[0] + nblk[1], 1));
-  for (int k = 0; k < 2; ++k) {
-    I.span[k].bytes = dbytes[k];
-    I.span[k].block_crc.assign(nblk[k], 0u);
-    if (!nblk[k]) continue;
-    if (nblk[k] >= (size_t(1) << 31)) fail(BM_EUNSUPPORTED, "Huffman stream too large");
-    hipLaunchKernelGGL(k_crc_blocks, dim3(unsigned(nblk[k])), dim3(256), 0, I.st, static_cast<const uint4*>(dsrc[k]),
-                       crc_tree(), dcrc.p + (k ? nblk[0] : 0));
-    BM_HIP(hipGetLastError());
-  }
+  launch_span_crcs(I.span, {dwords.p, doval.p}, dcrc, I.crc, I.st);
   BM_HIP(hipEventRecord(ee.b, I.st));
+  BM_HIP(hipEventRecord(ec.a, I.st));
+  if (nw) BM_HIP(hipMemcpyAsync(dst + I.span[0].offset, dwords.p, I.span[0].bytes, hipMemcpyDeviceToHost, I.st));
+  if (nout) BM_HIP(hipMemcpyAsync(dst + I.span[1].offset, doval.p, I.span[1].bytes, hipMemcpyDeviceToHost, I.st));
+  BM_HIP(hipEventRecord(ec.b, I.st));
+  // the rest of the stream and its CRC, while the copies run
   HuffHeader hh{kHuffMagic, 3, I.n, nch, nw, nout, np};
-  uint8_t* o = dst;
+  o = dst;
   std::memcpy(o, &hh, sizeof(hh));
   o += sizeof(hh);
-  if (np) std::memcpy(o, I.psym.data(), size_t(np) * 2);
+  if (np) std::memcpy(o, I.psym.p, size_t(np) * 2);
   o += size_t(np) * 2;
-  if (np) std::memcpy(o, I.plen.data(), size_t(np));
+  if (np) std::memcpy(o, I.plen.p, size_t(np));
   o += size_t(np);
-  std::memcpy(o, I.woff.data(), (nch + 1) * 8);
+  std::memcpy(o, I.woff.p, (nch + 1) * 8);
   o += (nch + 1) * 8;
-  std::memcpy(o, I.ooff.data(), (nch + 1) * 8);
-  o += (nch + 1) * 8;
-  BM_HIP(hipEventRecord(ec.a, I.st));
-  I.span[0].offset = size_t(o - dst);
-  if (nw) BM_HIP(hipMemcpyAsync(o, dwords.p, size_t(nw) * 4, hipMemcpyDeviceToHost, I.st));
-  for (int k = 0; k < 2; ++k)
-    if (nblk[k])
-      BM_HIP(hipMemcpyAsync(I.span[k].block_crc.data(), dcrc.p + (k ? nblk[0] : 0), nblk[k] * 4, hipMemcpyDeviceToHost,
-                            I.st));
-  o += size_t(nw) * 4;
-  I.span[1].offset = size_t(o - dst);
-  if (nout) BM_HIP(hipMemcpyAsync(o, doval.p, size_t(nout) * 4, hipMemcpyDeviceToHost, I.st));
-  BM_HIP(hipEventRecord(ec.b, I.st));
+  std::memcpy(o, I.ooff.p, (nch + 1) * 8);
+  I.head = container_crc(dst, I.span[0].offset);
+  if (meanwhile) meanwhile();
   BM_HIP(hipStreamSynchronize(I.st));
   T.enc_encode_ms = ee.ms();
   T.enc_copy_ms = ec.ms();
 }
 
-size_t huffman_size(const int32_t* codes, int64_t n, hipStream_t st) { return HuffmanEncoder(codes, n, st).bytes(); }
+size_t huffman_size(const int32_t* codes, int64_t n, hipStream_t st) {
+  HuffmanEncoder e(codes, n, st);
+  e.plan();
+  return e.bytes();
+}
 
 size_t huffman_encode(const int32_t* codes, int64_t n, std::vector<uint8_t>& out, hipStream_t st) {
   HuffmanEncoder e(codes, n, st);
+  e.plan();
   out.resize(e.bytes());
   e.write(out.data(), out.size());
   return out.size();
@@ -921,14 +1027,18 @@ size_t huffman_encode(const int32_t* codes, int64_t n, std::vector<uint8_t>& out
 
 void set_lossless_crc_ms(double ms) { g_times.enc_crc_ms = ms; }
 
-void huffman_code_lengths(const uint64_t* hist, uint8_t* len) {
-  auto work = std::make_unique<LenWork>();
-  code_lengths(hist, len, *work);
-}
+void huffman_code_lengths(const uint64_t* hist, uint8_t* len) { code_lengths(hist, len, table_work().lw); }
 
 bm_lossless_times lossless_times() { return g_times; }
 
 // ------------------------------------------------------------------ decode (host)
+struct DecHost {
+  uint8_t len[NSYM];
+  uint32_t cw[NSYM], sorted[NSYM];
+  uint32_t hdr[kDecHdrWords];
+  uint16_t psym[NSYM], sorted16[NSYM];
+};
+
 struct HuffmanDecoder::Impl {
   hipStream_t st;
   const uint8_t* in;
@@ -936,17 +1046,19 @@ struct HuffmanDecoder::Impl {
   int64_t n = 0, nch = 0, nw = 0, nout = 0;
   uint64_t wcap = 0;
   CrcSpan span[2];
-  std::vector<uint32_t> hdr;
-  std::vector<uint16_t> sorted16;
-  std::vector<uint64_t> woff, ooff;
-  uint32_t escidx = 0;
-  std::unique_ptr<DevBuf<uint32_t>> dhdr, dwords;
-  std::unique_ptr<DevBuf<uint16_t>> dsorted, drel;
-  std::unique_ptr<DevBuf<uint64_t>> dwoff, dooff;
-  std::unique_ptr<DevBuf<int32_t>> doval;
-  std::unique_ptr<DevBuf<int>> derr;
+  uint32_t nsorted = 1, escidx = 0;
+  HostBuf<DecHost> host{1};
+  HostBuf<uint64_t> off;             // word offsets, then outlier offsets
+  HostBuf<uint32_t> crc;
+  HostBuf<int> err{1};
+  DevBuf<uint32_t> dhdr{kDecHdrWords}, dwords, dcrc;
+  DevBuf<uint16_t> dsorted{NSYM}, drel;
+  DevBuf<uint64_t> doff;
+  DevBuf<int32_t> doval;
+  DevBuf<unsigned long long> derr{1};
   EventPair eu;
-  Impl(const uint8_t* i, size_t ib, hipStream_t s) : st(s), in(i), in_bytes(ib) {}
+  IdleOnError idle;
+  Impl(const uint8_t* i, size_t ib, hipStream_t s) : st(s), in(i), in_bytes(ib), idle(s) {}
 };
 
 HuffmanDecoder::~HuffmanDecoder() = default;
@@ -968,26 +1080,35 @@ HuffmanDecoder::HuffmanDecoder(const uint8_t* in, size_t in_bytes, hipStream_t s
   const int64_t nch = hh.nchunks, nw = hh.nwords, nout = hh.noutliers, np = hh.npresent;
   const size_t need = sizeof(hh) + size_t(np) * 3 + size_t(nch + 1) * 16 + size_t(nw) * 4 + size_t(nout) * 4;
   if (in_bytes < need) fail(BM_ECORRUPT, "Huffman stream truncated");
+  I.n = n;
+  I.nch = nch;
+  I.nw = nw;
+  I.nout = nout;
+  I.span[0] = CrcSpan{sizeof(hh) + size_t(np) * 3 + size_t(nch + 1) * 16, size_t(nw) * 4};
+  I.span[1] = CrcSpan{I.span[0].offset + I.span[0].bytes, size_t(nout) * 4};
+  // the code words and outlier values start on their way while the rest is
+  // parsed here
+  I.dwords.reset(size_t(std::max<int64_t>(nw, 1)));
+  I.doval.reset(size_t(std::max<int64_t>(nout, 1)));
+  I.drel.reset(size_t(std::max<int64_t>(nout, 1)));
+  I.doff.reset(size_t(2 * (nch + 1)));
+  I.off.reset(size_t(2 * (nch + 1)));
+  BM_HIP(hipEventRecord(I.eu.a, st));
+  if (nw) BM_HIP(hipMemcpyAsync(I.dwords.p, in + I.span[0].offset, I.span[0].bytes, hipMemcpyHostToDevice, st));
+  if (nout) BM_HIP(hipMemcpyAsync(I.doval.p, in + I.span[1].offset, I.span[1].bytes, hipMemcpyHostToDevice, st));
   const uint8_t* p = in + sizeof(hh);
-  std::vector<uint8_t> len(NSYM, 0);
-  {
-    std::vector<uint16_t> psym(np);
-    if (np) std::memcpy(psym.data(), p, size_t(np) * 2);
-    for (int64_t k = 0; k < np; ++k) {
-      if (k && psym[k] <= psym[k - 1]) fail(BM_ECORRUPT, "code table symbols out of order");
-      len[psym[k]] = p[size_t(np) * 2 + k];
-      if (len[psym[k]] == 0) fail(BM_ECORRUPT, "zero code length in the table");
-    }
+  DecHost& H = I.host[0];
+  uint8_t* const len = H.len;
+  std::memset(len, 0, NSYM);
+  if (np) std::memcpy(H.psym, p, size_t(np) * 2);
+  for (int64_t k = 0; k < np; ++k) {
+    if (k && H.psym[k] <= H.psym[k - 1]) fail(BM_ECORRUPT, "code table symbols out of order");
+    len[H.psym[k]] = p[size_t(np) * 2 + k];
+    if (len[H.psym[k]] == 0) fail(BM_ECORRUPT, "zero code length in the table");
   }
   p += size_t(np) * 3;
-  std::vector<uint64_t>& woff = I.woff;
-  woff.resize(nch + 1);
-  std::memcpy(woff.data(), p, (nch + 1) * 8);
-  p += (nch + 1) * 8;
-  std::vector<uint64_t>& ooff = I.ooff;
-  ooff.resize(nch + 1);
-  std::memcpy(ooff.data(), p, (nch + 1) * 8);
-  p += (nch + 1) * 8;
+  std::memcpy(I.off.p, p, size_t(nch + 1) * 16);
+  const uint64_t *woff = I.off.p, *ooff = I.off.p + nch + 1;
   if (woff[0] != 0 || ooff[0] != 0 || ooff[nch] != uint64_t(nout)) fail(BM_ECORRUPT, "bad chunk offsets");
   uint64_t wcap = 0;
   for (int64_t c = 0; c < nch; ++c) {
@@ -998,29 +1119,28 @@ HuffmanDecoder::HuffmanDecoder(const uint8_t* in, size_t in_bytes, hipStream_t s
       fail(BM_ECORRUPT, "bad chunk offsets");
     wcap = std::max(wcap, woff[c + 1] - woff[c]);
   }
+  I.wcap = wcap;
   uint64_t kraft = 0;
   for (int s = 0; s < NSYM; ++s) {
     if (len[s] > LMAX) fail(BM_ECORRUPT, "code length above 32");
     if (len[s]) kraft += uint64_t(1) << (LMAX - len[s]);
   }
   if (kraft > (uint64_t(1) << LMAX)) fail(BM_ECORRUPT, "code lengths violate Kraft's inequality");
-  std::vector<uint32_t> cw(NSYM), sorted(NSYM);
+  const uint32_t *const cw = H.cw, *const sorted = H.sorted;
   int ns = 0;
-  canonical(len.data(), cw.data(), sorted.data(), &ns);
-  sorted.resize(ns);
+  canonical(len, H.cw, H.sorted, &ns);
   // decode tables (layout at k_decode)
-  std::vector<uint32_t>& hdr = I.hdr;
-  hdr.assign(kDecHdrWords, 0);
-  std::vector<uint16_t>& sorted16 = I.sorted16;
-  sorted16.assign(std::max<size_t>(sorted.size(), 1), 0);
+  std::memset(H.hdr, 0, sizeof(H.hdr));
+  H.sorted16[0] = 0;
+  I.nsorted = uint32_t(std::max(ns, 1));
   {
-    uint32_t* lut = hdr.data();
+    uint32_t* lut = H.hdr;
     uint32_t* lastc = lut + (1 << DLB);
     uint32_t* offs = lastc + (LMAX + 1);
     uint32_t first[LMAX + 1] = {}, count[LMAX + 1] = {}, base[LMAX + 1] = {};
-    for (size_t i = 0; i < sorted.size(); ++i) {
+    for (int i = 0; i < ns; ++i) {
       const uint32_t s = sorted[i], l = len[s];
-      sorted16[i] = uint16_t(s);
+      H.sorted16[i] = uint16_t(s);
       if (count[l] == 0) {
         first[l] = cw[s];
         base[l] = uint32_t(i);
@@ -1039,7 +1159,7 @@ HuffmanDecoder::HuffmanDecoder(const uint8_t* in, size_t in_bytes, hipStream_t s
       const uint32_t e = lut[pf];
       if (!(e & kLong)) continue;
       const uint32_t lmin = (e >> 16) & 63u, lmax = (e >> 24) & 63u, i0 = e & 0xFFFFu;
-      if (lmin != lmax || i0 + (1u << (lmin - DLB)) > uint32_t(sorted.size())) continue;
+      if (lmin != lmax || i0 + (1u << (lmin - DLB)) > uint32_t(ns)) continue;
       const uint32_t s0 = sorted[i0], sl = sorted[i0 + (1u << (lmin - DLB)) - 1];
       // the prefix's first code starts it; the 2^(l - DLB)-th code of length l from there ends it
       if (len[sl] == lmin && (cw[s0] >> (lmin - DLB)) == pf && (cw[sl] >> (lmin - DLB)) == pf)
@@ -1052,56 +1172,22 @@ HuffmanDecoder::HuffmanDecoder(const uint8_t* in, size_t in_bytes, hipStream_t s
       offs[l] = base[l] - first[l];
     }
   }
-  T.dec_parse_ms = ms_since(t0);
-  I.n = n;
-  I.nch = nch;
-  I.nw = nw;
-  I.nout = nout;
-  I.wcap = wcap;
-  I.dhdr = std::make_unique<DevBuf<uint32_t>>(hdr.size());
-  I.dsorted = std::make_unique<DevBuf<uint16_t>>(sorted16.size());
-  I.dwoff = std::make_unique<DevBuf<uint64_t>>(nch + 1);
-  I.dooff = std::make_unique<DevBuf<uint64_t>>(nch + 1);
-  I.dwords = std::make_unique<DevBuf<uint32_t>>(size_t(std::max<int64_t>(nw, 1)));
-  I.doval = std::make_unique<DevBuf<int32_t>>(size_t(std::max<int64_t>(nout, 1)));
-  I.drel = std::make_unique<DevBuf<uint16_t>>(size_t(std::max<int64_t>(nout, 1)));
-  I.derr = std::make_unique<DevBuf<int>>(1);
-  BM_HIP(hipEventRecord(I.eu.a, st));
-  BM_HIP(hipMemcpyAsync(I.dhdr->p, hdr.data(), hdr.size() * 4, hipMemcpyHostToDevice, st));
-  BM_HIP(hipMemcpyAsync(I.dsorted->p, sorted16.data(), sorted16.size() * 2, hipMemcpyHostToDevice, st));
-  BM_HIP(hipMemcpyAsync(I.dwoff->p, woff.data(), (nch + 1) * 8, hipMemcpyHostToDevice, st));
-  BM_HIP(hipMemcpyAsync(I.dooff->p, ooff.data(), (nch + 1) * 8, hipMemcpyHostToDevice, st));
-  I.span[0].offset = size_t(p - in);
-  I.span[0].bytes = size_t(nw) * 4;
-  if (nw) BM_HIP(hipMemcpyAsync(I.dwords->p, p, size_t(nw) * 4, hipMemcpyHostToDevice, st));
-  p += size_t(nw) * 4;
-  I.span[1].offset = size_t(p - in);
-  I.span[1].bytes = size_t(nout) * 4;
-  if (nout) BM_HIP(hipMemcpyAsync(I.doval->p, p, size_t(nout) * 4, hipMemcpyHostToDevice, st));
-  BM_HIP(hipEventRecord(I.eu.b, st));
-  I.escidx = uint32_t(sorted16.size());
-  for (size_t i = 0; i < sorted.size(); ++i)
+  I.escidx = I.nsorted;
+  for (int i = 0; i < ns; ++i)
     if (sorted[i] == 0) I.escidx = uint32_t(i);
+  T.dec_parse_ms = ms_since(t0);
+  BM_HIP(hipMemcpyAsync(I.dhdr.p, H.hdr, sizeof(H.hdr), hipMemcpyHostToDevice, st));
+  BM_HIP(hipMemcpyAsync(I.dsorted.p, H.sorted16, size_t(I.nsorted) * 2, hipMemcpyHostToDevice, st));
+  BM_HIP(hipMemcpyAsync(I.doff.p, I.off.p, size_t(nch + 1) * 16, hipMemcpyHostToDevice, st));
+  BM_HIP(hipEventRecord(I.eu.b, st));
 }
 
 uint32_t HuffmanDecoder::crc(uint32_t crc) {
   Impl& I = *d_;
-  const void* src[2] = {I.dwords->p, I.doval->p};
-  size_t nblk[2];
-  for (int k = 0; k < 2; ++k) nblk[k] = I.span[k].bytes / kCrcBlock;
-  DevBuf<uint32_t> dcrc(std::max<size_t>(nblk[0] + nblk[1], 1));
-  for (int k = 0; k < 2; ++k) {
-    I.span[k].block_crc.assign(nblk[k], 0u);
-    if (!nblk[k]) continue;
-    if (nblk[k] >= (size_t(1) << 31)) fail(BM_EUNSUPPORTED, "Huffman stream too large");
-    hipLaunchKernelGGL(k_crc_blocks, dim3(unsigned(nblk[k])), dim3(256), 0, I.st, static_cast<const uint4*>(src[k]),
-                       crc_tree(), dcrc.p + (k ? nblk[0] : 0));
-    BM_HIP(hipGetLastError());
-    BM_HIP(hipMemcpyAsync(I.span[k].block_crc.data(), dcrc.p + (k ? nblk[0] : 0), nblk[k] * 4,
-                          hipMemcpyDeviceToHost, I.st));
-  }
+  launch_span_crcs(I.span, {I.dwords.p, I.doval.p}, I.dcrc, I.crc, I.st);
+  const uint32_t head = container_crc(I.in, I.span[0].offset);   // while the stream is on its way
   BM_HIP(hipStreamSynchronize(I.st));
-  return crc_with_spans(I.in, I.in_bytes, crc, I.span, 2);
+  return crc_with_spans(I.in, I.in_bytes, crc, head, I.span, 2);
 }
 
 void HuffmanDecoder::decode(int32_t* codes, int64_t n) {
@@ -1110,27 +1196,28 @@ void HuffmanDecoder::decode(int32_t* codes, int64_t n) {
   if (I.n != n) fail(BM_EINVAL, "symbol count does not match the destination");
   T.dec_n = n;
   const int64_t nch = I.nch;
-  const DecTables t{I.dhdr->p, I.dsorted->p, uint32_t(I.sorted16.size()), I.escidx};
-  const int zero = 0;
-  BM_HIP(hipMemcpyAsync(I.derr->p, &zero, sizeof(int), hipMemcpyHostToDevice, I.st));
+  const DecTables t{I.dhdr.p, I.dsorted.p, I.nsorted, I.escidx};
+  int* const derr = reinterpret_cast<int*>(I.derr.p);
+  const uint64_t *const dwoff = I.doff.p, *const dooff = I.doff.p + nch + 1;
+  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, I.st, I.derr.p, int64_t(1));
+  BM_HIP(hipGetLastError());
   EventPair ed;
   BM_HIP(hipEventRecord(ed.a, I.st));
   if (nch) {
-    launch_decode<kDecWpc, kDecCpw>(I.dwords->p, I.dwoff->p, nch, n, t, I.dooff->p, I.drel->p, codes, I.derr->p,
+    launch_decode<kDecWpc, kDecCpw>(I.dwords.p, dwoff, nch, n, t, dooff, I.drel.p, codes, derr,
                                     int(I.wcap), I.st);
     BM_HIP(hipGetLastError());
     if (I.nout)
-      hipLaunchKernelGGL(k_outliers, dim3(unsigned(nch)), dim3(256), 0, I.st, I.dooff->p, I.drel->p, I.doval->p, codes,
+      hipLaunchKernelGGL(k_outliers, dim3(unsigned(nch)), dim3(256), 0, I.st, dooff, I.drel.p, I.doval.p, codes,
                          n);
     BM_HIP(hipGetLastError());
   }
   BM_HIP(hipEventRecord(ed.b, I.st));
-  int herr = 0;
-  BM_HIP(hipMemcpyAsync(&herr, I.derr->p, sizeof(int), hipMemcpyDeviceToHost, I.st));
+  BM_HIP(hipMemcpyAsync(I.err.p, derr, sizeof(int), hipMemcpyDeviceToHost, I.st));
   BM_HIP(hipStreamSynchronize(I.st));
   T.dec_upload_ms = I.eu.ms();
   T.dec_decode_ms = ed.ms();
-  if (herr) fail(BM_ECORRUPT, "Huffman stream does not decode");
+  if (I.err[0]) fail(BM_ECORRUPT, "Huffman stream does not decode");
 }
 
 void huffman_decode(const uint8_t* in, size_t in_bytes, int32_t* codes, int64_t n, hipStream_t st) {
@@ -1148,6 +1235,7 @@ void huffman_decode(const uint8_t* in, size_t in_bytes, int32_t* codes, int64_t 
 // of Algorithm 1): histogram, code table, chunk sizes + encode, copy-out + CRC.
 void huffman_stage_times(const int32_t* codes, int64_t n, hipStream_t st, double ms[4]) {
   HuffmanEncoder e(codes, n, st);
+  e.plan();
   std::vector<uint8_t> out(e.bytes());
   e.write(out.data(), out.size());
   const auto t0 = clk::now();
@@ -1227,12 +1315,7 @@ size_t huffman_encode_noalloc(const int32_t* codes, int64_t n, void* out, size_t
   auto* dwoff = reinterpret_cast<uint64_t*>(scr + kScrWoff);
   auto* dooff = reinterpret_cast<uint64_t*>(scr + kScrOoff);
   const int64_t nch = (n + CHUNK - 1) / CHUNK;
-  hipLaunchKernelGGL(k_zero_u64, dim3(64), dim3(256), 0, st, hist, int64_t(NSYM));
-  if (n) {
-    const int64_t g = std::min<int64_t>(2048, (n + 255) / 256);
-    hipLaunchKernelGGL(k_hist, dim3(unsigned(g)), dim3(256), 0, st, codes, n, hist);
-  }
-  BM_HIP(hipGetLastError());
+  launch_hist(codes, n, hist, st);
   BM_HIP(hipMemcpyAsync(H.hist, hist, sizeof(H.hist), hipMemcpyDeviceToHost, st));
   BM_HIP(hipStreamSynchronize(st));
   code_lengths(H.hist, H.len, H.work);

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <exception>
+#include <functional>
 #include <memory>
 #include <string>
 #include <vector>
@@ -128,6 +130,10 @@ struct Level {
   double* d_inv[3];    // device: Thomas reciprocal pivots of the coarse mass matrix (global levels)
 };
 
+// The quantizer preparation's device record: a field record, then 2 x 9 task
+// prefixes of two entries.
+constexpr size_t kPrepFirst = 2048, kPrepBytes = kPrepFirst + 36 * sizeof(int64_t);
+
 // Device workspace sizes and buffers owned by a plan.
 struct Workspace {
   std::vector<void*> grid;       // grid[s] = compact G^s, s = 1..L+M (grid[0] unused)
@@ -145,9 +151,60 @@ struct Workspace {
   void* gpad = nullptr;          // dtype, padded grid: level-1 gradient before the pad transpose
   void* contrib = nullptr;       // dtype: a slab of blocks' contributions in the transposes of the block levels
   void* prep_dev = nullptr;      // quantizer preparation of this plan: field record + task prefixes (device)
+  bool prep_set = false;         // its task prefixes are there
   void* part = nullptr;          // double: per-block partial load vectors of the first global level (fused)
   std::vector<uint8_t> prep_key; // field record last uploaded
   const double* kept_tol = nullptr;  // map whose tables are kept (bm_quant_prepare); null: none
+};
+
+}  // namespace bm
+
+namespace bm {
+// Memory of calls that wait for their stream before they return, kept for
+// the next such call (pool.cpp): device memory of the current GPU, or pinned
+// host memory (device -1).  pool_put only when no work on it is pending.
+struct PoolMem {
+  void* p = nullptr;
+  size_t bytes = 0;
+  int device = -1;
+};
+PoolMem pool_take(size_t bytes, bool host);
+void pool_put(const PoolMem& m);
+void pool_release();
+
+template <typename T, bool HOST>
+struct PoolBuf {
+  PoolMem m;
+  T* p = nullptr;
+  PoolBuf() = default;
+  explicit PoolBuf(size_t n) { reset(n); }
+  ~PoolBuf() { pool_put(m); }
+  PoolBuf(const PoolBuf&) = delete;
+  PoolBuf& operator=(const PoolBuf&) = delete;
+  void reset(size_t n) {
+    pool_put(m);
+    m = PoolMem{};
+    p = nullptr;
+    if (n) m = pool_take(n * sizeof(T), HOST);
+    p = static_cast<T*>(m.p);
+  }
+  T& operator[](size_t i) { return p[i]; }
+  const T& operator[](size_t i) const { return p[i]; }
+};
+template <typename T>
+using DevBuf = PoolBuf<T, false>;
+template <typename T>
+using HostBuf = PoolBuf<T, true>;
+
+// Waits for a stream when a scope is left by an exception: declared after the
+// pool buffers that work on the stream may still use.
+struct IdleOnError {
+  hipStream_t st;
+  int n = std::uncaught_exceptions();
+  explicit IdleOnError(hipStream_t s) : st(s) {}
+  ~IdleOnError() {
+    if (std::uncaught_exceptions() > n) (void)hipStreamSynchronize(st);
+  }
 };
 
 }  // namespace bm
@@ -193,6 +250,10 @@ struct bm_plan_s {
   // the plan's own rule
   std::vector<double> w_override;
   size_t dev_bytes = 0;          // device memory the plan holds (bm_workspace_size)
+  // one allocation holds every buffer that is made with the plan; from the
+  // pool for the plans that a call makes and frees itself
+  bm::PoolMem slab;
+  bool pooled = false;
 };
 
 namespace bm {
@@ -395,19 +456,8 @@ void quantize_delta(bm_plan_s& p, const void* coeff, const double* delta, int32_
                     hipStream_t st);
 void dequantize_delta(bm_plan_s& p, const int32_t* codes, const double* delta, void* coeff, hipStream_t st);
 
-// compress path: lazily allocated code / coefficient buffers of a plan, the
-// tolerance-map check, and the container writer (false: capacity too small,
-// *needed holds the size)
+// compress path: the lazily allocated code array of a plan
 void ensure_code_buffer(bm_plan_s& p);
-void check_block_tol(bm_plan_s& p, const double* block_tol, hipStream_t st);
-bool write_container(bm_plan_s& p, const void* x, const double* block_tol, bool too_fine, void* out, size_t capacity,
-                     size_t* needed, hipStream_t st);
-// the same in two steps: plan (sizes, Huffman plan; synchronizes), then write
-std::shared_ptr<PendingContainer> plan_container(bm_plan_s& p, const void* x, const double* block_tol, bool too_fine,
-                                                 hipStream_t st);
-size_t pending_bytes(const PendingContainer& c);
-void write_pending(PendingContainer& c, void* out);
-
 // batches of fields (one dtype and block size): build / free, the fused
 // pipeline both ways (graph: capture once per binding, then replay), and the
 // fields whose codes overflowed int32 (synchronizes)
@@ -449,21 +499,22 @@ int batch_overflows(bm_batch_s& b, std::vector<int>& bad, hipStream_t st);
 std::vector<bm_candidate> autotune(const bm_config& in, const void* x, const double* voxel_tol, double slack, int reps,
                                    bm_config& out, hipStream_t st, double budget_ms = 0.0, bool* fits = nullptr);
 
-// huffman (host buffers).  An encoder plans its stream once on creation
-// (histogram and chunk sizes on the device, code table on the host;
-// synchronizes): bytes() is the exact stream size, write() encodes into a
-// host buffer of at least that size.  Stage times of the calling thread's
+// huffman (host buffers).  An encoder launches the histogram on creation
+// (stream-ordered); plan() makes the code table on the host and the chunk
+// sizes on the device (synchronizes): bytes() is then the exact stream size,
+// and write() encodes into a host buffer of at least that size.  Stage times of the calling thread's
 // last encode and decode are kept for lossless_times().
 // A part of a byte stream that is also on the device, with the CRC-32 of
 // each of its whole kCrcBlock-byte blocks formed there.
 struct CrcSpan {
-  size_t offset = 0, bytes = 0;
-  std::vector<uint32_t> block_crc;
+  size_t offset = 0, bytes = 0, nblk = 0;
+  const uint32_t* block_crc = nullptr;   // nblk values (host)
 };
 constexpr size_t kCrcBlock = 16384;
 // CRC-32 (zlib's) of buf[0, n), continuing from crc: the spans' block CRCs
-// folded on the host, every other byte read there.
-uint32_t crc_with_spans(const uint8_t* buf, size_t n, uint32_t crc, const CrcSpan* spans, int nspans);
+// folded on the host, every other byte read there; head is the CRC-32 of the
+// bytes before the first span (formed while the spans were still copied).
+uint32_t crc_with_spans(const uint8_t* buf, size_t n, uint32_t crc, uint32_t head, const CrcSpan* spans, int nspans);
 
 class HuffmanEncoder {
  public:
@@ -471,12 +522,15 @@ class HuffmanEncoder {
   ~HuffmanEncoder();
   HuffmanEncoder(const HuffmanEncoder&) = delete;
   HuffmanEncoder& operator=(const HuffmanEncoder&) = delete;
+  void plan();
   size_t bytes() const;
-  void write(uint8_t* dst, size_t capacity);
+  // meanwhile: host work to do while the stream is copied
+  void write(uint8_t* dst, size_t capacity, const std::function<void()>& meanwhile = {});
   // after write: the stream's parts that came from the device (the code
   // words, the outlier values), where they lie in it, and the CRC-32 of each
   // whole kCrcBlock of them, formed on the device before they were copied
   const CrcSpan (&device_spans() const)[2];
+  uint32_t head_crc() const;   // of the stream's bytes before the first of them
 
  private:
   struct Impl;

@@ -24,7 +24,7 @@
 
 #include "internal.h"
 
-bm_plan_s* bm_plan_build(const bm_config* c);
+bm_plan_s* bm_plan_build(const bm_config* c, bool pooled = false);
 void bm_plan_free(bm_plan_s* p);
 
 namespace bm {

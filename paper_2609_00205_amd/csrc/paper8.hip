@@ -438,7 +438,7 @@ struct bm_p8_s {
   double* tg = nullptr;                    // tau_global (the smallest last-level block tau), then its reduction key
 };
 
-bm_plan_s* bm_plan_build(const bm_config* c);
+bm_plan_s* bm_plan_build(const bm_config* c, bool pooled = false);
 void bm_plan_free(bm_plan_s* p);
 
 namespace bm {

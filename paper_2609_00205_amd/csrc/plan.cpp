@@ -271,7 +271,10 @@ using namespace bm;
 
 static int64_t prod3(const int64_t n[3]) { return n[0] * n[1] * n[2]; }
 
-bm_plan_s* bm_plan_build(const bm_config* c) {
+void bm_plan_free(bm_plan_s* p);
+
+// pooled: a plan that the calling entry point frees itself, its stream idle
+bm_plan_s* bm_plan_build(const bm_config* c, bool pooled) {
   if (!c) fail(BM_EINVAL, "null config");
   if (c->ndim < 1 || c->ndim > 3) fail(BM_EINVAL, "ndim must be 1, 2 or 3");
   if (c->dtype != BM_F32 && c->dtype != BM_F64) fail(BM_EINVAL, "dtype must be BM_F32 or BM_F64");
@@ -314,6 +317,18 @@ bm_plan_s* bm_plan_build(const bm_config* c) {
   auto p = new bm_plan_s();
   p->cfg = *c;
   p->device = dev;
+  p->pooled = pooled;
+  // the buffers made with the plan, laid out in one allocation (a hipMalloc
+  // and hipFree each cost more than a small field's transform)
+  struct Want {
+    void** ptr;
+    size_t bytes;
+  };
+  std::vector<Want> want;
+  auto ask = [&](auto** ptr, size_t bytes) {
+    want.push_back({reinterpret_cast<void**>(ptr), (bytes + 255) / 256 * 256});
+  };
+  std::vector<double> piv;                              // pivots of every global level and axis, in order
   p->esize = c->dtype == BM_F32 ? 4 : 8;
   for (int a = 0; a < 3; ++a) p->dims[a] = d[a];
   p->L = c->L;
@@ -350,8 +365,7 @@ bm_plan_s* bm_plan_build(const bm_config* c) {
           if (!L.coarsen[a]) continue;
           std::vector<double> inv;
           thomas_pivots_natural(L.m[a], inv);
-          plan_alloc(*p, &L.d_inv[a], inv.size() * sizeof(double));
-          BM_HIP(hipMemcpy(L.d_inv[a], inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice));
+          piv.insert(piv.end(), inv.begin(), inv.end());
         }
       }
       p->lv.push_back(L);
@@ -370,13 +384,13 @@ bm_plan_s* bm_plan_build(const bm_config* c) {
     if (p->fuse_next) {
       // per-block partial load vectors of the first global level (FP64): H^3 per block, H = (b+3)/4
       const int64_t h = (bL + 3) / 4;
-      plan_alloc(*p, &p->ws.part, size_t(prod3(p->lv[c->L - 1].nb)) * h * h * h * sizeof(double));
+      ask(&p->ws.part, size_t(prod3(p->lv[c->L - 1].nb)) * h * h * h * sizeof(double));
     }
     // workspace
     p->ws.grid.assign(p->nlev + 1, nullptr);
-    if (c->L == 0) plan_alloc(*p, &p->ws.grid[0], size_t(prod3(p->pdims)) * p->esize);
+    if (c->L == 0) ask(&p->ws.grid[0], size_t(prod3(p->pdims)) * p->esize);
     for (int s = 1; s <= p->nlev; ++s)
-      plan_alloc(*p, &p->ws.grid[s], size_t(prod3(p->lv[s - 1].m)) * p->esize);
+      ask(&p->ws.grid[s], size_t(prod3(p->lv[s - 1].m)) * p->esize);
     size_t t = 0;
     for (auto& L : p->lv) {
       if (L.local) {
@@ -388,8 +402,8 @@ bm_plan_s* bm_plan_build(const bm_config* c) {
     }
     p->ws.t_elems = t;
     if (t) {
-      plan_alloc(*p, &p->ws.t1, t * p->esize);
-      plan_alloc(*p, &p->ws.t2, t * p->esize);
+      ask(&p->ws.t1, t * p->esize);
+      ask(&p->ws.t2, t * p->esize);
     }
     int64_t tot = 0;
     p->ws.tol_off.assign(p->nlev + 2, 0);
@@ -401,28 +415,37 @@ bm_plan_s* bm_plan_build(const bm_config* c) {
     const int64_t nlastb = c->L > 0 ? prod3(p->lv[c->L - 1].nb) : 0;
     // propagated taus; tau_global; then the 27-class Delta and 1/Delta tables
     // of the levels and of the coarsest values
-    plan_alloc(*p, &p->ws.tolbuf, size_t(tot + 8 + 54 * (tot + nlastb)) * sizeof(double));
-    plan_alloc(*p, &p->ws.boxbuf, size_t(kMaxBoxes) * 7 * sizeof(double));
-    BM_HIP(hipHostMalloc(&p->ws.boxhost, size_t(kMaxBoxes) * 7 * sizeof(double), hipHostMallocDefault));
-    plan_alloc(*p, &p->ws.qparam, size_t(4 * (p->nlev + 2)) * sizeof(double));
+    ask(&p->ws.tolbuf, size_t(tot + 8 + 54 * (tot + nlastb)) * sizeof(double));
+    ask(&p->ws.boxbuf, size_t(kMaxBoxes) * 7 * sizeof(double));
+    ask(&p->ws.qparam, size_t(4 * (p->nlev + 2)) * sizeof(double));
     // 16 counters, then per-workgroup partial statistics of the quantizer (3 x 8192)
-    plan_alloc(*p, &p->ws.counters, (16 + 3 * 8192) * sizeof(int64_t));
-  } catch (...) {
-    // release what was allocated, then rethrow
-    for (auto& L : p->lv)
+    ask(&p->ws.counters, (16 + 3 * 8192) * sizeof(int64_t));
+    ask(&p->ws.prep_dev, kPrepBytes);
+    double* d_piv = nullptr;
+    if (!piv.empty()) ask(&d_piv, piv.size() * sizeof(double));
+    size_t total = 0;
+    for (const Want& w : want) total += w.bytes;
+    if (pooled) {
+      p->slab = pool_take(total, false);
+    } else {
+      BM_HIP(hipMalloc(&p->slab.p, total));
+      p->slab.bytes = total;
+    }
+    p->dev_bytes = total - (kPrepBytes + 255) / 256 * 256;   // (the quantizer counts its task table once it is set up)
+    uint8_t* at = static_cast<uint8_t*>(p->slab.p);
+    for (const Want& w : want) {
+      *w.ptr = at;
+      at += w.bytes;
+    }
+    if (!piv.empty()) BM_HIP(hipMemcpy(d_piv, piv.data(), piv.size() * sizeof(double), hipMemcpyHostToDevice));
+    for (Level& L : p->lv)
       for (int a = 0; a < 3; ++a)
-        if (!L.local && L.d_inv[a]) (void)hipFree(L.d_inv[a]);
-    for (void* g : p->ws.grid)
-      if (g) (void)hipFree(g);
-    if (p->ws.t1) (void)hipFree(p->ws.t1);
-    if (p->ws.t2) (void)hipFree(p->ws.t2);
-    if (p->ws.tolbuf) (void)hipFree(p->ws.tolbuf);
-    if (p->ws.qparam) (void)hipFree(p->ws.qparam);
-    if (p->ws.counters) (void)hipFree(p->ws.counters);
-    if (p->ws.boxbuf) (void)hipFree(p->ws.boxbuf);
-    if (p->ws.boxhost) (void)hipHostFree(p->ws.boxhost);
-    if (p->ws.part) (void)hipFree(p->ws.part);
-    delete p;
+        if (!L.local && L.coarsen[a]) {
+          L.d_inv[a] = d_piv;
+          d_piv += L.m[a];
+        }
+  } catch (...) {
+    bm_plan_free(p);
     throw;
   }
   return p;
@@ -435,14 +458,12 @@ void bm_plan_free(bm_plan_s* p) {
     (void)hipEventDestroy(e.a);
     (void)hipEventDestroy(e.b);
   }
-  for (auto& L : p->lv)
-    for (int a = 0; a < 3; ++a)
-      if (!L.local && L.d_inv[a]) (void)hipFree(L.d_inv[a]);
-  for (void* g : p->ws.grid)
-    if (g) (void)hipFree(g);
-  for (void* q : {p->ws.t1, p->ws.t2, p->ws.codes, p->ws.coeff, (void*)p->ws.tolbuf, (void*)p->ws.qparam,
-                  (void*)p->ws.counters, (void*)p->ws.boxbuf, p->ws.gpad, p->ws.contrib, p->ws.prep_dev, p->ws.part})
+  for (void* q : {p->ws.codes, p->ws.coeff, p->ws.gpad, p->ws.contrib})
     if (q) (void)hipFree(q);
+  if (p->pooled)
+    pool_put(p->slab);
+  else if (p->slab.p)
+    (void)hipFree(p->slab.p);
   if (p->ws.boxhost) (void)hipHostFree(p->ws.boxhost);
   delete p;
 }

@@ -778,13 +778,12 @@ QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool 
   }
   p.ws.kept_tol = nullptr;   // the tables built here replace the kept ones
   const PrepField f = prep_field(p, block_tol, a);
-  constexpr size_t kFirst = 2048;                   // offset of the task prefix arrays
-  static_assert(sizeof(PrepField) <= kFirst, "field record too large");
+  static_assert(sizeof(PrepField) <= kPrepFirst, "field record too large");
   int64_t cnt_prop[9] = {}, cnt_tab[9] = {};
   for (int s = 1; s < 9; ++s) cnt_prop[s] = p.L > s ? prod3(p.lv[s].nb) : 0;
   for (int s = 1; s < 9; ++s) cnt_tab[s] = p.L >= s ? 27 * prod3(p.lv[s - 1].nb) : 0;
   cnt_tab[0] = (p.L > 0 && p.M == 0) ? 27 * prod3(p.lv[p.L - 1].nb) : 0;
-  if (!p.ws.prep_dev) {
+  if (!p.ws.prep_set) {
     std::vector<int64_t> first(4 * 9);
     for (int s = 0; s < 9; ++s) {
       first[2 * s] = 0;
@@ -792,9 +791,10 @@ QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool 
       first[18 + 2 * s] = 0;
       first[18 + 2 * s + 1] = cnt_tab[s];
     }
-    plan_alloc(p, &p.ws.prep_dev, kFirst + first.size() * sizeof(int64_t));
-    BM_HIP(hipMemcpy(static_cast<uint8_t*>(p.ws.prep_dev) + kFirst, first.data(), first.size() * sizeof(int64_t),
+    BM_HIP(hipMemcpy(static_cast<uint8_t*>(p.ws.prep_dev) + kPrepFirst, first.data(), first.size() * sizeof(int64_t),
                      hipMemcpyHostToDevice));
+    p.ws.prep_set = true;
+    p.dev_bytes += kPrepBytes;
   }
   const uint8_t* fb = reinterpret_cast<const uint8_t*>(&f);
   if (p.ws.prep_key.size() != sizeof(f) || std::memcmp(p.ws.prep_key.data(), fb, sizeof(f)) != 0) {
@@ -803,7 +803,7 @@ QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool 
     p.ws.prep_key.assign(fb, fb + sizeof(f));
   }
   PrepStages g;
-  const int64_t* first = reinterpret_cast<const int64_t*>(static_cast<uint8_t*>(p.ws.prep_dev) + kFirst);
+  const int64_t* first = reinterpret_cast<const int64_t*>(static_cast<uint8_t*>(p.ws.prep_dev) + kPrepFirst);
   for (int s = 0; s < 9; ++s) {
     g.prop_first[s] = first + 2 * s;
     g.prop_n[s] = cnt_prop[s];
@@ -1025,6 +1025,8 @@ void tolmap_from_boxes(bm_plan_s& p, const double* boxes, int nbox, double backg
   if (nbox) {
     // the caller's list goes through pinned staging; the call then waits for
     // the copy so the staging buffer can be reused
+    if (!p.ws.boxhost)
+      BM_HIP(hipHostMalloc(&p.ws.boxhost, size_t(kMaxBoxes) * 7 * sizeof(double), hipHostMallocDefault));
     std::copy(boxes, boxes + 7 * nbox, p.ws.boxhost);
     BM_HIP(hipMemcpyAsync(p.ws.boxbuf, p.ws.boxhost, size_t(nbox) * 7 * sizeof(double), hipMemcpyHostToDevice, st));
     dbox = p.ws.boxbuf;
