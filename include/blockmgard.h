@@ -422,14 +422,14 @@ bm_status bm_release_memory(void);
 
 /* A batch of independent fields sharing dtype and block size (each its own
  * dims and L, M).  The fused pipeline of all fields runs as one launch per
- * stage of the quantizer-table preparation, one persistent launch per block
+ * stage of the quantizer-table preparation, one launch per block
  * level covering the blocks of every field that has that level, and each
  * field's global levels.  With use_graph the sequence is captured once in a
  * HIP graph (per set of bound pointers) and replayed; use_graph needs a
  * stream other than the null stream.  The batch owns one plan per field
  * (bm_batch_plan borrows it: coefficient shapes, tolerance maps); a batch is
  * used from one stream at a time.  With the nested schedule (b = 17, every
- * field) a field's 17- and 9-node levels run as one pair: one persistent
+ * field) a field's 17- and 9-node levels run as one pair: one
  * launch covers the pairs of all such fields, beside the plain launch of
  * the fields with one block level.  A 33-node level runs its column,
  * coarse (and, recomposing, interpolation) steps as one persistent launch

@@ -660,14 +660,14 @@ class Paper8Plan:
 
 class Batch:
     """Many fields of one dtype and block size through the fused pipeline in
-    few launches (one persistent launch per block level for all fields; for
+    few launches (one launch per block level for all fields; for
     33-node blocks one per step of the split block), optionally captured once
     in a HIP graph and replayed.
 
     L: per-field block levels (default: the most each shape tiles without
     padding, chosen by the library); M: global levels (int or per field);
     nested: the nested block schedule for every field (b = 17: a field's
-    17- and 9-node levels run as one pair in one persistent launch).
+    17- and 9-node levels run as one pair in one launch).
     """
 
     def __init__(self, shapes: Sequence[Sequence[int]], dtype=torch.float32, block: int = 17, L=None, M=0,

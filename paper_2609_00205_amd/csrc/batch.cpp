@@ -2,7 +2,7 @@
 //
 // The fused pipeline of every field (decompose + ROI quantize, or dequantize
 // + recompose) is issued as: one launch per stage of the quantizer-table
-// preparation for all fields, one persistent launch per block level
+// preparation for all fields, one launch per block level
 // covering the blocks of every field that has that level (a 33-node level:
 // one per step of the split block, over halves or blocks; the nested
 // schedule: one for the 17/9 pairs), and the (small) global levels of each
@@ -109,13 +109,20 @@ void bind(bm_batch_s& b, Bound& B, bool dec, const void* const* x, const double*
   }
   const size_t off_fields = im.put(pf.data(), pf.size() * sizeof(PrepField));
   size_t off_prop[kMaxLev] = {}, off_tab[kMaxLev] = {};
+  bool big = false;   // some field has more level-2 blocks than one workgroup propagates
+  B.stages.fields = dec;
+  for (const bm_plan_s* p : b.plans) {
+    big = big || (p->L > 1 && prod(p->lv[1].nb) > kPropOneGroup);
+    B.stages.fields = B.stages.fields || p->L != 1 || p->M > 0;
+  }
   for (int s = 0; s < kMaxLev; ++s) {
     std::vector<int64_t> fp(nf + 1, 0), ft(nf + 1, 0);
     for (int f = 0; f < nf; ++f) {
       const bm_plan_s& p = *b.plans[f];
-      const int64_t np = (s >= 1 && p.L > s) ? prod(p.lv[s].nb) : 0;                        // into level s+1
-      const int64_t nt = s >= 1 ? (p.L >= s ? 27 * prod(p.lv[s - 1].nb) : 0)
-                                : ((p.L > 0 && p.M == 0) ? 27 * prod(p.lv[p.L - 1].nb) : 0);  // coarsest values
+      const int64_t np = (big && s >= 1 && p.L > s) ? prod(p.lv[s].nb) : 0;                 // into level s+1
+      // (only 33-node levels read class tables)
+      const int ts = s >= 1 ? s : p.M == 0 ? p.L : 0;                                       // 0: the coarsest values
+      const int64_t nt = ts >= 1 && p.L >= ts && p.lv[ts - 1].b == 33 ? 27 * prod(p.lv[ts - 1].nb) : 0;
       fp[f + 1] = fp[f] + np;
       ft[f + 1] = ft[f] + nt;
     }
@@ -227,7 +234,7 @@ void level_launch(const bm_batch_s& b, const Bound& B, int s, bool dec, hipStrea
 
 void enqueue(bm_batch_s& b, Bound& B, bool dec, hipStream_t st) {
   const int nf = int(b.plans.size());
-  launch_prep_batch(B.stages, B.fields, nf, st);
+  launch_prep_batch(B.stages, B.fields, nf, nullptr, dec, st);
   if (dec) {
     for (int s = 1; s <= b.Lmax; ++s) {
       if (s == 1) launch_block_batch_nest(b.dtype, true, B.nargs1, B.nargs2, B.nfirst, B.nnf, B.nntasks, st);

@@ -123,6 +123,48 @@ __device__ inline int pos_class(int c) {
   return c == 0 ? 0 : (c == B - 1 ? 2 : 1);
 }
 
+// The classes of a workgroup's NB blocks from the blocks' tolerances, formed
+// by its first 32 NB lanes: lane c of a block loads the tolerance of the
+// neighbour at offset (c / 9, c / 3 % 3, c % 3) - 1 (the block itself beyond
+// the grid), and the minimum over the blocks that share a class (first face:
+// this block and the one before, interior: itself, last face: the one after
+// too) is taken along x, y and z by lane exchanges.  cls[0][block][27] gets
+// Delta (1/Delta when INV) with kap, cls[1] with kapc when coarse.  27 lanes
+// and 27 loads per block, hidden behind the block's own loads, take the place
+// of a table of 27 (54 with the coarsest values) x 2 values per block that a
+// launch wrote and every column read: 1024 x 1024 x 512 FP64 spent 2 x 64 us
+// on it and tau_global, 32 fields of a batch 2 x 30 us.
+template <int NB, bool INV>
+__device__ inline void class_table(const double* tau, double kap, double kapc, bool coarse, int64_t blk0,
+                                   int64_t nblocks, const FastDiv& f2, const FastDiv& f1, const int64_t nb[3],
+                                   double (*cls)[NB * 27]) {
+  const int tid = threadIdx.x;
+  if (tid >= 32 * NB) return;
+  const int bl = tid >> 5, c = tid & 31, half = tid & 32;
+  const int64_t blk = blk0 + bl;
+  const bool in = c < 27 && blk < nblocks;
+  const int cz = c / 9, cy = c / 3 - 3 * (c / 9), cx = c - 3 * (c / 3);
+  double v = INFINITY;
+  if (in) {
+    int64_t b[3];
+    block_coords(uint32_t(blk), f2, f1, nb, b[0], b[1], b[2]);
+    const int o[3] = {cz - 1, cy - 1, cx - 1};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int64_t k = b[d] + o[d];
+      b[d] = k < 0 || k >= nb[d] ? b[d] : k;
+    }
+    v = tau[(b[0] * nb[1] + b[1]) * nb[2] + b[2]];
+  }
+  v = fmin(v, __shfl(v, half + cz * 9 + cy * 3 + 1, 64));
+  v = fmin(v, __shfl(v, half + cz * 9 + 3 + cx, 64));
+  v = fmin(v, __shfl(v, half + 9 + cy * 3 + cx, 64));
+  if (!in) return;
+  const double d = v * kap, dc = v * kapc;
+  cls[0][bl * 27 + c] = INV ? 1.0 / d : d;
+  if (coarse) cls[1][bl * 27 + c] = INV ? 1.0 / dc : dc;
+}
+
 // The Delta-table entries (27 classes per block) of one z-column: a node takes
 // the smallest Delta (largest 1/Delta) of the blocks that contain it.  Entries
 // for z = 0, for 0 < z < B-1 and for z = B-1.

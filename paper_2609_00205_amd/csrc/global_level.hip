@@ -1200,7 +1200,7 @@ void decompose_quantize_global(bm_plan_s& p, const void* x, int32_t* codes, cons
 
 void decompose_quantize(bm_plan_s& p, const void* x, const double* block_tol, int32_t* codes, bm_qstats* stats,
                         hipStream_t st) {
-  const QPrep q = quant_prepare(p, block_tol, st);   // also clears the overflow flag
+  const QPrep q = quant_prepare(p, block_tol, st, true, false);   // also clears the overflow flag
   const View3 xv = dense_view(const_cast<void*>(x), p.dims);
   for (int s = 1; s <= p.L; ++s) {
     const Level& L = p.lv[s - 1];
@@ -1262,7 +1262,7 @@ void dequantize_recompose_global(bm_plan_s& p, const int32_t* codes, const QPrep
 // Inverse of decompose_quantize: dequantize on load, then recompose.  Equal
 // to bm_dequantize followed by bm_recompose.
 void dequantize_recompose(bm_plan_s& p, const int32_t* codes, const double* block_tol, void* x, hipStream_t st) {
-  const QPrep q = quant_prepare(p, block_tol, st, false);
+  const QPrep q = quant_prepare(p, block_tol, st, false, false);
   dequantize_recompose_global(p, codes, q, x, st);
   for (int s = p.L; s >= 1; --s) {
     TimedScope ts(p, 2 * (s - 1) + 1, st);

@@ -343,6 +343,10 @@ void recompose_adjoint(bm_plan_s& p, const void* gx, void* gcoeff, hipStream_t s
 // per global level (q[2(s-1)], q[2(s-1)+1]) and for the coarsest values
 // (q[2(L+M)], q[2(L+M)+1]).
 struct QTab {
+  // the level's block tolerances and kappa: Delta = kap * tau (the block
+  // kernels form their blocks' classes from these themselves)
+  const double* tau = nullptr;
+  double kap = 0.0;
   // per block, per class of node position (first face / interior / last face
   // along z, y, x: 27 classes, index 9 cz + 3 cy + cx) the smallest Delta and
   // the largest 1/Delta over the blocks that contain such a node
@@ -358,16 +362,18 @@ struct QPrep {
 constexpr int kCoarseSlotHost = 8;
 // where a plan's quantizer tables live (host arithmetic, no launches)
 QPrep qprep_layout(bm_plan_s& p, const double* block_tol);
-// builds the tables on the device (stream-ordered) and returns their layout;
-// with the kept map (quant_keep) only the overflow flag is cleared, and not
-// even that for the dequantizing callers (clear_flag false: they set no flag)
-QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool clear_flag = true);
+// propagates the map and builds what the caller needs on the device
+// (stream-ordered): the class tables of every level (tables) or only those of
+// 33-node levels, whose kernels read them; with the kept map (quant_keep) only
+// the overflow flag is cleared, and not even that for the dequantizing
+// callers (clear_flag false: they set no flag)
+QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool clear_flag = true, bool tables = true);
 // builds the tables of block_tol and keeps them (null: drops the kept ones)
 void quant_keep(bm_plan_s& p, const double* block_tol, hipStream_t st);
 
 // The same preparation for many fields at once: one field's inputs...
 struct PrepField {
-  const double* tau[9];       // block taus of local level s at [s-1] (level 1: the caller's map)
+  const double* tau[9];       // block taus of local level s at [s-1] (level 1: the caller's map; null: the launch's)
   int64_t nb[9][3];           // blocks per axis of local level s at [s-1]
   double kap[9];              // kappa of local level s at [s-1]
   double kapc;                // kappa of the coarsest values (M == 0)
@@ -381,15 +387,19 @@ struct PrepField {
 };
 PrepField prep_field(bm_plan_s& p, const double* block_tol, const QPrep& q);
 // ...and the task lists of its launches: propagation into level s+1 (index
-// s), tables of level s (index s; index 0: coarsest values), each a device
-// prefix array over the fields (first[nf] = total tasks)
+// s; only where a field has more blocks than one workgroup propagates),
+// tables of level s (index s; index 0: coarsest values), each a device prefix
+// array over the fields (first[nf] = total tasks)
+constexpr int64_t kPropOneGroup = 4096;   // level-2 blocks that one workgroup propagates
 struct PrepStages {
   const int64_t* prop_first[9] = {};
   int64_t prop_n[9] = {};
   const int64_t* tab_first[9] = {};
   int64_t tab_n[9] = {};
+  bool fields = true;         // a field needs the per-field launch (propagation, tau_global, flag)
 };
-void launch_prep_batch(const PrepStages& g, const PrepField* F, int nf, hipStream_t st);
+void launch_prep_batch(const PrepStages& g, const PrepField* F, int nf, const double* map, bool clear_flag,
+                       hipStream_t st);
 
 // fused decompose + quantize and dequantize + recompose (codes in place)
 void decompose_quantize(bm_plan_s& p, const void* x, const double* block_tol, int32_t* codes, bm_qstats* stats,
@@ -414,7 +424,7 @@ void local_recompose_nest(const bm_plan_s& p, int s, const void* coeff, const vo
 
 // many fields per launch (block levels): per-field kernel arguments are
 // built on the host (block_*_args writes block_args_size bytes), uploaded,
-// and one persistent launch covers block_groups(p_f, s) groups of every field
+// and one launch covers block_groups(p_f, s) groups of every field
 int64_t block_groups(const bm_plan_s& p, int s, bool dec);
 size_t block_args_size(const bm_plan_s& p, bool dec);
 void block_dec_args(const bm_plan_s& p, int s, const View3& src, bool first, void* coeff, void* cout, int32_t* codes,

@@ -72,8 +72,8 @@ struct DecArgs {
   FastDiv fnb2, fnb1;     // block index -> (bz, by, bx)
   // fused quantization (codes written instead of coefficients)
   int32_t* codes;         // same layout as coeff
-  QTab tab;               // this level's block tables
-  QTab ctab;              // coarsest-value tables (last block level when M == 0)
+  const double* tau;      // this level's block tolerances, kappa of its details and of the
+  double kap, kapc;       // coarsest values (last block level when M == 0)
   int coarsest_here;
   int64_t* flag;          // set when a code does not fit in int32
   // last block level followed by a global level: its details are formed
@@ -100,7 +100,8 @@ struct RecArgs {
   int64_t nb[3], nblocks, nwg, per;
   FastDiv fnb2, fnb1;
   const int32_t* codes;   // fused dequantization: codes instead of coefficients
-  QTab tab, ctab;
+  const double* tau;      // as in DecArgs
+  double kap, kapc;
   int coarsest_here;
   // last block level under a global level: the coarse values of G^s are
   // interpolated here from the next level's coarse grid G^{s+1} plus its
@@ -132,7 +133,8 @@ constexpr int nest_offset() {
 // SRC_LDS: the level's input is the coarse values a (2B-1)-node block level
 // left in LDS for this group (nested schedule), not the source grid.
 template <typename T, int B, bool Q, int NBG = Geo<B, sizeof(T)>::NB, bool SRC_LDS = false>
-__device__ __attribute__((always_inline)) inline void decompose_group(const DecArgs<T>& a, int64_t g, T* lds) {
+__device__ __attribute__((always_inline)) inline void decompose_group(const DecArgs<T>& a, int64_t g, T* lds,
+                                                                        double (*cls)[NBG * 27]) {
   using G = Geo<B, sizeof(T)>;
   constexpr int BB = G::BB, MC = G::MC, MI = G::MI, NB = NBG;
   constexpr int PREG = SRC_LDS ? Geo<2 * B - 1>::DEC_LDS : G::DEC_LDS;   // LDS elements per block
@@ -159,9 +161,9 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
   // a node on a shared face is written by the block that starts on it
   const bool owned = (y < B - 1 || by == a.nb[1] - 1) && (x < B - 1 || bx == a.nb[2] - 1);
   const bool lastz = bz == a.nb[0] - 1;
-  // fused quantization: this column's 1/Delta, loaded early so the latency hides
-  double iv[3];
-  if (Q && act) column_class<B>(a.tab.cinv, blk, y, x, iv);
+  // fused quantization: the blocks' 1/Delta classes (read after the barrier)
+  if (Q)
+    class_table<NB, true>(a.tau, a.kap, a.kapc, a.coarsest_here, g * NB, a.nblocks, a.fnb2, a.fnb1, a.nb, cls);
   T v[B];
   if (act && SRC_LDS) {
     const T* cc = lds + bl * PREG;                   // [B][B][B] coarse values of the finer level
@@ -225,6 +227,8 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
         }
       } else {
         int32_t* dst = a.codes + oz * a.cs[0] + gy * a.cs[1] + gx * a.cs[2];
+        double iv[3];
+        column_class<B>(cls[0], bl, y, x, iv);
         unsigned bad = 0;
 #pragma unroll
         for (int z = 1; z < B - 1; z += 2) dst[z * a.cs0] = quant(v[z], iv[zcase<B>(z)], false, bad);
@@ -280,7 +284,7 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
     if (Q && a.coarsest_here) {
       // last level of the hierarchy: codes for the coarsest values
       double ci[3];
-      column_class<B>(a.ctab.cinv, blk, y, x, ci);
+      column_class<B>(cls[1], bl, y, x, ci);
       int32_t* dst = a.codes + oz * a.cs[0] + gy * a.cs[1] + gx * a.cs[2];
       unsigned bad = 0;
 #pragma unroll
@@ -351,7 +355,8 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
 // after them; MODE 2 is that finer level, which reads its coarse values
 // there instead of from the coarse grid.
 template <typename T, int B, bool Q, int NBG = Geo<B, sizeof(T), false>::NB, int MODE = 0>
-__device__ __attribute__((always_inline)) inline void recompose_group(const RecArgs<T>& a, int64_t g, T* lds) {
+__device__ __attribute__((always_inline)) inline void recompose_group(const RecArgs<T>& a, int64_t g, T* lds,
+                                                                        double (*cls)[NBG * 27]) {
   using G = Geo<B, sizeof(T), false>;
   constexpr int BB = G::BB, MC = G::MC, MI = G::MI, NB = NBG;
   constexpr int PREG = MODE == 1 ? Geo<2 * B - 1>::REC_LDS : G::REC_LDS;   // LDS elements per block
@@ -372,56 +377,57 @@ __device__ __attribute__((always_inline)) inline void recompose_group(const RecA
   int64_t bz = 0, by = 0, bx = 0;
   if (act) block_coords(uint32_t(blk), a.fnb2, a.fnb1, a.nb, bz, by, bx);
   const int64_t oz = bz * (B - 1), gy = by * (B - 1) + y, gx = bx * (B - 1) + x;
-  // fused with the next (global) level: its coarse values over this block,
-  // UC2[H][H][H] (in T2, which is first written by the y pass)
-  constexpr int H = (MC + 1) / 2;
-  T* UC2 = T2;
-  if (a.fuse) {
-    if (act) {
-      const int64_t h0 = (MC - 1) / 2, pl2 = a.cn2[1] * a.cn2[2];
-      const T* src = a.cin2 + bz * h0 * pl2 + by * h0 * a.cn2[2] + bx * h0;
-      for (int i = tb; i < H * H * H; i += BB) {
-        const int k0 = i / (H * H), r = i - k0 * H * H, k1 = r / H, k2 = r - k1 * H;
-        UC2[i] = src[k0 * pl2 + k1 * a.cn2[2] + k2];
-      }
-    }
-    __syncthreads();
-  }
   T w[B], ce[MC];
+  int32_t qv[B];
+  // the whole column is read (coarse nodes too, then zeroed): one load per
+  // node, on its way before anything is waited for
+  const int64_t off = oz * a.cs[0] + gy * a.cs[1] + gx * a.cs[2];
   if (act) {
-    // the whole column is read (coarse nodes too, then zeroed): one load per node
-    const int64_t off = oz * a.cs[0] + gy * a.cs[1] + gx * a.cs[2];
     if (!Q) {
       const T* col = a.coeff + off;
 #pragma unroll
       for (int z = 0; z < B; ++z) w[z] = col[z * a.cs0];
     } else {
-      // fused dequantization: c_hat = (T)(q * Delta)
       const int32_t* col = a.codes + off;
-      int32_t qv[B];
 #pragma unroll
       for (int z = 0; z < B; ++z) qv[z] = col[z * a.cs0];
+    }
+  }
+  // fused dequantization: the blocks' Delta classes
+  if (Q)
+    class_table<NB, false>(a.tau, a.kap, a.kapc, a.coarsest_here, g * NB, a.nblocks, a.fnb2, a.fnb1, a.nb, cls);
+  // fused with the next (global) level: its coarse values over this block,
+  // UC2[H][H][H] (in T2, which is first written by the y pass)
+  constexpr int H = (MC + 1) / 2;
+  T* UC2 = T2;
+  if (a.fuse && act) {
+    const int64_t h0 = (MC - 1) / 2, pl2 = a.cn2[1] * a.cn2[2];
+    const T* src = a.cin2 + bz * h0 * pl2 + by * h0 * a.cn2[2] + bx * h0;
+    for (int i = tb; i < H * H * H; i += BB) {
+      const int k0 = i / (H * H), r = i - k0 * H * H, k1 = r / H, k2 = r - k1 * H;
+      UC2[i] = src[k0 * pl2 + k1 * a.cn2[2] + k2];
+    }
+  }
+  if (Q || a.fuse) __syncthreads();
+  if (act) {
+    if (Q) {
+      // c_hat = (T)(q * Delta)
       double dd[3];
-      column_class<B>(a.tab.cdel, blk, y, x, dd);
+      column_class<B>(cls[0], bl, y, x, dd);
 #pragma unroll
       for (int z = 0; z < B; ++z) w[z] = T(mul_rn(double(qv[z]), dd[zcase<B>(z)]));
     }
     if (ecol) {
       if (Q && a.coarsest_here) {
-        const int32_t* col = a.codes + off;
-        int32_t qc[MC];
-#pragma unroll
-        for (int j = 0; j < MC; ++j) qc[j] = col[2 * j * a.cs0];
         double cd[3];
-        column_class<B>(a.ctab.cdel, blk, y, x, cd);
+        column_class<B>(cls[1], bl, y, x, cd);
 #pragma unroll
-        for (int j = 0; j < MC; ++j) ce[j] = T(mul_rn(double(qc[j]), cd[zcase<B>(2 * j)]));
+        for (int j = 0; j < MC; ++j) ce[j] = T(mul_rn(double(qv[2 * j]), cd[zcase<B>(2 * j)]));
       } else if (a.fuse) {
         // u at this column's coarse nodes = next level's detail + interpolant
         // of its coarse values (exactly the next level's recomposition)
         const int p = y >> 1, q = x >> 1, op = p & 1, oq = q & 1;
         const double del2 = Q ? *a.nqdel : 0.0;
-        const int32_t* qcol = a.codes + off;
         T in[MC];
         column_interp<T, MC>(p, q, [&](int J, int P, int K) { return UC2[(J * H + P) * H + K]; }, in);
 #pragma unroll
@@ -429,7 +435,7 @@ __device__ __attribute__((always_inline)) inline void recompose_group(const RecA
           if (((j & 1) | op | oq) == 0) {
             ce[j] = in[j];   // the next level's coarse value itself (exact)
           } else {
-            const T w2 = Q ? T(mul_rn(double(qcol[2 * j * a.cs0]), del2)) : w[2 * j];
+            const T w2 = Q ? T(mul_rn(double(qv[2 * j]), del2)) : w[2 * j];
             ce[j] = w2 + in[j];
           }
         }
@@ -513,17 +519,19 @@ __device__ __attribute__((always_inline)) inline void recompose_group(const RecA
 template <typename T, int B, bool Q>
 __global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_local_decompose(DecArgs<T> a) {
   __shared__ __attribute__((aligned(16))) T lds[Geo<B, sizeof(T)>::NB * Geo<B>::DEC_LDS];   // FP64 scratch inside
+  __shared__ double cls[Q ? 2 : 1][Geo<B, sizeof(T)>::NB * 27];   // Delta classes of the blocks
   const int64_t g = xcd_group(blockIdx.x, a.per);
   if (g >= a.nwg) return;
-  decompose_group<T, B, Q>(a, g, lds);
+  decompose_group<T, B, Q>(a, g, lds, cls);
 }
 
 template <typename T, int B, bool Q>
 __global__ __launch_bounds__((Geo<B, sizeof(T), false>::NT)) void k_local_recompose(RecArgs<T> a) {
   __shared__ T lds[Geo<B, sizeof(T), false>::NB * Geo<B>::REC_LDS];
+  __shared__ double cls[Q ? 2 : 1][Geo<B, sizeof(T), false>::NB * 27];   // Delta classes of the blocks
   const int64_t g = xcd_group(blockIdx.x, a.per);
   if (g >= a.nwg) return;
-  recompose_group<T, B, Q>(a, g, lds);
+  recompose_group<T, B, Q>(a, g, lds, cls);
 }
 
 // Nested schedule: block levels of 17- and 9-node blocks over the same
@@ -536,44 +544,45 @@ template <typename T, bool Q>
 __global__ __launch_bounds__((Geo<17, sizeof(T)>::NT)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_local_decompose_nest(DecArgs<T> a1, DecArgs<T> a2) {
   constexpr int NB = Geo<17, sizeof(T)>::NB;
   __shared__ __attribute__((aligned(16))) T lds[NB * Geo<17>::DEC_LDS];   // FP64 scratch inside
+  __shared__ double cls[Q ? 2 : 1][NB * 27];   // Delta classes of the blocks
   const int64_t g = xcd_group(blockIdx.x, a1.per);
   if (g >= a1.nwg) return;
-  decompose_group<T, 17, Q>(a1, g, lds);
+  decompose_group<T, 17, Q>(a1, g, lds, cls);
   __syncthreads();
-  decompose_group<T, 9, Q, NB, true>(a2, g, lds);
+  decompose_group<T, 9, Q, NB, true>(a2, g, lds, cls);
 }
 
 template <typename T, bool Q>
 __global__ __launch_bounds__((Geo<17, sizeof(T), false>::NT)) void k_local_recompose_nest(RecArgs<T> a2, RecArgs<T> a1) {
   constexpr int NB = Geo<17, sizeof(T), false>::NB;
   __shared__ __attribute__((aligned(16))) T lds[NB * Geo<17>::REC_LDS];
+  __shared__ double cls[Q ? 2 : 1][NB * 27];   // Delta classes of the blocks
   const int64_t g = xcd_group(blockIdx.x, a1.per);
   if (g >= a1.nwg) return;
-  recompose_group<T, 9, Q, NB, 1>(a2, g, lds);
+  recompose_group<T, 9, Q, NB, 1>(a2, g, lds, cls);
   __syncthreads();
-  recompose_group<T, 17, Q, NB, 2>(a1, g, lds);
+  recompose_group<T, 17, Q, NB, 2>(a1, g, lds, cls);
 }
 
-// Many fields in one persistent launch: task k is block group k - first[f]
-// of field f (first[] ascending, first[nf] = total, task_field); workgroups
-// stride over the tasks.
+// Many fields in one launch: workgroup k takes task k, block group
+// k - first[f] of field f (first[] ascending, first[nf] = total, task_field),
+// in the XCD order of a single field's launch.
 
-// (no wave target here: the per-field arguments come from memory and the
-// extra registers are cheaper than spills.  The field index is the same for
-// every lane of the workgroup; said so with readfirstlane, and with the
-// argument array read-only and unaliased, the record is read by scalar
-// loads instead of vector loads kept in vector registers: the FP32
-// decomposition went from 113 to 102 VGPRs, and a batched step of 256
-// fields from 5.61 to 5.14 ms)
+// (One workgroup per task and no loop over tasks: in a persistent launch the
+// compiler kept the addresses of 17 planes over the loop, 106 to 111 VGPRs
+// against 63, which left one FP32 decomposition workgroup per CU.  The field
+// index is the same for every lane of the workgroup; said so with
+// readfirstlane, and with the argument array read-only and unaliased, the
+// record is read by scalar loads.)
 template <typename T, int B, bool Q>
-__global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) void k_batch_decompose(
+__global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_batch_decompose(
     const DecArgs<T>* __restrict__ fa, const int64_t* __restrict__ first, int nf, int64_t ntasks) {
   __shared__ __attribute__((aligned(16))) T lds[Geo<B, sizeof(T)>::NB * Geo<B>::DEC_LDS];   // FP64 scratch inside
-  for (int64_t k = blockIdx.x; k < ntasks; k += gridDim.x) {
-    const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
-    decompose_group<T, B, Q>(fa[f], k - first[f], lds);
-    __syncthreads();
-  }
+  __shared__ double cls[Q ? 2 : 1][Geo<B, sizeof(T)>::NB * 27];   // Delta classes of the blocks
+  const int64_t k = xcd_group(blockIdx.x, (ntasks + 7) / 8);
+  if (k >= ntasks) return;
+  const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
+  decompose_group<T, B, Q>(fa[f], k - first[f], lds, cls);
 }
 
 template <typename T, int B, bool Q>
@@ -581,32 +590,32 @@ __global__ __launch_bounds__((Geo<B, sizeof(T), false>::NT)) void k_batch_recomp
                                                                               const int64_t* __restrict__ first, int nf,
                                                                               int64_t ntasks) {
   __shared__ T lds[Geo<B, sizeof(T), false>::NB * Geo<B>::REC_LDS];
-  for (int64_t k = blockIdx.x; k < ntasks; k += gridDim.x) {
-    const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
-    recompose_group<T, B, Q>(fa[f], k - first[f], lds);
-    __syncthreads();
-  }
+  __shared__ double cls[Q ? 2 : 1][Geo<B, sizeof(T), false>::NB * 27];   // Delta classes of the blocks
+  const int64_t k = xcd_group(blockIdx.x, (ntasks + 7) / 8);
+  if (k >= ntasks) return;
+  const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
+  recompose_group<T, B, Q>(fa[f], k - first[f], lds, cls);
 }
 
-// The nested schedule of every field in one persistent launch: task k is
+// The nested schedule of every field in one launch: task k is
 // block group k - first[f] of field f at its 17-node level (arguments f1[f]),
 // then the same group of its 9-node level (f2[f]) on the coarse values the
 // first left in LDS, as k_local_decompose_nest / k_local_recompose_nest do
 // for one field.
 template <typename T, bool Q>
-__global__ __launch_bounds__((Geo<17, sizeof(T)>::NT)) void k_batch_decompose_nest(
+__global__ __launch_bounds__((Geo<17, sizeof(T)>::NT)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_batch_decompose_nest(
     const DecArgs<T>* __restrict__ f1, const DecArgs<T>* __restrict__ f2, const int64_t* __restrict__ first, int nf,
     int64_t ntasks) {
   constexpr int NB = Geo<17, sizeof(T)>::NB;
   __shared__ __attribute__((aligned(16))) T lds[NB * Geo<17>::DEC_LDS];   // FP64 scratch inside
-  for (int64_t k = blockIdx.x; k < ntasks; k += gridDim.x) {
-    const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
-    const int64_t g = k - first[f];
-    decompose_group<T, 17, Q>(f1[f], g, lds);
-    __syncthreads();
-    decompose_group<T, 9, Q, NB, true>(f2[f], g, lds);
-    __syncthreads();
-  }
+  __shared__ double cls[Q ? 2 : 1][NB * 27];   // Delta classes of the blocks
+  const int64_t k = xcd_group(blockIdx.x, (ntasks + 7) / 8);
+  if (k >= ntasks) return;
+  const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
+  const int64_t g = k - first[f];
+  decompose_group<T, 17, Q>(f1[f], g, lds, cls);
+  __syncthreads();
+  decompose_group<T, 9, Q, NB, true>(f2[f], g, lds, cls);
 }
 
 template <typename T, bool Q>
@@ -615,14 +624,14 @@ __global__ __launch_bounds__((Geo<17, sizeof(T), false>::NT)) void k_batch_recom
     int64_t ntasks) {
   constexpr int NB = Geo<17, sizeof(T), false>::NB;
   __shared__ T lds[NB * Geo<17>::REC_LDS];
-  for (int64_t k = blockIdx.x; k < ntasks; k += gridDim.x) {
-    const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
-    const int64_t g = k - first[f];
-    recompose_group<T, 9, Q, NB, 1>(f2[f], g, lds);
-    __syncthreads();
-    recompose_group<T, 17, Q, NB, 2>(f1[f], g, lds);
-    __syncthreads();
-  }
+  __shared__ double cls[Q ? 2 : 1][NB * 27];   // Delta classes of the blocks
+  const int64_t k = xcd_group(blockIdx.x, (ntasks + 7) / 8);
+  if (k >= ntasks) return;
+  const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
+  const int64_t g = k - first[f];
+  recompose_group<T, 9, Q, NB, 1>(f2[f], g, lds, cls);
+  __syncthreads();
+  recompose_group<T, 17, Q, NB, 2>(f1[f], g, lds, cls);
 }
 
 // 32-bit z stride within one block column
@@ -661,9 +670,10 @@ DecArgs<T> dec_args(const bm_plan_s& p, int s, const View3& src, bool first, voi
   a.per = (a.nwg + 7) / 8;
   if (q) {
     a.codes = codes;
-    a.tab = q->lv[s - 1];
+    a.tau = q->lv[s - 1].tau;
+    a.kap = q->lv[s - 1].kap;
     a.coarsest_here = (p.M == 0 && s == p.L) ? 1 : 0;
-    if (a.coarsest_here) a.ctab = q->lv[kCoarseSlotHost];
+    if (a.coarsest_here) a.kapc = q->lv[kCoarseSlotHost].kap;
     a.flag = q->flag;
   }
   a.fuse = (p.fuse_next && s == p.L) ? 1 : 0;
@@ -716,9 +726,10 @@ RecArgs<T> rec_args(const bm_plan_s& p, int s, const void* coeff, const void* ci
   a.per = (a.nwg + 7) / 8;
   if (q) {
     a.codes = codes;
-    a.tab = q->lv[s - 1];
+    a.tau = q->lv[s - 1].tau;
+    a.kap = q->lv[s - 1].kap;
     a.coarsest_here = (p.M == 0 && s == p.L) ? 1 : 0;
-    if (a.coarsest_here) a.ctab = q->lv[kCoarseSlotHost];
+    if (a.coarsest_here) a.kapc = q->lv[kCoarseSlotHost].kap;
   }
   a.fuse = (p.fuse_next && s == p.L) ? 1 : 0;
   if (a.fuse) {
@@ -742,6 +753,13 @@ void launch_rec(const bm_plan_s& p, int s, const void* coeff, const void* cin, v
 }
 
 
+// workgroups of a launch over ntasks tasks in XCD order
+unsigned task_grid(int64_t ntasks) {
+  const int64_t g = 8 * ((ntasks + 7) / 8);
+  if (g >= (int64_t(1) << 31)) fail(BM_EUNSUPPORTED, "too many block groups in one batch");
+  return unsigned(g);
+}
+
 template <typename T, int B>
 void launch_batch(bool dec, bool quant, const void* args, const int64_t* first, int nf, int64_t ntasks,
                   hipStream_t st) {
@@ -751,20 +769,20 @@ void launch_batch(bool dec, bool quant, const void* args, const int64_t* first, 
     const auto* fa = static_cast<const DecArgs<T>*>(args);
     if (quant) {
       auto k = k_batch_decompose<T, B, true>;
-      hipLaunchKernelGGL(k, dim3(resident_grid(k, G::NT, ntasks)), dim3(G::NT), 0, st, fa, first, nf, ntasks);
+      hipLaunchKernelGGL(k, dim3(task_grid(ntasks)), dim3(G::NT), 0, st, fa, first, nf, ntasks);
     } else {
       auto k = k_batch_decompose<T, B, false>;
-      hipLaunchKernelGGL(k, dim3(resident_grid(k, G::NT, ntasks)), dim3(G::NT), 0, st, fa, first, nf, ntasks);
+      hipLaunchKernelGGL(k, dim3(task_grid(ntasks)), dim3(G::NT), 0, st, fa, first, nf, ntasks);
     }
   } else {
     using R = Geo<B, sizeof(T), false>;
     const auto* fa = static_cast<const RecArgs<T>*>(args);
     if (quant) {
       auto k = k_batch_recompose<T, B, true>;
-      hipLaunchKernelGGL(k, dim3(resident_grid(k, R::NT, ntasks)), dim3(R::NT), 0, st, fa, first, nf, ntasks);
+      hipLaunchKernelGGL(k, dim3(task_grid(ntasks)), dim3(R::NT), 0, st, fa, first, nf, ntasks);
     } else {
       auto k = k_batch_recompose<T, B, false>;
-      hipLaunchKernelGGL(k, dim3(resident_grid(k, R::NT, ntasks)), dim3(R::NT), 0, st, fa, first, nf, ntasks);
+      hipLaunchKernelGGL(k, dim3(task_grid(ntasks)), dim3(R::NT), 0, st, fa, first, nf, ntasks);
     }
   }
   BM_HIP(hipGetLastError());
@@ -963,12 +981,12 @@ void launch_batch_nest(bool dec, const void* a1, const void* a2, const int64_t* 
   if (dec) {
     auto k = k_batch_decompose_nest<T, true>;
     const int nt = Geo<17, sizeof(T)>::NT;
-    hipLaunchKernelGGL(k, dim3(resident_grid(k, nt, ntasks)), dim3(nt), 0, st, static_cast<const DecArgs<T>*>(a1),
+    hipLaunchKernelGGL(k, dim3(task_grid(ntasks)), dim3(nt), 0, st, static_cast<const DecArgs<T>*>(a1),
                        static_cast<const DecArgs<T>*>(a2), first, nf, ntasks);
   } else {
     auto k = k_batch_recompose_nest<T, true>;
     const int nt = Geo<17, sizeof(T), false>::NT;
-    hipLaunchKernelGGL(k, dim3(resident_grid(k, nt, ntasks)), dim3(nt), 0, st, static_cast<const RecArgs<T>*>(a1),
+    hipLaunchKernelGGL(k, dim3(task_grid(ntasks)), dim3(nt), 0, st, static_cast<const RecArgs<T>*>(a1),
                        static_cast<const RecArgs<T>*>(a2), first, nf, ntasks);
   }
   BM_HIP(hipGetLastError());

@@ -730,7 +730,8 @@ __global__ __launch_bounds__(NT) void k_qoi_final(QArgs a, const T* s, const Qoi
 }
 
 QPrep qprep_layout(bm_plan_s& p, const double* block_tol) {
-  (void)block_tol;
+  const std::vector<double> w = level_weights(p);
+  const double eta = p.cfg.eta;
   if (p.L > 8) fail(BM_EUNSUPPORTED, "more than 8 local levels");
   QPrep a{};
   a.flag = p.ws.counters + 2;
@@ -742,6 +743,8 @@ QPrep qprep_layout(bm_plan_s& p, const double* block_tol) {
     const int64_t nbs = prod3(p.lv[s - 1].nb);
     const int64_t off = p.ws.tol_off[s];
     QTab& t = a.lv[s - 1];
+    t.tau = s == 1 ? block_tol : p.ws.tolbuf + off;
+    t.kap = (2.0 * (1.0 - eta)) * w[s - 1] / p.lv[s - 1].gain;
     t.cdel = cls + 54 * off;
     t.cinv = cls + 54 * off + 27 * nbs;
     for (int d = 0; d < 3; ++d) t.nb[d] = p.lv[s - 1].nb[d];
@@ -749,6 +752,8 @@ QPrep qprep_layout(bm_plan_s& p, const double* block_tol) {
   if (p.L > 0 && p.M == 0) {
     // coarsest values (no gain), over the level-L blocks
     QTab& t = a.lv[kCoarseSlotHost];
+    t.tau = a.lv[p.L - 1].tau;
+    t.kap = (2.0 * (1.0 - eta)) * w[p.nlev];
     t.cdel = cls + 54 * tot;
     t.cinv = cls + 54 * tot + 27 * nlastb;
     for (int d = 0; d < 3; ++d) t.nb[d] = p.lv[p.L - 1].nb[d];
@@ -767,7 +772,7 @@ __global__ void k_clear_flag(int64_t* flag) {
 }
 }  // namespace
 
-QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool clear_flag) {
+QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool clear_flag, bool tables) {
   const QPrep a = qprep_layout(p, block_tol);
   if (block_tol && block_tol == p.ws.kept_tol) {   // the kept tables are this map's
     if (clear_flag) {
@@ -777,19 +782,24 @@ QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool 
     return a;
   }
   p.ws.kept_tol = nullptr;   // the tables built here replace the kept ones
-  const PrepField f = prep_field(p, block_tol, a);
+  // the record holds everything but the map, which comes with each launch: a
+  // new map costs no upload
+  const PrepField f = prep_field(p, nullptr, a);
   static_assert(sizeof(PrepField) <= kPrepFirst, "field record too large");
   int64_t cnt_prop[9] = {}, cnt_tab[9] = {};
-  for (int s = 1; s < 9; ++s) cnt_prop[s] = p.L > s ? prod3(p.lv[s].nb) : 0;
-  for (int s = 1; s < 9; ++s) cnt_tab[s] = p.L >= s ? 27 * prod3(p.lv[s - 1].nb) : 0;
-  cnt_tab[0] = (p.L > 0 && p.M == 0) ? 27 * prod3(p.lv[p.L - 1].nb) : 0;
+  if (p.L > 1 && prod3(p.lv[1].nb) > kPropOneGroup)
+    for (int s = 1; s < 9; ++s) cnt_prop[s] = p.L > s ? prod3(p.lv[s].nb) : 0;
+  auto wants = [&](int s) { return tables || p.lv[s - 1].b == 33; };
+  for (int s = 1; s < 9; ++s) cnt_tab[s] = p.L >= s && wants(s) ? 27 * prod3(p.lv[s - 1].nb) : 0;
+  cnt_tab[0] = (p.L > 0 && p.M == 0 && wants(p.L)) ? 27 * prod3(p.lv[p.L - 1].nb) : 0;
   if (!p.ws.prep_set) {
     std::vector<int64_t> first(4 * 9);
     for (int s = 0; s < 9; ++s) {
       first[2 * s] = 0;
-      first[2 * s + 1] = cnt_prop[s];
+      first[2 * s + 1] = s >= 1 && p.L > s ? prod3(p.lv[s].nb) : 0;
       first[18 + 2 * s] = 0;
-      first[18 + 2 * s + 1] = cnt_tab[s];
+      first[18 + 2 * s + 1] = s == 0 ? (p.L > 0 && p.M == 0 ? 27 * prod3(p.lv[p.L - 1].nb) : 0)
+                                     : (p.L >= s ? 27 * prod3(p.lv[s - 1].nb) : 0);
     }
     BM_HIP(hipMemcpy(static_cast<uint8_t*>(p.ws.prep_dev) + kPrepFirst, first.data(), first.size() * sizeof(int64_t),
                      hipMemcpyHostToDevice));
@@ -810,7 +820,8 @@ QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool 
     g.tab_first[s] = first + 18 + 2 * s;
     g.tab_n[s] = cnt_tab[s];
   }
-  launch_prep_batch(g, static_cast<const PrepField*>(p.ws.prep_dev), 1, st);
+  g.fields = clear_flag || p.L != 1 || p.M > 0;
+  launch_prep_batch(g, static_cast<const PrepField*>(p.ws.prep_dev), 1, block_tol, clear_flag, st);
   return a;
 }
 
@@ -825,25 +836,55 @@ void quant_keep(bm_plan_s& p, const double* block_tol, hipStream_t st) {
 
 namespace {
 
-// Eq. 2 from level s to level s+1 (s 1-based) for every field that has it
-__global__ void k_batch_propagate(const PrepField* F, const int64_t* first, int nf, int64_t ntot, int s) {
+// taus of local level s (1-based); map: the level-1 map of a record without one
+__device__ inline const double* taus(const PrepField& P, int s, const double* map) {
+  return s == 1 && map ? map : P.tau[s - 1];
+}
+
+// Eq. 2: block i of level s+1 takes the smallest tau of the level-s blocks
+// that share a node with it.  It spans blocks 2Z, 2Z+1 of level s and touches
+// 2Z-1, 2Z+2 (nested: it is block Z itself, touching Z-1, Z+1); the 4^3 box
+// is read with clamped coordinates (a repeated block changes no minimum), so
+// that its loads overlap instead of following each other.
+__device__ inline double propagate_task(const PrepField& P, int s, const double* tau, uint32_t i) {
+  const uint32_t n0 = uint32_t(P.nb[s - 1][0]), n1 = uint32_t(P.nb[s - 1][1]), n2 = uint32_t(P.nb[s - 1][2]);
+  const uint32_t m1 = uint32_t(P.nb[s][1]), m2 = uint32_t(P.nb[s][2]);
+  const uint32_t t = i / m2, X = i - t * m2, Z = t / m1, Y = t - Z * m1;
+  const uint32_t f = P.nested ? 1u : 2u;
+  uint32_t z[4], y[4], x[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int o = (k < int(f) + 2 ? k : int(f) + 1) - 1;
+    auto at = [&](uint32_t c, uint32_t n) {
+      const int v = int(c * f) + o;
+      return uint32_t(v < 0 ? 0 : v >= int(n) ? int(n) - 1 : v);
+    };
+    z[k] = at(Z, n0);
+    y[k] = at(Y, n1);
+    x[k] = at(X, n2);
+  }
+  double v = INFINITY;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    double r[16];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r[4 * b + c] = tau[(z[a] * n1 + y[b]) * n2 + x[c]];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v = fmin(v, r[k]);
+  }
+  return v;
+}
+
+// one step for every field that has level s+1
+__global__ void k_batch_propagate(const PrepField* F, const int64_t* first, int nf, int64_t ntot, int s,
+                                  const double* map) {
   for (int64_t k = int64_t(blockIdx.x) * NT + threadIdx.x; k < ntot; k += int64_t(gridDim.x) * NT) {
     const int f = task_field(first, nf, k);
     const PrepField& P = F[f];
     const int64_t i = k - first[f];
-    const int64_t* nb = P.nb[s - 1];
-    const int64_t* nn = P.nb[s];
-    const int64_t X = i % nn[2], t = i / nn[2], Y = t % nn[1], Z = t / nn[1];
-    // next-level block (Z, Y, X) spans blocks 2Z, 2Z+1 of this level and
-    // touches 2Z-1, 2Z+2; nested, it is block Z itself, touching Z-1, Z+1
-    const int64_t c0 = P.nested ? Z : 2 * Z, c1 = P.nested ? Y : 2 * Y, c2 = P.nested ? X : 2 * X;
-    const int64_t e = P.nested ? 1 : 2;
-    double v = INFINITY;
-    for (int64_t z = i64max(0, c0 - 1); z <= i64min(nb[0] - 1, c0 + e); ++z)
-      for (int64_t y = i64max(0, c1 - 1); y <= i64min(nb[1] - 1, c1 + e); ++y)
-        for (int64_t x = i64max(0, c2 - 1); x <= i64min(nb[2] - 1, c2 + e); ++x)
-          v = fmin(v, P.tau[s - 1][(z * nb[1] + y) * nb[2] + x]);
-    const_cast<double*>(P.tau[s])[i] = v;
+    const_cast<double*>(P.tau[s])[i] = propagate_task(P, s, taus(P, s, map), uint32_t(i));
   }
 }
 
@@ -856,11 +897,11 @@ __global__ void k_batch_propagate(const PrepField* F, const int64_t* first, int 
 // (last face) the block and the one after.  32-bit index arithmetic (a
 // level has fewer than 2^32 / 27 blocks).
 // one task of k_batch_tables: task i of field P
-__device__ inline void table_task(const PrepField& P, int s, uint32_t i) {
+__device__ inline void table_task(const PrepField& P, int s, uint32_t i, const double* map) {
   const int li = s > 0 ? s - 1 : P.L - 1;
   const QTab& T = s > 0 ? P.tab[li] : P.tab[kCoarseSlotHost];
   const double kap = s > 0 ? P.kap[li] : P.kapc;
-  const double* tau = P.tau[li];
+  const double* tau = taus(P, li + 1, map);
   const uint32_t blk = i / 27u;
   const int c = int(i - blk * 27u);
   const int cls[3] = {c / 9, (c / 3) % 3, c % 3};
@@ -886,58 +927,69 @@ __device__ inline void table_task(const PrepField& P, int s, uint32_t i) {
   const_cast<double*>(T.cinv)[i] = iv;
 }
 
-__global__ void k_batch_tables(const PrepField* F, const int64_t* first, int nf, int64_t ntot, int s) {
+__global__ void k_batch_tables(const PrepField* F, const int64_t* first, int nf, int64_t ntot, int s,
+                               const double* map) {
   if (nf == 1) {
     // one field: its record is the same for every lane (scalar loads)
     for (int64_t k = int64_t(blockIdx.x) * NT + threadIdx.x; k < ntot; k += int64_t(gridDim.x) * NT)
-      table_task(F[0], s, uint32_t(k - first[0]));
+      table_task(F[0], s, uint32_t(k - first[0]), map);
     return;
   }
   for (int64_t k = int64_t(blockIdx.x) * NT + threadIdx.x; k < ntot; k += int64_t(gridDim.x) * NT) {
     const int f = task_field(first, nf, k);
-    table_task(F[f], s, uint32_t(k - first[f]));
+    table_task(F[f], s, uint32_t(k - first[f]), map);
   }
 }
 
-// tau_global (minimum over the last block level, or the single map value
-// when there is none) and the scalar Deltas; one workgroup per field, which
-// also clears the field's overflow flag.
+// One workgroup per field: the propagation (prop: unless launches of many
+// workgroups did it), tau_global (minimum over the last block level, or the
+// single map value when there is none) and the scalar Deltas where a global
+// level or the coarsest values use them, and the overflow flag cleared.
 constexpr int kScalarNT = 1024;
 
-__global__ __launch_bounds__(kScalarNT) void k_batch_scalar(const PrepField* F) {
-  __shared__ double red[kScalarNT];
+__global__ __launch_bounds__(kScalarNT) void k_batch_prep(const PrepField* F, const double* map, int prop, int clear) {
+  __shared__ double red[kScalarNT / 64];
   const PrepField& P = F[blockIdx.x];
+  const int tid = threadIdx.x;
+  if (clear && tid == 0) *P.flag = 0;
+  if (prop) {
+    for (int s = 1; s < P.L; ++s) {
+      const uint32_t n = uint32_t(P.nb[s][0] * P.nb[s][1] * P.nb[s][2]);
+      const double* tau = taus(P, s, map);
+      double* out = const_cast<double*>(P.tau[s]);
+      for (uint32_t i = tid; i < n; i += kScalarNT) out[i] = propagate_task(P, s, tau, i);
+      __syncthreads();   // the next level reads what this workgroup wrote
+    }
+  }
+  if (P.L > 0 && P.M == 0) return;
   double m = INFINITY;
   if (P.L > 0) {
     const int64_t* nb = P.nb[P.L - 1];
     const int64_t n = nb[0] * nb[1] * nb[2];
-    const double* tau = P.tau[P.L - 1];
+    const double* tau = taus(P, P.L, map);
     // eight independent loads in flight per lane
     double mm[8] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
-    int64_t i = threadIdx.x;
+    int64_t i = tid;
     for (; i + 7 * kScalarNT < n; i += 8 * kScalarNT)
 #pragma unroll
       for (int u = 0; u < 8; ++u) mm[u] = fmin(mm[u], tau[i + u * kScalarNT]);
     for (; i < n; i += kScalarNT) mm[0] = fmin(mm[0], tau[i]);
 #pragma unroll
     for (int u = 0; u < 8; ++u) m = fmin(m, mm[u]);
-  } else if (threadIdx.x == 0) {
-    m = P.tau[0][0];
+  } else if (tid == 0) {
+    m = taus(P, 1, map)[0];
   }
-  red[threadIdx.x] = m;
+  for (int off = 32; off > 0; off >>= 1) m = fmin(m, __shfl_down(m, off, 64));
+  if ((tid & 63) == 0) red[tid >> 6] = m;
   __syncthreads();
-  for (int w = kScalarNT / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] = fmin(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    *P.tg = red[0];
-    *P.flag = 0;
-  }
-  if (threadIdx.x <= P.nlev) {
-    const double d = red[0] * P.kq[threadIdx.x];
-    P.q[2 * threadIdx.x] = d;
-    P.q[2 * threadIdx.x + 1] = 1.0 / d;
+  m = red[0];
+#pragma unroll
+  for (int k = 1; k < kScalarNT / 64; ++k) m = fmin(m, red[k]);
+  if (tid == 0) *P.tg = m;
+  if (tid <= P.nlev) {
+    const double d = m * P.kq[tid];
+    P.q[2 * tid] = d;
+    P.q[2 * tid + 1] = 1.0 / d;
   }
 }
 
@@ -955,12 +1007,14 @@ PrepField prep_field(bm_plan_s& p, const double* block_tol, const QPrep& q) {
   for (int s = 1; s <= p.L; ++s) {
     f.tau[s - 1] = s == 1 ? block_tol : p.ws.tolbuf + p.ws.tol_off[s];
     for (int d = 0; d < 3; ++d) f.nb[s - 1][d] = p.lv[s - 1].nb[d];
-    f.kap[s - 1] = (2.0 * (1.0 - eta)) * w[s - 1] / p.lv[s - 1].gain;
+    f.kap[s - 1] = q.lv[s - 1].kap;
     f.tab[s - 1] = q.lv[s - 1];
+    f.tab[s - 1].tau = nullptr;
   }
   if (p.L == 0) f.tau[0] = block_tol;
   f.kapc = (2.0 * (1.0 - eta)) * w[p.nlev];
   f.tab[kCoarseSlotHost] = q.lv[kCoarseSlotHost];
+  f.tab[kCoarseSlotHost].tau = nullptr;   // (the record holds no map pointer of its own)
   f.tg = p.ws.tolbuf + p.ws.tol_off[p.L + 1];
   f.q = p.ws.qparam;
   for (int s = 1; s <= p.nlev; ++s) f.kq[s - 1] = (2.0 * (1.0 - eta)) * w[s - 1] / p.lv[s - 1].gain;
@@ -969,16 +1023,19 @@ PrepField prep_field(bm_plan_s& p, const double* block_tol, const QPrep& q) {
   return f;
 }
 
-void launch_prep_batch(const PrepStages& g, const PrepField* F, int nf, hipStream_t st) {
+void launch_prep_batch(const PrepStages& g, const PrepField* F, int nf, const double* map, bool clear_flag,
+                       hipStream_t st) {
   for (int s = 1; s < 9; ++s)
     if (g.prop_n[s] > 0)
       hipLaunchKernelGGL(k_batch_propagate, dim3(grid_for(g.prop_n[s])), dim3(NT), 0, st, F, g.prop_first[s], nf,
-                         g.prop_n[s], s);
+                         g.prop_n[s], s, map);
+  if (g.fields)
+    hipLaunchKernelGGL(k_batch_prep, dim3(unsigned(nf)), dim3(kScalarNT), 0, st, F, map, g.prop_n[1] > 0 ? 0 : 1,
+                       clear_flag ? 1 : 0);
   for (int s = 0; s < 9; ++s)
     if (g.tab_n[s] > 0)
       hipLaunchKernelGGL(k_batch_tables, dim3(grid_for(g.tab_n[s])), dim3(NT), 0, st, F, g.tab_first[s], nf,
-                         g.tab_n[s], s);
-  hipLaunchKernelGGL(k_batch_scalar, dim3(unsigned(nf)), dim3(kScalarNT), 0, st, F);
+                         g.tab_n[s], s, map);
   BM_HIP(hipGetLastError());
 }
 
