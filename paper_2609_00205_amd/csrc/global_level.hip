@@ -100,10 +100,11 @@ __device__ inline void load_corners(Cell<T>& k, int64_t cz, int64_t cy, int64_t 
         k.c[dz][dy][dx] = (dz <= k.oz && dy <= k.oy && dx <= k.ox) ? rd(cz + dz, cy + dy, cx + dx) : T(0);
 }
 
+// cells first, first + step, ...
 template <typename T>
-__global__ __launch_bounds__(NT) void k_details(DetArgs<T> a) {
+__device__ inline void cell_details(const DetArgs<T>& a, int64_t first, int64_t step) {
   const int64_t tot = a.m.n0 * a.m.n1 * a.m.n2;
-  for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < tot; i += int64_t(gridDim.x) * NT) {
+  for (int64_t i = first; i < tot; i += step) {
     int64_t cz, cy, cx;
     unflat(i, a.m, cz, cy, cx);
     const int64_t z = a.cm0 ? 2 * cz : cz, y = a.cm1 ? 2 * cy : cy, x = a.cm2 ? 2 * cx : cx;
@@ -135,6 +136,11 @@ __global__ __launch_bounds__(NT) void k_details(DetArgs<T> a) {
         a.coeff[o] = d;
     }
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(NT) void k_details(DetArgs<T> a) {
+  cell_details(a, int64_t(blockIdx.x) * NT + threadIdx.x, int64_t(gridDim.x) * NT);
 }
 
 template <typename T>
@@ -668,12 +674,19 @@ void launch_pass(const bm_plan_s& p, int s, int axis, const View3& in, const int
 constexpr int kPlaneNT = 1024;
 constexpr int kPlaneLds = 152 * 1024;
 
+// A level of up to this many cells has its details written by the plane pass's
+// launch (129^3 FP32 into 512^3 codes 20.2 + 13.9 -> 26.4 us, 65^3 4.6 + 7.1
+// -> 7.8); beyond it the workgroups of 152 KB LDS would hold back what k_details
+// keeps in flight.
+constexpr int64_t kDetCells = int64_t(1) << 19;
+
 template <typename T>
 struct PlaneArgs {
   const T* in;
   const int32_t* qin;    // optional: codes (same strides), times *qdel
   const double* qdel;
   int64_t is[3];         // input strides
+  int64_t planes;
   int n1, n2;            // plane dims (y, x)
   int m1, m2;            // result dims
   FastDiv fn2;           // plane index -> (y, x)
@@ -701,9 +714,18 @@ __device__ inline T restrict_row(int J, int nl, int m, V v) {
   return T(3) * r;
 }
 
-template <typename T, int Q>
-__global__ __launch_bounds__(kPlaneNT) void k_plane_pass(PlaneArgs<T> a) {
+// DET: the workgroups past the planes (a.planes) write the level's details, which need
+// the same grid: a launch less, and cells run on the CUs that have no plane.
+template <typename T, int Q, bool DET>
+__global__ __launch_bounds__(kPlaneNT) void k_plane_pass(PlaneArgs<T> a, DetArgs<T> det) {
   __shared__ __align__(16) unsigned char smem[kPlaneLds];
+  if constexpr (DET) {
+    const int64_t k = int64_t(blockIdx.x) - a.planes;
+    if (k >= 0) {
+      cell_details(det, k * kPlaneNT + threadIdx.x, (int64_t(gridDim.x) - a.planes) * kPlaneNT);
+      return;
+    }
+  }
   const int n1 = a.n1, n2 = a.n2, m1 = a.m1, m2 = a.m2, sr = a.sr, sp = a.sp;
   T* px = reinterpret_cast<T*>(smem);                 // [m2] pivots along x
   T* py = px + m2;                                    // [m1] pivots along y
@@ -781,7 +803,7 @@ __global__ __launch_bounds__(kPlaneNT) void k_plane_pass(PlaneArgs<T> a) {
 // fit a workgroup's LDS or the two axes take different row layouts.
 template <typename T>
 bool launch_plane(const bm_plan_s& p, int s, const View3& in, bool mask, void* out, const int32_t* qin,
-                  const double* qdel, hipStream_t st, bool solve_only = false) {
+                  const double* qdel, hipStream_t st, bool solve_only = false, const DetArgs<T>* det = nullptr) {
   const Level& L = p.lv[s - 1];
   if (!p.plane_pass || !L.coarsen[1] || !L.coarsen[2]) return false;
   const int64_t n1 = in.n[1], n2 = in.n[2], m1 = L.m[1], m2 = L.m[2];
@@ -813,15 +835,274 @@ bool launch_plane(const bm_plan_s& p, int s, const View3& in, bool mask, void* o
   a.inv_x = L.d_inv[2];
   a.inv_y = L.d_inv[1];
   a.out = static_cast<T*>(out);
-  const dim3 g{unsigned(in.n[0])}, b{unsigned(kPlaneNT)};
+  a.planes = in.n[0];
+  const int64_t cells = det ? det->m.n0 * det->m.n1 * det->m.n2 : 0;
+  const dim3 g{unsigned(a.planes + (cells + kPlaneNT - 1) / kPlaneNT)}, b{unsigned(kPlaneNT)};
+  auto go = [&](auto qc) {
+    constexpr int Q = decltype(qc)::value;
+    if (det)
+      hipLaunchKernelGGL((k_plane_pass<T, Q, true>), g, b, 0, st, a, *det);
+    else
+      hipLaunchKernelGGL((k_plane_pass<T, Q, false>), g, b, 0, st, a, DetArgs<T>{});
+  };
   switch (q) {
-    case 3: hipLaunchKernelGGL((k_plane_pass<T, 3>), g, b, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((k_plane_pass<T, 5>), g, b, 0, st, a); break;
-    case 9: hipLaunchKernelGGL((k_plane_pass<T, 9>), g, b, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_plane_pass<T, 11>), g, b, 0, st, a); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    case 5: go(std::integral_constant<int, 5>{}); break;
+    case 9: go(std::integral_constant<int, 9>{}); break;
+    default: go(std::integral_constant<int, 11>{}); break;
   }
   BM_HIP(hipGetLastError());
   return true;
+}
+
+// ------------------------------------------------------------- tail levels
+
+// The last levels of a deep hierarchy, whose grids fit one workgroup's LDS,
+// in one launch of one workgroup each way.  Such a level is bound by latency
+// alone: as launches of its own (details, plane pass, z pass; plane pass, z
+// pass, interpolation) it takes 3 x 4 us however small it is.  Here a level
+// stays in LDS from the one before, each of its steps costs a barrier, and
+// only details and coarsest values (or codes) touch memory.  The arithmetic
+// is that of the launches it replaces (same cell means, restriction rows and
+// 16-lane solves), so results are equal bit for bit.  What bounds it is the
+// chain of dependent instructions of each pass (about a microsecond, twice
+// that for the VALU work of a 17^3 level on one CU).  65^3 FP32 with six
+// levels, of which the last four (17^3 down to 3^3) run here: 24 launches of
+// 3 to 5 us -> two of 24 us, the fused step 161 -> 112 us.
+constexpr int kTailLevels = 8;         // levels a launch can hold
+constexpr int kTailNodes = 5000;       // nodes of its first level (see tail_first)
+constexpr int kTailM = 16 * 3;         // coarse nodes per line (Q = 3)
+
+struct TailLevel {
+  int n[3], m[3], cm[3];
+  FastDiv fn1, fn2, fm1, fm2;   // by n[1], n[2], m[1], m[2]
+  int f[3];              // node spacing in units of the first tail level's
+  const double* inv[3];  // reciprocal pivots (axes that coarsen)
+  const double* q;       // 1/Delta (decompose) or Delta of this level
+};
+
+template <typename T>
+struct TailArgs {
+  TailLevel lv[kTailLevels];
+  int nlev;
+  int64_t st[3];         // strides of the first tail level in the coefficient (code) array
+  const T* in;           // decompose: the first level's grid (dense)
+  T* out;                // recompose: the same
+  T* coeff;              // coefficients written (decompose) or read, or
+  int32_t* codes;        // their codes
+  const double* qc;      // 1/Delta or Delta of the coarsest values
+  int64_t* flag;
+  int big, small, half;  // LDS elements of a grid of the first level, of its coarse grid, of its x pass
+};
+
+// K along the axes of a tail level that coarsen: x from src (dense n) into B,
+// y in place, z last; put(i, v) receives node i of the dense coarse grid.
+// Every pass ends with a barrier.
+template <typename T, typename Put>
+__device__ inline void tail_K3(const TailLevel& L, const T* src, T* B, const T* piv, Put put) {
+  const int tid = threadIdx.x;
+  const T* cur = src;
+  int d[3] = {L.n[0], L.n[1], L.n[2]};
+  int st[3] = {d[1] * d[2], d[2], 1};
+#pragma unroll
+  for (int axis = 2; axis >= 0; --axis) {
+    if (!L.cm[axis]) continue;
+    const bool last = !((axis > 0 && L.cm[0]) || (axis > 1 && L.cm[1]));
+    const int pa = axis == 0 ? 1 : 0, qa = axis == 2 ? 1 : 2;   // the two other axes (q fastest)
+    const int nl = d[axis], m = L.m[axis], nq = d[qa], np = d[pa];
+    const FastDiv fq = axis == 2 ? L.fn1 : L.cm[2] ? L.fm2 : L.fn2;
+    const int sA = st[axis], sQ = st[qa], sP = st[pa];
+    d[axis] = m;
+    // the first pass writes a dense grid of its own, the second stays in place
+    if (cur == src) {
+      st[0] = d[1] * d[2];
+      st[1] = d[2];
+    }
+    const int oA = st[axis], oQ = st[qa], oP = st[pa];
+    auto rhs = [&](int w, int J) {
+      const int p = int(fq.div(uint32_t(w))), q = w - p * nq;
+      const T* col = cur + p * sP + q * sQ;
+      return restrict_row<T>(J, nl, m, [&](int i) { return col[i * sA]; });
+    };
+    auto out = [&](int w, int J, T v) {
+      const int p = int(fq.div(uint32_t(w))), q = w - p * nq;
+      if (last) {
+        int c[3];
+        c[axis] = J;
+        c[pa] = p;
+        c[qa] = q;
+        put((c[0] * L.m[1] + c[1]) * L.m[2] + c[2], v);
+      } else {
+        B[p * oP + q * oQ + J * oA] = v;
+      }
+    };
+    // (up to 16 unknowns a lane of the 16 has one: the same sums in a third of
+    // the instructions, which is what the first tail level is bound by)
+    const T* pv = piv + axis * kTailM;
+    if (m <= 16)
+      solve_lines<T, kPlaneNT, 1>(m, pv, np * nq, tid, rhs, out);
+    else
+      solve_lines<T, kPlaneNT, 3>(m, pv, np * nq, tid, rhs, out);
+    cur = B;
+    __syncthreads();
+  }
+}
+
+// (z, y, x) of a flat index
+__device__ inline void tail_node(const FastDiv& f1, const FastDiv& f2, int i, int& z, int& y, int& x) {
+  const int t = int(f2.div(uint32_t(i)));
+  x = i - t * int(f2.d);
+  z = int(f1.div(uint32_t(t)));
+  y = t - z * int(f1.d);
+}
+
+// The cell of coarse node i of a tail level, its corners from a reader of
+// coarse-grid values; the fine node of its offset (0, 0, 0) in z, y, x.
+template <typename T, typename F>
+__device__ inline Cell<T> tail_cell(const TailLevel& L, int i, int& z, int& y, int& x, F rd) {
+  int cz, cy, cx;
+  tail_node(L.fm1, L.fm2, i, cz, cy, cx);
+  z = cz << L.cm[0];
+  y = cy << L.cm[1];
+  x = cx << L.cm[2];
+  Cell<T> k;
+  k.oz = L.cm[0] && z + 1 < L.n[0];
+  k.oy = L.cm[1] && y + 1 < L.n[1];
+  k.ox = L.cm[2] && x + 1 < L.n[2];
+  load_corners(k, cz, cy, cx, [&](int64_t zz, int64_t yy, int64_t xx) { return rd(int(zz), int(yy), int(xx)); });
+  return k;
+}
+
+// pivots of every level: [level][axis][kTailM]
+template <typename T>
+__device__ inline void tail_pivots(const TailArgs<T>& a, T* piv) {
+  for (int i = threadIdx.x; i < a.nlev * 3 * kTailM; i += kPlaneNT) {
+    const int l = i / (3 * kTailM), r = i - l * (3 * kTailM), d = r / kTailM, J = r - d * kTailM;
+    if (a.lv[l].cm[d] && J < a.lv[l].m[d]) piv[i] = T(a.lv[l].inv[d][J]);
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kPlaneNT) void k_tail_dec(TailArgs<T> a) {
+  __shared__ __align__(16) unsigned char smem[kPlaneLds];
+  T* piv = reinterpret_cast<T*>(smem);
+  T* cur = piv + a.nlev * 3 * kTailM;     // this level's grid
+  T* next = cur + a.big;                  // its coarse grid
+  T* B = next + a.small;                  // its x pass
+  const int tid = threadIdx.x;
+  tail_pivots(a, piv);
+  for (int i = tid; i < a.big; i += kPlaneNT) cur[i] = a.in[i];
+  __syncthreads();
+  auto put = [&](int64_t o, T v, double inv) {
+    if (a.codes)
+      a.codes[o] = quant_g(v, inv, a.flag);
+    else
+      a.coeff[o] = v;
+  };
+  for (int l = 0; l < a.nlev; ++l) {
+    const TailLevel& L = a.lv[l];
+    const double inv = a.codes ? *L.q : 0.0;
+    const int n1 = L.n[1], n2 = L.n[2];
+    for (int i = tid; i < L.m[0] * L.m[1] * L.m[2]; i += kPlaneNT) {
+      int z, y, x;
+      const Cell<T> k = tail_cell<T>(L, i, z, y, x, [&](int zz, int yy, int xx) {
+        return cur[((zz << L.cm[0]) * n1 + (yy << L.cm[1])) * n2 + (xx << L.cm[2])];
+      });
+#pragma unroll
+      for (int t = 1; t < 8; ++t) {
+        const int dz = t >> 2, dy = (t >> 1) & 1, dx = t & 1;
+        if (dz > k.oz || dy > k.oy || dx > k.ox) continue;
+        const T d = cur[((z + dz) * n1 + y + dy) * n2 + x + dx] - k.interp(dz, dy, dx);
+        put(int64_t((z + dz) * L.f[0]) * a.st[0] + int64_t((y + dy) * L.f[1]) * a.st[1] +
+                int64_t((x + dx) * L.f[2]) * a.st[2],
+            d, inv);
+      }
+    }
+    tail_K3<T>(L, cur, B, piv + l * 3 * kTailM, [&](int i, T v) { next[i] = v; });
+    T* t = cur;
+    cur = next;
+    next = t;
+  }
+  const TailLevel& L = a.lv[a.nlev - 1];
+  const double inv = a.codes ? *a.qc : 0.0;
+  for (int i = tid; i < L.m[0] * L.m[1] * L.m[2]; i += kPlaneNT) {
+    int z, y, x;
+    tail_node(L.fm1, L.fm2, i, z, y, x);
+    put(int64_t((z << L.cm[0]) * L.f[0]) * a.st[0] + int64_t((y << L.cm[1]) * L.f[1]) * a.st[1] +
+            int64_t((x << L.cm[2]) * L.f[2]) * a.st[2],
+        cur[i], inv);
+  }
+}
+
+// R: what is read, coefficients (T) or codes.  All of them, every level's and
+// the coarsest, are the nodes of the first level's view: one round of loads.
+template <typename T, typename R>
+__global__ __launch_bounds__(kPlaneNT) void k_tail_rec(TailArgs<T> a, const R* src) {
+  __shared__ __align__(16) unsigned char smem[kPlaneLds];
+  T* piv = reinterpret_cast<T*>(smem);
+  T* big = piv + a.nlev * 3 * kTailM;
+  T* small = big + a.big;
+  T* B = small + a.small;
+  R* raw = reinterpret_cast<R*>(B + a.half);
+  const int tid = threadIdx.x;
+  const int N1 = a.lv[0].n[1], N2 = a.lv[0].n[2];
+  tail_pivots(a, piv);
+  for (int i = tid; i < a.big; i += kPlaneNT) {
+    int z, y, x;
+    tail_node(a.lv[0].fn1, a.lv[0].fn2, i, z, y, x);
+    raw[i] = src[z * a.st[0] + y * a.st[1] + x * a.st[2]];
+  }
+  __syncthreads();
+  auto value = [](R v, double del) {
+    if constexpr (std::is_same_v<R, int32_t>)
+      return T(mul_rn(double(v), del));
+    else
+      return v;
+  };
+  // grids alternate between the two places so that the first level's is `big`
+  T* uc = a.nlev & 1 ? small : big;
+  T* w = a.nlev & 1 ? big : small;
+  {
+    const TailLevel& L = a.lv[a.nlev - 1];
+    const double del = std::is_same_v<R, int32_t> ? *a.qc : 0.0;
+    for (int i = tid; i < L.m[0] * L.m[1] * L.m[2]; i += kPlaneNT) {
+      int z, y, x;
+      tail_node(L.fm1, L.fm2, i, z, y, x);
+      uc[i] = value(raw[((z << L.cm[0]) * L.f[0] * N1 + (y << L.cm[1]) * L.f[1]) * N2 + (x << L.cm[2]) * L.f[2]], del);
+    }
+  }
+  for (int l = a.nlev - 1; l >= 0; --l) {
+    const TailLevel& L = a.lv[l];
+    const double del = std::is_same_v<R, int32_t> ? *L.q : 0.0;
+    const int n1 = L.n[1], n2 = L.n[2];
+    for (int i = tid; i < L.n[0] * n1 * n2; i += kPlaneNT) {
+      int z, y, x;
+      tail_node(L.fn1, L.fn2, i, z, y, x);
+      const bool coarse = !((L.cm[0] && (z & 1)) || (L.cm[1] && (y & 1)) || (L.cm[2] && (x & 1)));
+      w[i] = coarse ? T(0) : value(raw[(z * L.f[0] * N1 + y * L.f[1]) * N2 + x * L.f[2]], del);
+    }
+    __syncthreads();
+    // u_C = c - K3 w in place, then u = interpolant + w in place of w
+    tail_K3<T>(L, w, B, piv + l * 3 * kTailM, [&](int i, T v) { uc[i] -= v; });
+    for (int i = tid; i < L.m[0] * L.m[1] * L.m[2]; i += kPlaneNT) {
+      int z, y, x;
+      const Cell<T> k = tail_cell<T>(
+          L, i, z, y, x, [&](int zz, int yy, int xx) { return uc[(zz * L.m[1] + yy) * L.m[2] + xx]; });
+      T* const at = w + (z * n1 + y) * n2 + x;
+      at[0] = k.c[0][0][0];
+#pragma unroll
+      for (int t = 1; t < 8; ++t) {
+        const int dz = t >> 2, dy = (t >> 1) & 1, dx = t & 1;
+        if (dz > k.oz || dy > k.oy || dx > k.ox) continue;
+        at[(dz * n1 + dy) * n2 + dx] += k.interp(dz, dy, dx);
+      }
+    }
+    __syncthreads();
+    T* t = uc;
+    uc = w;
+    w = t;
+  }
+  for (int i = tid; i < a.big; i += kPlaneNT) a.out[i] = uc[i];
 }
 
 // The first global level's load vector when the last block level is fused
@@ -882,15 +1163,22 @@ __global__ __launch_bounds__(NT) void k_gather_part(GatherArgs<T> a) {
 
 // ------------------------------------------------------------- launchers
 
+// The details of level s (from its grid u), and K_y K_x of u into t1 where
+// the level takes a plane pass: true, and the z pass alone is left.
 template <typename T>
-void launch_details(const bm_plan_s& p, int s, const void* u, void* coeff, int32_t* codes, const double* qinv,
+bool launch_details(const bm_plan_s& p, int s, const void* u, void* coeff, int32_t* codes, const double* qinv,
                     int64_t* flag, hipStream_t st) {
   const Level& L = p.lv[s - 1];
   const View3 cv = level_view(p, s, codes ? static_cast<void*>(codes) : coeff);
   DetArgs<T> a{static_cast<const T*>(u), {L.n[0], L.n[1], L.n[2]}, {L.m[0], L.m[1], L.m[2]}, L.coarsen[0],
                L.coarsen[1], L.coarsen[2], static_cast<T*>(coeff), {cv.s[0], cv.s[1], cv.s[2]}, codes, qinv, flag};
-  hipLaunchKernelGGL(k_details<T>, dim3(grid_for(L.m[0] * L.m[1] * L.m[2])), dim3(NT), 0, st, a);
+  const int64_t cells = L.m[0] * L.m[1] * L.m[2];
+  if (L.coarsen[0] && cells <= kDetCells &&
+      launch_plane<T>(p, s, dense_view(const_cast<void*>(u), L.n), false, p.ws.t1, nullptr, nullptr, st, false, &a))
+    return true;
+  hipLaunchKernelGGL(k_details<T>, dim3(grid_for(cells)), dim3(NT), 0, st, a);
   BM_HIP(hipGetLastError());
+  return false;
 }
 
 template <typename T>
@@ -903,6 +1191,114 @@ void launch_interp(const bm_plan_s& p, int s, const void* coeff, const int32_t* 
                static_cast<T*>(out), codes, qdel};
   hipLaunchKernelGGL(k_interp_add<T>, dim3(grid_for(L.m[0] * L.m[1] * L.m[2])), dim3(NT), 0, st, a);
   BM_HIP(hipGetLastError());
+}
+
+// The first of the last levels that run in one tail launch (nlev + 1: none):
+// global levels that are not fused with a block level, of at most kTailNodes
+// nodes, whose lines take the 3-unknown row solves and whose grids fit a
+// workgroup's LDS.  A 17^3 level takes 7 us more here than a 9^3 one and 14 us
+// as launches of its own; twice its nodes would take as long on the one CU as
+// spread over the chip, and 33^3 does not fit.
+int64_t tail_half(const Level& L) {   // the first pass's result (no pass: nothing)
+  if (L.coarsen[2]) return L.n[0] * L.n[1] * L.m[2];
+  return L.coarsen[1] ? L.n[0] * L.m[1] * L.n[2] : 0;
+}
+
+int tail_first(const bm_plan_s& p) {
+  int s0 = p.nlev + 1;
+  if (!p.plane_pass) return s0;
+  const int lo = p.L + (p.fuse_next ? 2 : 1);
+  for (int s = p.nlev; s >= lo && p.nlev - s < kTailLevels; --s) {
+    const Level& L = p.lv[s - 1];
+    if (L.local) break;
+    int64_t n = 1, m = 1;
+    bool ok = true;
+    for (int k = 0; k < 3; ++k) {
+      n *= L.n[k];
+      m *= L.m[k];
+      ok = ok && L.n[k] <= kTailNodes;
+      if (L.coarsen[k]) ok = ok && L.n[k] >= 3 && L.m[k] == (L.n[k] + 1) / 2 && L.m[k] <= kTailM;
+    }
+    if (!ok || n > kTailNodes) break;
+    const int64_t half = tail_half(L);
+    const int64_t piv = int64_t(p.nlev - s + 1) * 3 * kTailM;
+    if ((piv + n + m + half) * int64_t(p.esize) + n * int64_t(std::max<size_t>(p.esize, 4)) > kPlaneLds) break;
+    s0 = s;
+  }
+  return s0;
+}
+
+// The tail launch from level s0 on; q0: the prepared steps (null: plain coefficients)
+template <typename T>
+TailArgs<T> tail_args(const bm_plan_s& p, int s0, bool dec, const QPrep* q) {
+  TailArgs<T> a{};
+  a.nlev = p.nlev - s0 + 1;
+  const Level& F = p.lv[s0 - 1];
+  const View3 v = level_view(p, s0, nullptr);
+  for (int k = 0; k < 3; ++k) a.st[k] = v.s[k];
+  for (int s = s0; s <= p.nlev; ++s) {
+    const Level& L = p.lv[s - 1];
+    TailLevel& t = a.lv[s - s0];
+    for (int k = 0; k < 3; ++k) {
+      t.n[k] = int(L.n[k]);
+      t.m[k] = int(L.m[k]);
+      t.cm[k] = L.coarsen[k] ? 1 : 0;
+      t.f[k] = int(L.ps[k] / F.ps[k]);
+      t.inv[k] = L.d_inv[k];
+    }
+    t.fn1 = FastDiv(uint32_t(L.n[1]));
+    t.fn2 = FastDiv(uint32_t(L.n[2]));
+    t.fm1 = FastDiv(uint32_t(L.m[1]));
+    t.fm2 = FastDiv(uint32_t(L.m[2]));
+    if (q) t.q = q->q + 2 * (s - 1) + (dec ? 1 : 0);
+  }
+  if (q) {
+    a.qc = q->q + 2 * p.nlev + (dec ? 1 : 0);
+    a.flag = q->flag;
+  }
+  a.big = int(F.n[0] * F.n[1] * F.n[2]);
+  a.small = int(F.m[0] * F.m[1] * F.m[2]);
+  a.half = int(tail_half(F));
+  return a;
+}
+
+// Levels s0 .. nlev from the grid u of level s0 to coefficients or codes
+template <typename T>
+void launch_tail_dec(const bm_plan_s& p, int s0, const void* u, void* coeff, int32_t* codes, const QPrep* q,
+                     hipStream_t st) {
+  TailArgs<T> a = tail_args<T>(p, s0, true, q);
+  a.in = static_cast<const T*>(u);
+  a.coeff = static_cast<T*>(coeff);
+  a.codes = codes;
+  hipLaunchKernelGGL(k_tail_dec<T>, dim3(1), dim3(kPlaneNT), 0, st, a);
+  BM_HIP(hipGetLastError());
+}
+
+template <typename T>
+void launch_tail_rec(const bm_plan_s& p, int s0, const void* coeff, const int32_t* codes, const QPrep* q, void* out,
+                     hipStream_t st) {
+  TailArgs<T> a = tail_args<T>(p, s0, false, q);
+  a.out = static_cast<T*>(out);
+  if (codes)
+    hipLaunchKernelGGL((k_tail_rec<T, int32_t>), dim3(1), dim3(kPlaneNT), 0, st, a, codes);
+  else
+    hipLaunchKernelGGL((k_tail_rec<T, T>), dim3(1), dim3(kPlaneNT), 0, st, a, static_cast<const T*>(coeff));
+  BM_HIP(hipGetLastError());
+}
+
+void tail_dec(const bm_plan_s& p, int s0, const void* u, void* coeff, int32_t* codes, const QPrep* q, hipStream_t st) {
+  if (p.cfg.dtype == BM_F32)
+    launch_tail_dec<float>(p, s0, u, coeff, codes, q, st);
+  else
+    launch_tail_dec<double>(p, s0, u, coeff, codes, q, st);
+}
+
+void tail_rec(const bm_plan_s& p, int s0, const void* coeff, const int32_t* codes, const QPrep* q, void* out,
+              hipStream_t st) {
+  if (p.cfg.dtype == BM_F32)
+    launch_tail_rec<float>(p, s0, coeff, codes, q, out, st);
+  else
+    launch_tail_rec<double>(p, s0, coeff, codes, q, out, st);
 }
 
 // quantize (to_codes) or dequantize a strided view; *scale is 1/Delta or Delta
@@ -925,11 +1321,9 @@ __global__ __launch_bounds__(NT) void k_qcopy(const T* src, int64_t ss0, int64_t
 
 }  // namespace
 
-void global_details(const bm_plan_s& p, int s, const void* u, void* coeff, hipStream_t st) {
-  if (p.cfg.dtype == BM_F32)
-    launch_details<float>(p, s, u, coeff, nullptr, nullptr, nullptr, st);
-  else
-    launch_details<double>(p, s, u, coeff, nullptr, nullptr, nullptr, st);
+static bool global_details(const bm_plan_s& p, int s, const void* u, void* coeff, hipStream_t st) {
+  if (p.cfg.dtype == BM_F32) return launch_details<float>(p, s, u, coeff, nullptr, nullptr, nullptr, st);
+  return launch_details<double>(p, s, u, coeff, nullptr, nullptr, nullptr, st);
 }
 
 void global_interp_add(const bm_plan_s& p, int s, const void* coeff, const void* uc, void* out, hipStream_t st) {
@@ -1003,19 +1397,37 @@ void launch_pad_extend(const bm_plan_s& p, void* g, bool zero, hipStream_t st) {
   BM_HIP(hipGetLastError());
 }
 
-// The level-1 grid of a plan without block levels: the input padded into
-// the plan's grid, or, when the input is that grid already (its logical
-// region at the padded strides, as a caller inside the library leaves it),
-// only its extension filled in place.
-static void level1_input(const bm_plan_s& p, const void* x, hipStream_t st) {
+// Whether the caller's array itself can be the level-1 grid: nothing padded,
+// and no byte shared with the coefficients or codes (na, nb: bytes).
+static bool direct(const bm_plan_s& p, const void* x, const void* other, size_t osize) {
+  const int64_t n = p.pdims[0] * p.pdims[1] * p.pdims[2];
+  for (int k = 0; k < 3; ++k)
+    if (p.dims[k] != p.pdims[k]) return false;
+  const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(other);
+  return a + size_t(n) * p.esize <= b || b + size_t(n) * osize <= a;
+}
+
+// The level-1 grid of a plan without block levels: the input itself where it
+// is that grid already, else the input padded into the plan's grid (or, when
+// the input is the plan's grid, its logical region at the padded strides as
+// a caller inside the library leaves it, only its extension filled in place).
+static const void* level1_input(const bm_plan_s& p, const void* x, const void* out, size_t osize, hipStream_t st) {
   const bool zero = p.cfg.pad_mode == 1;
   if (x != p.ws.grid[0]) {
+    if (direct(p, x, out, osize)) return x;
     pad_input(p, x, p.ws.grid[0], zero, st);
   } else if (p.cfg.dtype == BM_F32) {
     launch_pad_extend<float>(p, p.ws.grid[0], zero, st);
   } else {
     launch_pad_extend<double>(p, p.ws.grid[0], zero, st);
   }
+  return p.ws.grid[0];
+}
+
+// Where the last recomposition step writes, and the copy to x it leaves when
+// that is the plan's padded grid.
+static void* level1_output(const bm_plan_s& p, void* x, const void* in, size_t isize) {
+  return p.cfg.L > 0 ? nullptr : x == p.ws.grid[0] || direct(p, x, in, isize) ? x : p.ws.grid[0];
 }
 
 void* level1_grid(const bm_plan_s& p) { return p.cfg.L == 0 ? p.ws.grid[0] : nullptr; }
@@ -1034,6 +1446,15 @@ void pad_input(const bm_plan_s& p, const void* x, void* dst, bool zero, hipStrea
   BM_HIP(hipGetLastError());
 }
 
+static void level1_result(const bm_plan_s& p, void* out, void* x, hipStream_t st) {
+  if (x == out) return;   // (written there, or a caller that passed the plan's grid reads it in place)
+  View3 src = dense_view(out, p.pdims);
+  src.n[0] = p.dims[0];
+  src.n[1] = p.dims[1];
+  src.n[2] = p.dims[2];
+  strided_copy(p.esize, src, dense_view(x, p.dims), st);
+}
+
 // ------------------------------------------------------------- drivers
 
 static bool plane_pass(const bm_plan_s& p, int s, const View3& in, bool mask, void* out, const int32_t* qin,
@@ -1045,10 +1466,12 @@ static bool plane_pass(const bm_plan_s& p, int s, const View3& in, bool mask, vo
 // coarse = K_z K_y K_x (in), applied as line passes over the axes that
 // coarsen; intermediate results go through the plan's temporaries.
 static void apply_K3(bm_plan_s& p, int s, View3 in, bool mask, void* out, const void* base, hipStream_t st,
-                     const int32_t* qin = nullptr, const double* qdel = nullptr, const CoarseIO* cio = nullptr) {
+                     const int32_t* qin = nullptr, const double* qdel = nullptr, const CoarseIO* cio = nullptr,
+                     bool planes_done = false) {
   const Level& L = p.lv[s - 1];
-  // x and y in one plane pass where the planes fit, then z
-  if (L.coarsen[0] && plane_pass(p, s, in, mask, p.ws.t1, qin, qdel, st)) {
+  // x and y in one plane pass where the planes fit (into t1, perhaps before
+  // this call), then z
+  if (planes_done || (L.coarsen[0] && plane_pass(p, s, in, mask, p.ws.t1, qin, qdel, st))) {
     const int64_t on[3] = {in.n[0], L.m[1], L.m[2]};
     line_pass_q(p, s, 0, dense_view(p.ws.t1, on), nullptr, out, base, nullptr, qdel, st, cio);
     return;
@@ -1106,6 +1529,7 @@ static void global_from_parts(bm_plan_s& p, int s, hipStream_t st) {
 
 void decompose(bm_plan_s& p, const void* x, void* coeff, hipStream_t st) {
   const View3 xv = dense_view(const_cast<void*>(x), p.dims);
+  const int s0 = tail_first(p);
   for (int s = 1; s <= p.nlev; ++s) {
     const Level& L = p.lv[s - 1];
     TimedScope ts(p, 2 * (s - 1), st);
@@ -1118,12 +1542,10 @@ void decompose(bm_plan_s& p, const void* x, void* coeff, hipStream_t st) {
       }
       local_decompose(p, s, src, s == 1, coeff, p.ws.grid[s], st);
     } else {
-      const void* u;
-      if (s == 1) {
-        level1_input(p, x, st);
-        u = p.ws.grid[0];
-      } else {
-        u = p.ws.grid[s - 1];
+      const void* u = s == 1 ? level1_input(p, x, coeff, p.esize, st) : p.ws.grid[s - 1];
+      if (s == s0) {
+        tail_dec(p, s0, u, coeff, nullptr, nullptr, st);
+        return;
       }
       // (the first global level's details and load vector come from the
       // last block level when fused)
@@ -1131,8 +1553,9 @@ void decompose(bm_plan_s& p, const void* x, void* coeff, hipStream_t st) {
         global_from_parts(p, s, st);
         continue;
       }
-      global_details(p, s, u, coeff, st);
-      apply_K3(p, s, dense_view(const_cast<void*>(u), L.n), false, p.ws.grid[s], nullptr, st);
+      const bool pd = global_details(p, s, u, coeff, st);
+      apply_K3(p, s, dense_view(const_cast<void*>(u), L.n), false, p.ws.grid[s], nullptr, st, nullptr, nullptr, nullptr,
+               pd);
     }
   }
   const Level& last = p.lv[p.nlev - 1];
@@ -1140,9 +1563,13 @@ void decompose(bm_plan_s& p, const void* x, void* coeff, hipStream_t st) {
 }
 
 void recompose(bm_plan_s& p, const void* coeff, void* x, hipStream_t st) {
-  const Level& last = p.lv[p.nlev - 1];
-  strided_copy(p.esize, coarsest_view(p, const_cast<void*>(coeff)), dense_view(p.ws.grid[p.nlev], last.m), st);
-  for (int s = p.nlev; s >= 1; --s) {
+  const int s0 = tail_first(p);
+  void* const top = level1_output(p, x, coeff, p.esize);
+  if (s0 > p.nlev) {
+    const Level& last = p.lv[p.nlev - 1];
+    strided_copy(p.esize, coarsest_view(p, const_cast<void*>(coeff)), dense_view(p.ws.grid[p.nlev], last.m), st);
+  }
+  for (int s = s0 > p.nlev ? p.nlev : s0; s >= 1; --s) {
     const Level& L = p.lv[s - 1];
     TimedScope ts(p, 2 * (s - 1) + 1, st);
     if (L.local) {
@@ -1156,19 +1583,17 @@ void recompose(bm_plan_s& p, const void* coeff, void* x, hipStream_t st) {
       void* out = s == 1 ? x : p.ws.grid[s - 1];
       local_recompose(p, s, coeff, p.ws.grid[s], out, s == 1, st);
     } else {
-      // u_C = c - K3 w in place in grid[s], then u = interpolant + w (which
-      // the last block level does itself when fused)
-      apply_K3(p, s, level_view(p, s, const_cast<void*>(coeff)), true, p.ws.grid[s], p.ws.grid[s], st);
-      if (p.fuse_next && s == p.L + 1) continue;
-      void* out = p.ws.grid[s - 1];
-      global_interp_add(p, s, coeff, p.ws.grid[s], out, st);
-      if (s == 1 && x != out) {   // (a caller that passed the plan's grid reads it in place)
-        View3 src = dense_view(out, p.pdims);
-        src.n[0] = p.dims[0];
-        src.n[1] = p.dims[1];
-        src.n[2] = p.dims[2];
-        strided_copy(p.esize, src, dense_view(x, p.dims), st);
+      void* out = s == 1 ? top : p.ws.grid[s - 1];
+      if (s == s0) {
+        tail_rec(p, s0, coeff, nullptr, nullptr, out, st);
+      } else {
+        // u_C = c - K3 w in place in grid[s], then u = interpolant + w (which
+        // the last block level does itself when fused)
+        apply_K3(p, s, level_view(p, s, const_cast<void*>(coeff)), true, p.ws.grid[s], p.ws.grid[s], st);
+        if (p.fuse_next && s == p.L + 1) continue;
+        global_interp_add(p, s, coeff, p.ws.grid[s], out, st);
       }
+      if (s == 1) level1_result(p, out, x, st);
     }
   }
 }
@@ -1178,26 +1603,24 @@ void recompose(bm_plan_s& p, const void* coeff, void* x, hipStream_t st) {
 // detail stencil produces them, and the coarsest values last.  The codes are
 // identical to bm_decompose followed by bm_quantize_roi.
 void decompose_quantize_global(bm_plan_s& p, const void* x, int32_t* codes, const QPrep& q, hipStream_t st) {
+  const int s0 = tail_first(p);
   bool coarsest_done = false;
   for (int s = p.L + 1; s <= p.nlev; ++s) {
     const Level& L = p.lv[s - 1];
     TimedScope ts(p, 2 * (s - 1), st);
-    const void* u;
-    if (s == 1) {
-      level1_input(p, x, st);
-      u = p.ws.grid[0];
-    } else {
-      u = p.ws.grid[s - 1];
+    const void* u = s == 1 ? level1_input(p, x, codes, sizeof(int32_t), st) : p.ws.grid[s - 1];
+    if (s == s0) {
+      tail_dec(p, s0, u, nullptr, codes, &q, st);
+      return;
     }
     if (p.fuse_next && s == p.L + 1) {
       // details (codes) and load vector from the last block level
       global_from_parts(p, s, st);
       continue;
     }
-    if (p.cfg.dtype == BM_F32)
-      launch_details<float>(p, s, u, nullptr, codes, q.q + 2 * (s - 1) + 1, q.flag, st);
-    else
-      launch_details<double>(p, s, u, nullptr, codes, q.q + 2 * (s - 1) + 1, q.flag, st);
+    const double* qinv = q.q + 2 * (s - 1) + 1;
+    const bool pd = p.cfg.dtype == BM_F32 ? launch_details<float>(p, s, u, nullptr, codes, qinv, q.flag, st)
+                                          : launch_details<double>(p, s, u, nullptr, codes, qinv, q.flag, st);
     // the last level's last pass quantizes the coarsest values into the codes
     CoarseIO cio;
     if (s == p.nlev) {
@@ -1209,7 +1632,7 @@ void decompose_quantize_global(bm_plan_s& p, const void* x, int32_t* codes, cons
       coarsest_done = true;
     }
     apply_K3(p, s, dense_view(const_cast<void*>(u), L.n), false, p.ws.grid[s], nullptr, st, nullptr, nullptr,
-             s == p.nlev ? &cio : nullptr);
+             s == p.nlev ? &cio : nullptr, pd);
   }
   if ((p.M > 0 || p.L == 0) && !coarsest_done) {
     const Level& last = p.lv[p.nlev - 1];
@@ -1248,11 +1671,18 @@ void decompose_quantize(bm_plan_s& p, const void* x, const double* block_tol, in
 void dequantize_recompose_global(bm_plan_s& p, const int32_t* codes, const QPrep& q, void* x, hipStream_t st) {
   // (the coarsest values, a global level's, are dequantized by the last pass
   // of that level, where they are the base of u_C = c - K3 w)
-  for (int s = p.nlev; s > p.L; --s) {
+  const int s0 = tail_first(p);
+  for (int s = s0 > p.nlev ? p.nlev : s0; s > p.L; --s) {
     const Level& L = p.lv[s - 1];
     TimedScope ts(p, 2 * (s - 1) + 1, st);
     const double* qdel = q.q + 2 * (s - 1);
     const View3 lvw = level_view(p, s, const_cast<int32_t*>(codes));
+    void* out = s > 1 ? p.ws.grid[s - 1] : level1_output(p, x, codes, sizeof(int32_t));
+    if (s == s0) {
+      tail_rec(p, s0, nullptr, codes, &q, out, st);
+      if (s == 1) level1_result(p, out, x, st);
+      continue;
+    }
     if (s == p.nlev) {
       CoarseIO cio;
       const View3 cv = coarsest_view(p, const_cast<int32_t*>(codes));
@@ -1264,18 +1694,11 @@ void dequantize_recompose_global(bm_plan_s& p, const int32_t* codes, const QPrep
       apply_K3(p, s, lvw, true, p.ws.grid[s], p.ws.grid[s], st, codes, qdel);
     }
     if (p.fuse_next && s == p.L + 1) continue;   // the last block level interpolates
-    void* out = p.ws.grid[s - 1];
     if (p.cfg.dtype == BM_F32)
       launch_interp<float>(p, s, nullptr, codes, qdel, p.ws.grid[s], out, st);
     else
       launch_interp<double>(p, s, nullptr, codes, qdel, p.ws.grid[s], out, st);
-    if (s == 1 && x != out) {   // (a caller that passed the plan's grid reads it in place)
-      View3 src = dense_view(out, p.pdims);
-      src.n[0] = p.dims[0];
-      src.n[1] = p.dims[1];
-      src.n[2] = p.dims[2];
-      strided_copy(p.esize, src, dense_view(x, p.dims), st);
-    }
+    if (s == 1) level1_result(p, out, x, st);
   }
 }
 

@@ -314,7 +314,6 @@ void wide_recompose(const bm_plan_s& p, int s, const void* coeff, void* cin, voi
                     const int32_t* codes, const QPrep* q, hipStream_t st);
 
 // global level pieces
-void global_details(const bm_plan_s& p, int s, const void* u, void* coeff, hipStream_t st);
 void global_interp_add(const bm_plan_s& p, int s, const void* coeff, const void* uc, void* out,
                        hipStream_t st);
 // restriction + tridiagonal solve along one axis (0=z,1=y,2=x) of a view;
