@@ -13,23 +13,31 @@
 namespace bm {
 
 // ES: bytes per value; DEC: decomposition (else recomposition).  Blocks per
-// workgroup: three 9^3 blocks fill 256 lanes; for FP32 decomposition two
-// x-neighbouring 17^3 blocks (640 lanes) share the cache lines of their
-// common face in one workgroup, which halves the partial-line traffic across
-// workgroups.  FP64, and the recomposition (more registers per lane), keep
-// one 17^3 block so several workgroups still fit on a CU.
+// workgroup, neighbours along x: wider rows share the cache lines of their
+// common faces and leave fewer partial ones (512^3, decomposition /
+// recomposition with codes):
+//   17^3 FP32: one block - / 326 us, two 365 / 287, three (896 lanes) 435 / 367;
+//   17^3 FP64, whose rows are 128 bytes: one 524 / 451, two 613 / 501 (two
+//   workgroups of 640 lanes fill a CU less evenly than four of 320);
+//   9^3 (FP32; FP64): three 385 / 323; 521 / 372, four 422 / 335; 549 / 411,
+//   six 389 / 308; 507 / 365 (and 343 / 268; 580 / 421 against 373 / 324;
+//   675 / 454 without codes).
 template <int B, int ES = 4, bool DEC = true>
 struct Geo {
   static constexpr int BB = B * B;
   static constexpr int MC = (B + 1) / 2;        // coarse nodes per axis
   static constexpr int MI = MC - 2;             // interior coarse nodes per axis
-  static constexpr int NB = B <= 9 ? 3 : ((ES == 4 && DEC) ? 2 : 1);
+  static constexpr int NB = B <= 9 ? 6 : ES == 4 ? 2 : 1;
   static constexpr int NT = ((NB * BB + 63) / 64) * 64;
   static constexpr int NB1 = B <= 9 ? 3 : 1;    // blocks per workgroup in the transposes
-  // LDS per block: decompose UE[MC][B][B] + T1[MI][B][B] (T2 aliases UE, Z aliases T1)
+  // LDS per block: decompose UE[MC][B][B] + T1[MI][B][B]; T2[MI][MI][B] and
+  // then the coarse values CC[MC][MC][MC] (from DEC_CC on) alias UE
   static constexpr int DEC_LDS = MC * BB + MI * BB;
-  // recompose: UC[MC][MC][MC] + T1[MI][B][B] + T2[MI][MI][B] (Z aliases T1)
-  static constexpr int REC_LDS = MC * MC * MC + MI * BB + MI * MI * B;
+  static constexpr int DEC_CC = (MI * MI * B + 1) / 2 * 2;
+  // recompose: UC[MC][MC][MC] + T1[MI][B][B] + T2[MI][MI][B] + the next
+  // level's coarse values XC[H][H][H]
+  static constexpr int H = (MC + 1) / 2;
+  static constexpr int REC_LDS = MC * MC * MC + MI * BB + MI * MI * B + H * H * H;
   // transposes: T1[MI][B][B] + T2[MI][MI][B] + Z[MI][MI][MI]; the restriction
   // planes R[MC][B][B] alias the start
   static constexpr int ADJ_WORK = MI * BB + MI * MI * B + MI * MI * MI;
@@ -189,6 +197,21 @@ __device__ inline int32_t quant(T c, double inv, bool skip, unsigned& bad) {
   const bool ok = fabs(v) <= 2147483647.0;
   if (!ok && !skip) bad |= code_flag(double(c));
   return (ok && !skip) ? int32_t(v) : 0;
+}
+
+// The same in two parts: the code, with ok cleared where quant() would flag
+// it, and what quant() flags, for the lanes whose ok was cleared.
+template <typename T>
+__device__ inline int32_t quant_code(T c, double inv, bool& ok) {
+  const double v = rint(mul_rn(double(c), inv));
+  const bool in = fabs(v) <= 2147483647.0;
+  ok = ok && in;
+  return in ? int32_t(v) : 0;
+}
+
+template <typename T>
+__device__ inline unsigned quant_flag(T c, double inv) {
+  return fabs(rint(mul_rn(double(c), inv))) <= 2147483647.0 ? 0u : code_flag(double(c));
 }
 
 }  // namespace bm

@@ -65,6 +65,14 @@ __device__ inline double mul_rn(double a, double b) {
   return a * b;
 }
 
+// A sum whose terms keep their own rounding (no product of theirs is
+// contracted into it).
+template <typename T>
+__device__ inline T add_rn(T a, T b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
 // Multilinear interpolant at offset (dz, dy, dx) in {0,1}^3 of a cell of a
 // level's coarse grid: rd(az, ay, ax) reads corner (az, ay, ax), and only
 // az <= dz, ay <= dy, ax <= dx are read.  The 8-term sum in this fixed order

@@ -43,18 +43,74 @@ __device__ inline void pass_y(const T* T1, T* T2, int tb) {
   }
 }
 
-template <typename T, int B>
-__device__ inline void pass_x(const T* T2, T* Z, int tb) {
-  constexpr int MI = Geo<B>::MI;
+// (the x pass adds its line z, or subtracts it, at the interior coarse nodes
+// of C[MC][MC][MC] itself: no array of z, no pass that picks it up)
+template <typename T, int B, bool ADD>
+__device__ inline void pass_x(const T* T2, T* C, int tb) {
+  constexpr int MI = Geo<B>::MI, MC = Geo<B>::MC;
   if (tb < MI * MI) {
     T line[B], o[MI];
 #pragma unroll
     for (int x = 0; x < B; ++x) line[x] = T2[tb * B + x];
     restrict_solve<T, B>(line, o);
+    const int J = tb / MI, I = tb - (tb / MI) * MI;
+    T* const c = C + ((J + 1) * MC + I + 1) * MC + 1;
 #pragma unroll
-    for (int K = 0; K < MI; ++K) Z[tb * MI + K] = o[K];
+    for (int K = 0; K < MI; ++K) c[K] = add_rn(c[K], ADD ? o[K] : -o[K]);
   }
 }
+
+// The z-column (y, x) of block bl of this lane.  The block kernels are bound
+// by how their rows of B values lie in memory, not by arithmetic (without the
+// loads and stores left in place they take as long): a wavefront's request is
+// worked off 16 lanes at a time and costs by the 64-byte pieces that these
+// touch.  B - 1 (16 or 8) columns of a row side by side fill such a group,
+// the blocks of a workgroup follow each other, and the columns on the last
+// face (which the next block owns and stores) go to the lanes after them.
+// Rows of B lanes each made 18 pieces per wavefront and request of the
+// recomposition at 512^3 FP32, this 6.  The loads and stores alone, 512^3
+// FP32 (a copy of the bytes takes 173 us): one block a workgroup 330 us in
+// rows, 275 to 326 in groups; two blocks 265 and 225 to 249.
+template <int B, int NB, bool ROWS = false>
+struct ColumnLane {
+  int y, x, bl;
+  __device__ inline ColumnLane(int tid) {
+    constexpr int W = NB * (ROWS ? B : B - 1), MAIN = B * W;
+    if (ROWS) {
+      y = tid / W;
+      const int r = tid - y * W;
+      bl = y < B ? r / B : NB;
+      x = r - (r / B) * B;
+      y = y < B ? y : 0;
+    } else if (tid < MAIN) {
+      y = tid / W;
+      const int r = tid - y * W;
+      bl = r / (B - 1);
+      x = r - bl * (B - 1);
+    } else {
+      const int e = tid - MAIN;
+      bl = e / B;              // (NB and more: idle)
+      y = e - bl * B;
+      x = B - 1;
+    }
+  }
+};
+
+// The lanes that work on the coarse columns of a workgroup's NB blocks: the
+// first NB * MC * MC, along the rows of the blocks side by side.  (The even
+// columns' own lanes are a quarter of every wavefront.)
+template <int MC, int NB>
+struct CoarseLane {
+  int p, q, bl;
+  bool in;
+  __device__ inline CoarseLane(int tid) {
+    p = tid / (NB * MC);
+    const int r = tid - p * (NB * MC);
+    bl = r / MC;
+    q = r - bl * MC;
+    in = p < MC;
+  }
+};
 
 template <typename T>
 struct DecArgs {
@@ -121,12 +177,12 @@ template <typename T>
 constexpr int kWavesPerEU = sizeof(T) == 4 ? 8 : 5;
 
 // Nested schedule, two block levels in one launch: the finer level (blocks
-// of 2B-1 nodes) leaves each block's B^3 coarse values at the start of the
-// block's LDS region; the coarser level (B-node blocks over the same
-// regions) works in the same region after them, 16-byte aligned.
+// of 2B-1 nodes) has each block's B^3 coarse values at `first` of the block's
+// LDS region; the coarser level (B-node blocks over the same regions) works
+// in the same region after them, 16-byte aligned.
 template <typename T, int B>
-constexpr int nest_offset() {
-  return int(((size_t(B) * B * B * sizeof(T) + 15) / 16) * 16 / sizeof(T));
+constexpr int nest_offset(int first) {
+  return int(((size_t(first + B * B * B) * sizeof(T) + 15) / 16) * 16 / sizeof(T));
 }
 
 // One workgroup's block group g (NBG blocks) of a decomposition level.
@@ -138,22 +194,21 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
   using G = Geo<B, sizeof(T)>;
   constexpr int BB = G::BB, MC = G::MC, MI = G::MI, NB = NBG;
   constexpr int PREG = SRC_LDS ? Geo<2 * B - 1>::DEC_LDS : G::DEC_LDS;   // LDS elements per block
-  constexpr int POFF = SRC_LDS ? nest_offset<T, B>() : 0;
+  constexpr int PCC = Geo<2 * B - 1>::DEC_CC;
+  constexpr int NT = SRC_LDS ? Geo<2 * B - 1, sizeof(T)>::NT : G::NT;     // lanes of the workgroup
+  constexpr int POFF = SRC_LDS ? nest_offset<T, B>(PCC) : 0;
   static_assert(!SRC_LDS || POFF + G::DEC_LDS <= PREG, "nested level must fit in its parent's LDS region");
   const int tid = threadIdx.x;
-  // lanes run along the rows of the group's x-neighbouring blocks (NB
-  // columns x of row y side by side), so a wavefront reads and writes
-  // contiguous runs of NB * B values
-  const int row = tid / (NB * B), rr = tid - row * (NB * B);
-  const int bl = row < B ? rr / B : NB;              // block within the workgroup
-  const int tb = row < B ? row * B + (rr - (rr / B) * B) : 0;   // column within the block
+  const ColumnLane<B, NB> at(tid);
+  const int bl = at.bl, y = at.y, x = at.x, tb = y * B + x;
   const int64_t blk = g * NB + bl;
   const bool act = bl < NB && blk < a.nblocks;
   T* UE = lds + (bl < NB ? bl : 0) * PREG + POFF;   // even-z planes [MC][B][B]
   T* T1 = UE + MC * BB;                              // [MI][B][B]
-  T* T2 = UE;                                        // [MI][MI][B], after UE is dead
-  T* Z = T1;                                         // [MI][MI][MI], after T1 is dead
-  const int y = tb / B, x = tb - (tb / B) * B;
+  // after UE is dead: T2 [MI][MI][B] in its place, then the coarse values CC
+  T* CC = UE + G::DEC_CC;                            // [MC][MC][MC]
+  // region of block b of the group, if there is one
+  auto region = [&](int b) { return g * NB + b < a.nblocks ? lds + b * PREG + POFF : nullptr; };
   const bool ecol = ((y | x) & 1) == 0;
   int64_t bz = 0, by = 0, bx = 0;
   if (act) block_coords(uint32_t(blk), a.fnb2, a.fnb1, a.nb, bz, by, bx);
@@ -166,7 +221,7 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
     class_table<NB, true>(a.tau, a.kap, a.kapc, a.coarsest_here, g * NB, a.nblocks, a.fnb2, a.fnb1, a.nb, cls);
   T v[B];
   if (act && SRC_LDS) {
-    const T* cc = lds + bl * PREG;                   // [B][B][B] coarse values of the finer level
+    const T* cc = lds + bl * PREG + PCC;             // [B][B][B] coarse values of the finer level
 #pragma unroll
     for (int z = 0; z < B; ++z) v[z] = cc[(z * B + y) * B + x];
 #pragma unroll
@@ -229,15 +284,24 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
         int32_t* dst = a.codes + oz * a.cs[0] + gy * a.cs[1] + gx * a.cs[2];
         double iv[3];
         column_class<B>(cls[0], bl, y, x, iv);
-        unsigned bad = 0;
+        const double ie[3] = {ecol ? 0.0 : iv[0], ecol ? 0.0 : iv[1], ecol ? 0.0 : iv[2]};   // (placeholder 0)
+        bool ok = true;
 #pragma unroll
-        for (int z = 1; z < B - 1; z += 2) dst[z * a.cs0] = quant(v[z], iv[zcase<B>(z)], false, bad);
+        for (int z = 1; z < B - 1; z += 2) dst[z * a.cs0] = quant_code(v[z], iv[1], ok);
         if (!later) {   // even planes in one branch
 #pragma unroll
-          for (int z = 0; z < B - 1; z += 2) dst[z * a.cs0] = quant(v[z], iv[zcase<B>(z)], ecol, bad);
-          if (lastz) dst[(B - 1) * a.cs0] = quant(v[B - 1], iv[2], ecol, bad);
+          for (int z = 0; z < B - 1; z += 2) dst[z * a.cs0] = quant_code(v[z], ie[zcase<B>(z)], ok);
+          if (lastz) dst[(B - 1) * a.cs0] = quant_code(v[B - 1], ie[2], ok);
         }
-        if (bad) atomicOr(reinterpret_cast<unsigned long long*>(a.flag), (unsigned long long)bad);
+        if (!ok) {   // (or a coarse node that is not finite)
+          unsigned bad = 0;
+#pragma unroll
+          for (int z = 0; z < B; ++z) {
+            const bool here = (z & 1) || (!ecol && (z < B - 1 || lastz));
+            bad |= here ? quant_flag(v[z], iv[zcase<B>(z)]) : 0u;
+          }
+          if (bad) atomicOr(reinterpret_cast<unsigned long long*>(a.flag), (unsigned long long)bad);
+        }
       }
     }
     // correction, z pass: w is zero on the coarse nodes
@@ -249,80 +313,83 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
     for (int J = 0; J < MI; ++J) T1[J * BB + tb] = o[J];
   }
   __syncthreads();
-  if (act) pass_y<T, B>(T1, T2, tb);
-  __syncthreads();
-  if (act) pass_x<T, B>(T2, Z, tb);
-  __syncthreads();
-  // coarse values c = u_C + z (z = 0 on the block surface); the compact
-  // coarse grid feeds the next level
-  T c[MC];
-  T* CC = UE;                                        // [MC][MC][MC] when fused (T2 is dead)
-  // fused: the next level's load vector, in FP64 (see below): z pass in
-  // registers, then y and x passes in LDS after CC
-  constexpr int H = (MC + 1) / 2;
-  double* Z1 = reinterpret_cast<double*>(CC + ((MC * MC * MC * sizeof(T) + 7) / 8) * (8 / sizeof(T)));   // [H][MC][MC]
-  double* Y1 = Z1 + H * MC * MC;                     // [H][H][MC]
   if (act && ecol) {
 #pragma unroll
-    for (int j = 0; j < MC; ++j) c[j] = v[2 * j];
-    if (y >= 2 && y <= B - 3 && x >= 2 && x <= B - 3) {
-      const int I = (y - 2) >> 1, K = (x - 2) >> 1;
+    for (int j = 0; j < MC; ++j) CC[(j * MC + (y >> 1)) * MC + (x >> 1)] = v[2 * j];
+  }
+  if (const int b = tid / (MI * B); b < NB)
+    if (T* R = region(b)) pass_y<T, B>(R + MC * BB, R, tid - b * (MI * B));
+  __syncthreads();
+  // coarse values c = u_C + z (z = 0 on the block surface)
+  if (const int b = tid / (MI * MI); b < NB)
+    if (T* R = region(b)) pass_x<T, B, true>(R, R + G::DEC_CC, tid - b * (MI * MI));
+  __syncthreads();
+  // what follows is per coarse column, on lanes of its own
+  constexpr int H = (MC + 1) / 2;
+  // fused: the next level's load vector, in FP64 (see below): z pass in
+  // registers, then y and x passes in LDS after CC
+  constexpr int ZOFF = int(((MC * MC * MC * sizeof(T) + 7) / 8) * (8 / sizeof(T)));
+  auto Z1 = [&](T* R) { return reinterpret_cast<double*>(R + G::DEC_CC + ZOFF); };   // [H][MC][MC], then Y1 [H][H][MC]
+  const CoarseLane<MC, NB> cl(tid);
+  if (cl.in && g * NB + cl.bl < a.nblocks && !a.nest) {
+    const int p = cl.p, q = cl.q;
+    const T* const C = lds + cl.bl * PREG + POFF + G::DEC_CC;
+    int64_t cz, cy, cx;
+    block_coords(uint32_t(g * NB + cl.bl), a.fnb2, a.fnb1, a.nb, cz, cy, cx);
+    const bool own = (p < MC - 1 || cy == a.nb[1] - 1) && (q < MC - 1 || cx == a.nb[2] - 1);
+    const bool end = cz == a.nb[0] - 1;
+    const int64_t o = cz * (B - 1) * a.cs[0] + (cy * (B - 1) + 2 * p) * a.cs[1] + (cx * (B - 1) + 2 * q) * a.cs[2];
+    T c[MC];
 #pragma unroll
-      for (int J = 0; J < MI; ++J) c[J + 1] += Z[(J * MI + I) * MI + K];
-    }
-    if (a.fuse || a.nest) {
-#pragma unroll
-      for (int j = 0; j < MC; ++j) CC[(j * MC + (y >> 1)) * MC + (x >> 1)] = c[j];
-    }
+    for (int j = 0; j < MC; ++j) c[j] = C[(j * MC + p) * MC + q];
     if (a.fuse) {
+      double* const Zb = Z1(lds + cl.bl * PREG + POFF);
 #pragma unroll
       for (int k = 0; k < H; ++k)
-        Z1[(k * MC + (y >> 1)) * MC + (x >> 1)] = restrict_half<double, MC>(k, [&](int t) { return double(c[t]); });
+        Zb[(k * MC + p) * MC + q] = restrict_half<double, MC>(k, [&](int t) { return double(c[t]); });
     }
-  }
-  if (act && ecol && owned) {
-    if (Q && a.coarsest_here) {
+    if (own && Q && a.coarsest_here) {
       // last level of the hierarchy: codes for the coarsest values
       double ci[3];
-      column_class<B>(cls[1], bl, y, x, ci);
-      int32_t* dst = a.codes + oz * a.cs[0] + gy * a.cs[1] + gx * a.cs[2];
+      column_class<B>(cls[1], cl.bl, 2 * p, 2 * q, ci);
+      int32_t* dst = a.codes + o;
       unsigned bad = 0;
 #pragma unroll
       for (int j = 0; j < MC - 1; ++j) dst[2 * j * a.cs0] = quant(c[j], ci[zcase<B>(2 * j)], false, bad);
-      if (lastz) dst[(B - 1) * a.cs0] = quant(c[MC - 1], ci[2], false, bad);
+      if (end) dst[(B - 1) * a.cs0] = quant(c[MC - 1], ci[2], false, bad);
       if (bad) atomicOr(reinterpret_cast<unsigned long long*>(a.flag), (unsigned long long)bad);
-    } else if (!a.fuse && !a.nest) {
-      T* cdst = a.cout + (oz >> 1) * int64_t(a.cpl) + (gy >> 1) * a.cn[2] + (gx >> 1);
+    } else if (own && !a.fuse) {
+      // the compact coarse grid feeds the next level
+      T* cdst = a.cout + cz * (MC - 1) * int64_t(a.cpl) + (cy * (MC - 1) + p) * a.cn[2] + cx * (MC - 1) + q;
 #pragma unroll
       for (int j = 0; j < MC - 1; ++j) cdst[j * a.cpl] = c[j];
-      if (lastz) cdst[(MC - 1) * a.cpl] = c[MC - 1];
-    }
-  }
-  if (a.fuse) {
-    // details of the next (global) level at this column's coarse nodes: c
-    // minus the interpolant over the cell of the next coarse grid (every
-    // such cell lies inside the block); its coarse nodes get a placeholder
-    // (c, or code 0) that a later level or the coarsest values overwrite
-    __syncthreads();
-    if (act && ecol && owned) {
-      const int p = y >> 1, q = x >> 1, op = p & 1, oq = q & 1;
+      if (end) cdst[(MC - 1) * a.cpl] = c[MC - 1];
+    } else if (own) {
+      // details of the next (global) level at this column's coarse nodes: c
+      // minus the interpolant over the cell of the next coarse grid (every
+      // such cell lies inside the block); its coarse nodes get a placeholder
+      // (c, or code 0) that a later level or the coarsest values overwrite
+      const int op = p & 1, oq = q & 1;
       const double inv = Q ? *a.nqinv : 0.0;
       T in[MC];
-      column_interp<T, MC>(p, q, [&](int J, int P, int K) { return CC[((2 * J) * MC + 2 * P) * MC + 2 * K]; }, in);
+      column_interp<T, MC>(p, q, [&](int J, int P, int K) { return C[((2 * J) * MC + 2 * P) * MC + 2 * K]; }, in);
       unsigned bad = 0;
 #pragma unroll
       for (int j = 0; j < MC; ++j) {
-        if (j == MC - 1 && !lastz) continue;
+        if (j == MC - 1 && !end) continue;
         const bool cn = ((j & 1) | op | oq) == 0;
         const T d = cn ? c[j] : c[j] - in[j];
-        const int64_t o = oz * a.cs[0] + gy * a.cs[1] + gx * a.cs[2] + int64_t(2 * j) * a.cs0;
+        const int64_t oj = o + int64_t(2 * j) * a.cs0;
         if (Q)
-          a.codes[o] = quant(d, inv, cn, bad);
+          a.codes[oj] = quant(d, inv, cn, bad);
         else
-          a.coeff[o] = d;
+          a.coeff[oj] = d;
       }
       if (Q && bad) atomicOr(reinterpret_cast<unsigned long long*>(a.flag), (unsigned long long)bad);
     }
+  }
+  if (a.fuse) {
+    __syncthreads();
     // The next level's load vector 3 P^T M (per axis) at its coarse nodes in
     // this block, from the block's own coarse values only: rows on the block
     // faces take the half of the stencil on this side ({5/12, 1/2, 1/12}, the
@@ -331,18 +398,21 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
     // terms and the gather of up to 8 partials round once; the partial sums
     // go to a per-block array that a gather completes, so the global level
     // needs no pass over G^s.
-    if (act) {
-      for (int i = tb; i < H * H * MC; i += BB) {
-        const int k0 = i / (H * MC), r = i - k0 * (H * MC), k1 = r / MC, q = r - k1 * MC;
-        Y1[i] = restrict_half<double, MC>(k1, [&](int t) { return Z1[(k0 * MC + t) * MC + q]; });
+    for (int i = tid; i < NB * H * H * MC; i += NT) {
+      const int b = i / (H * H * MC), e = i - b * (H * H * MC);
+      if (T* R = region(b)) {
+        const int k0 = e / (H * MC), r = e - k0 * (H * MC), k1 = r / MC, q = r - k1 * MC;
+        const double* const Z = Z1(R);
+        Z1(R)[H * MC * MC + e] = restrict_half<double, MC>(k1, [&](int t) { return Z[(k0 * MC + t) * MC + q]; });
       }
     }
     __syncthreads();
-    if (act) {
-      double* dst = a.part + blk * (H * H * H);
-      for (int i = tb; i < H * H * H; i += BB) {
-        const int r = i / H, k2 = i - r * H;
-        dst[i] = restrict_half<double, MC>(k2, [&](int t) { return Y1[r * MC + t]; });
+    for (int i = tid; i < NB * H * H * H; i += NT) {
+      const int b = i / (H * H * H), e = i - b * (H * H * H);
+      if (T* R = region(b)) {
+        const int r = e / H, k2 = e - r * H;
+        const double* const Y1 = Z1(R) + H * MC * MC;
+        a.part[(g * NB + b) * (H * H * H) + e] = restrict_half<double, MC>(k2, [&](int t) { return Y1[r * MC + t]; });
       }
     }
   }
@@ -354,30 +424,34 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
 // start of the block's LDS region of the finer (2B-1)-node level and works
 // after them; MODE 2 is that finer level, which reads its coarse values
 // there instead of from the coarse grid.
+// (FP64 rows of 17 values are 128 bytes wide in any case and read best as
+// rows: 512^3 FP64 446 / 453 us against 463 / 465 in groups of 16 lanes, where
+// the decomposition has 602 / 555 against 574 / 524.)
 template <typename T, int B, bool Q, int NBG = Geo<B, sizeof(T), false>::NB, int MODE = 0>
 __device__ __attribute__((always_inline)) inline void recompose_group(const RecArgs<T>& a, int64_t g, T* lds,
                                                                         double (*cls)[NBG * 27]) {
   using G = Geo<B, sizeof(T), false>;
   constexpr int BB = G::BB, MC = G::MC, MI = G::MI, NB = NBG;
   constexpr int PREG = MODE == 1 ? Geo<2 * B - 1>::REC_LDS : G::REC_LDS;   // LDS elements per block
-  constexpr int POFF = MODE == 1 ? nest_offset<T, B>() : 0;
+  constexpr int POFF = MODE == 1 ? nest_offset<T, B>(0) : 0;
+  constexpr int NT = MODE == 1 ? Geo<2 * B - 1, sizeof(T), false>::NT : G::NT;   // lanes of the workgroup
   static_assert(MODE != 1 || POFF + G::REC_LDS <= PREG, "nested level must fit in its parent's LDS region");
   const int tid = threadIdx.x;
-  const int row = tid / (NB * B), rr = tid - row * (NB * B);   // as in decompose_group
-  const int bl = row < B ? rr / B : NB;
-  const int tb = row < B ? row * B + (rr - (rr / B) * B) : 0;
+  const ColumnLane<B, NB, sizeof(T) == 8> at(tid);
+  const int bl = at.bl, y = at.y, x = at.x, tb = y * B + x;
   const int64_t blk = g * NB + bl;
   const bool act = bl < NB && blk < a.nblocks;
   T* UC = lds + (bl < NB ? bl : 0) * PREG + POFF;   // coarse values u_C [MC][MC][MC]
   T* T1 = UC + MC * MC * MC;                         // [MI][B][B]
-  T* T2 = T1 + MI * BB;                              // [MI][MI][B]
-  T* Z = T1;                                         // [MI][MI][MI], after T1 is dead
-  const int y = tb / B, x = tb - (tb / B) * B;
+  constexpr int T2OFF = MC * MC * MC + MI * BB;      // [MI][MI][B]
+  constexpr int XOFF = T2OFF + MI * MI * B;          // [H][H][H] the next level's coarse values (fused)
+  // region of block b of the group, if there is one
+  auto region = [&](int b) { return g * NB + b < a.nblocks ? lds + b * PREG + POFF : nullptr; };
   const bool ecol = ((y | x) & 1) == 0;
   int64_t bz = 0, by = 0, bx = 0;
   if (act) block_coords(uint32_t(blk), a.fnb2, a.fnb1, a.nb, bz, by, bx);
   const int64_t oz = bz * (B - 1), gy = by * (B - 1) + y, gx = bx * (B - 1) + x;
-  T w[B], ce[MC];
+  T w[B];
   int32_t qv[B];
   // the whole column is read (coarse nodes too, then zeroed): one load per
   // node, on its way before anything is waited for
@@ -396,87 +470,94 @@ __device__ __attribute__((always_inline)) inline void recompose_group(const RecA
   // fused dequantization: the blocks' Delta classes
   if (Q)
     class_table<NB, false>(a.tau, a.kap, a.kapc, a.coarsest_here, g * NB, a.nblocks, a.fnb2, a.fnb1, a.nb, cls);
-  // fused with the next (global) level: its coarse values over this block,
-  // UC2[H][H][H] (in T2, which is first written by the y pass)
-  constexpr int H = (MC + 1) / 2;
-  T* UC2 = T2;
-  if (a.fuse && act) {
+  // fused with the next (global) level: its coarse values over this block
+  constexpr int H = G::H;
+  if (a.fuse) {
     const int64_t h0 = (MC - 1) / 2, pl2 = a.cn2[1] * a.cn2[2];
-    const T* src = a.cin2 + bz * h0 * pl2 + by * h0 * a.cn2[2] + bx * h0;
-    for (int i = tb; i < H * H * H; i += BB) {
-      const int k0 = i / (H * H), r = i - k0 * H * H, k1 = r / H, k2 = r - k1 * H;
-      UC2[i] = src[k0 * pl2 + k1 * a.cn2[2] + k2];
+    for (int i = tid; i < NB * H * H * H; i += NT) {
+      const int b = i / (H * H * H), e = i - b * (H * H * H);
+      if (T* R = region(b)) {
+        int64_t cz, cy, cx;
+        block_coords(uint32_t(g * NB + b), a.fnb2, a.fnb1, a.nb, cz, cy, cx);
+        const T* src = a.cin2 + cz * h0 * pl2 + cy * h0 * a.cn2[2] + cx * h0;
+        const int k0 = e / (H * H), r = e - k0 * H * H, k1 = r / H, k2 = r - k1 * H;
+        R[XOFF + e] = src[k0 * pl2 + k1 * a.cn2[2] + k2];
+      }
     }
   }
+  // the coarse values come from the column itself (coarsest codes, details of
+  // the fused next level), from the level's coarse grid, or are there already
+  const bool self = a.fuse || (Q && a.coarsest_here);
+  const CoarseLane<MC, NB> cl(tid);
+  const bool cact = cl.in && g * NB + cl.bl < a.nblocks;
+  T ce[MC];
+  if (MODE != 2 && !self && cact) {
+    int64_t cz, cy, cx;
+    block_coords(uint32_t(g * NB + cl.bl), a.fnb2, a.fnb1, a.nb, cz, cy, cx);
+    const T* ccol = a.cin + cz * (MC - 1) * int64_t(a.cpl) + (cy * (MC - 1) + cl.p) * a.cn[2] + cx * (MC - 1) + cl.q;
+#pragma unroll
+    for (int j = 0; j < MC; ++j) ce[j] = ccol[j * a.cpl];
+  }
   if (Q || a.fuse) __syncthreads();
+  if (MODE != 2 && !self && cact) {
+    T* const C = lds + cl.bl * PREG + POFF;
+#pragma unroll
+    for (int j = 0; j < MC; ++j) C[(j * MC + cl.p) * MC + cl.q] = ce[j];
+  }
   if (act) {
     if (Q) {
-      // c_hat = (T)(q * Delta)
-      double dd[3];
-      column_class<B>(cls[0], bl, y, x, dd);
+      // c_hat = (T)(q * Delta); an even column's even planes take Delta of the
+      // coarsest values or of the fused next level
+      double de[3];
+      column_class<B>(cls[ecol && a.coarsest_here ? 1 : 0], bl, y, x, de);
+      if (a.fuse && ecol) de[0] = de[1] = de[2] = *a.nqdel;
 #pragma unroll
-      for (int z = 0; z < B; ++z) w[z] = T(mul_rn(double(qv[z]), dd[zcase<B>(z)]));
+      for (int z = 0; z < B; z += 2) w[z] = T(mul_rn(double(qv[z]), de[zcase<B>(z)]));
+      column_class<B>(cls[0], bl, y, x, de);
+#pragma unroll
+      for (int z = 1; z < B; z += 2) w[z] = T(mul_rn(double(qv[z]), de[1]));
     }
     if (ecol) {
-      if (Q && a.coarsest_here) {
-        double cd[3];
-        column_class<B>(cls[1], bl, y, x, cd);
+      // c waits in UC through the correction passes instead of in registers
+      if (MODE != 2 && self) {
 #pragma unroll
-        for (int j = 0; j < MC; ++j) ce[j] = T(mul_rn(double(qv[2 * j]), cd[zcase<B>(2 * j)]));
-      } else if (a.fuse) {
-        // u at this column's coarse nodes = next level's detail + interpolant
-        // of its coarse values (exactly the next level's recomposition)
-        const int p = y >> 1, q = x >> 1, op = p & 1, oq = q & 1;
-        const double del2 = Q ? *a.nqdel : 0.0;
-        T in[MC];
-        column_interp<T, MC>(p, q, [&](int J, int P, int K) { return UC2[(J * H + P) * H + K]; }, in);
-#pragma unroll
-        for (int j = 0; j < MC; ++j) {
-          if (((j & 1) | op | oq) == 0) {
-            ce[j] = in[j];   // the next level's coarse value itself (exact)
-          } else {
-            const T w2 = Q ? T(mul_rn(double(qv[2 * j]), del2)) : w[2 * j];
-            ce[j] = w2 + in[j];
-          }
-        }
-      } else if (MODE == 2) {
-        // left here by the coarser level of the same launch
-#pragma unroll
-        for (int j = 0; j < MC; ++j) ce[j] = UC[(j * MC + (y >> 1)) * MC + (x >> 1)];
-      } else {
-        const T* ccol = a.cin + (oz >> 1) * int64_t(a.cpl) + (gy >> 1) * a.cn[2] + (gx >> 1);
-#pragma unroll
-        for (int j = 0; j < MC; ++j) ce[j] = ccol[j * a.cpl];
-      }
-      // c waits in UC through the correction passes (which do not touch UC)
-      // instead of in registers; a nested finer level finds it there already
-      if (MODE != 2) {
-#pragma unroll
-        for (int j = 0; j < MC; ++j) UC[(j * MC + (y >> 1)) * MC + (x >> 1)] = ce[j];
+        for (int j = 0; j < MC; ++j) UC[(j * MC + (y >> 1)) * MC + (x >> 1)] = w[2 * j];
       }
 #pragma unroll
       for (int j = 0; j < MC; ++j) w[2 * j] = T(0);
     }
+  }
+  if (act) {
     T o[MI];
     restrict_solve<T, B>(w, o);
 #pragma unroll
     for (int J = 0; J < MI; ++J) T1[J * BB + tb] = o[J];
   }
   __syncthreads();
-  if (act) pass_y<T, B>(T1, T2, tb);
-  __syncthreads();
-  if (act) pass_x<T, B>(T2, Z, tb);
-  __syncthreads();
-  if (act && ecol && y >= 2 && y <= B - 3 && x >= 2 && x <= B - 3) {
-    // u_C = c - z on this column's interior coarse nodes (z = 0 on the block
-    // surface, where u_C = c already)
-    const int I = (y - 2) >> 1, K = (x - 2) >> 1;
+  if (const int b = tid / (MI * B); b < NB)
+    if (T* R = region(b)) pass_y<T, B>(R + MC * MC * MC, R + T2OFF, tid - b * (MI * B));
+  if (a.fuse) {
+    // u at the coarse nodes = next level's detail + interpolant of its coarse
+    // values (exactly the next level's recomposition), on the last lanes: the
+    // y pass is on the first
+    const CoarseLane<MC, NB> fl(NT - 1 - tid);
+    if (fl.in && g * NB + fl.bl < a.nblocks) {
+      T* const C = lds + fl.bl * PREG + POFF;
+      const T* const X = C + XOFF;
+      const int op = fl.p & 1, oq = fl.q & 1;
+      T in[MC];
+      column_interp<T, MC>(fl.p, fl.q, [&](int J, int P, int K) { return X[(J * H + P) * H + K]; }, in);
 #pragma unroll
-    for (int j = 1; j <= MC - 2; ++j) {
-      T& u = UC[(j * MC + (y >> 1)) * MC + (x >> 1)];
-      u = u - Z[((j - 1) * MI + I) * MI + K];
+      for (int j = 0; j < MC; ++j) {
+        T& u = C[(j * MC + fl.p) * MC + fl.q];
+        u = ((j & 1) | op | oq) == 0 ? in[j] : u + in[j];   // (the next level's coarse value itself, exact)
+      }
     }
   }
+  __syncthreads();
+  // u_C = c - z (z = 0 on the block surface)
+  if (const int b = tid / (MI * MI); b < NB)
+    if (T* R = region(b)) pass_x<T, B, false>(R + T2OFF, R, tid - b * (MI * MI));
   __syncthreads();
   if (act) {
     // u = interpolant(u_C) + w
@@ -573,7 +654,9 @@ __global__ __launch_bounds__((Geo<17, sizeof(T), false>::NT)) void k_local_recom
 // against 63, which left one FP32 decomposition workgroup per CU.  The field
 // index is the same for every lane of the workgroup; said so with
 // readfirstlane, and with the argument array read-only and unaliased, the
-// record is read by scalar loads.)
+// record is read by scalar loads.  It is copied before use: read in place, its
+// fields were fetched where they were needed, into vector registers: 68 and
+// 121 of them in the recompositions against 61 and 92.)
 template <typename T, int B, bool Q>
 __global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_batch_decompose(
     const DecArgs<T>* __restrict__ fa, const int64_t* __restrict__ first, int nf, int64_t ntasks) {
@@ -582,7 +665,8 @@ __global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) __attribute__((amdgpu_wave
   const int64_t k = xcd_group(blockIdx.x, (ntasks + 7) / 8);
   if (k >= ntasks) return;
   const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
-  decompose_group<T, B, Q>(fa[f], k - first[f], lds, cls);
+  const DecArgs<T> a = fa[f];
+  decompose_group<T, B, Q>(a, k - first[f], lds, cls);
 }
 
 template <typename T, int B, bool Q>
@@ -594,7 +678,8 @@ __global__ __launch_bounds__((Geo<B, sizeof(T), false>::NT)) void k_batch_recomp
   const int64_t k = xcd_group(blockIdx.x, (ntasks + 7) / 8);
   if (k >= ntasks) return;
   const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
-  recompose_group<T, B, Q>(fa[f], k - first[f], lds, cls);
+  const RecArgs<T> a = fa[f];
+  recompose_group<T, B, Q>(a, k - first[f], lds, cls);
 }
 
 // The nested schedule of every field in one launch: task k is
@@ -613,9 +698,11 @@ __global__ __launch_bounds__((Geo<17, sizeof(T)>::NT)) __attribute__((amdgpu_wav
   if (k >= ntasks) return;
   const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
   const int64_t g = k - first[f];
-  decompose_group<T, 17, Q>(f1[f], g, lds, cls);
+  const DecArgs<T> a1 = f1[f];
+  decompose_group<T, 17, Q>(a1, g, lds, cls);
   __syncthreads();
-  decompose_group<T, 9, Q, NB, true>(f2[f], g, lds, cls);
+  const DecArgs<T> a2 = f2[f];
+  decompose_group<T, 9, Q, NB, true>(a2, g, lds, cls);
 }
 
 template <typename T, bool Q>
@@ -629,9 +716,11 @@ __global__ __launch_bounds__((Geo<17, sizeof(T), false>::NT)) void k_batch_recom
   if (k >= ntasks) return;
   const int f = __builtin_amdgcn_readfirstlane(task_field(first, nf, k));
   const int64_t g = k - first[f];
-  recompose_group<T, 9, Q, NB, 1>(f2[f], g, lds, cls);
+  const RecArgs<T> a2 = f2[f];
+  recompose_group<T, 9, Q, NB, 1>(a2, g, lds, cls);
   __syncthreads();
-  recompose_group<T, 17, Q, NB, 2>(f1[f], g, lds, cls);
+  const RecArgs<T> a1 = f1[f];
+  recompose_group<T, 17, Q, NB, 2>(a1, g, lds, cls);
 }
 
 // 32-bit z stride within one block column
