@@ -56,7 +56,16 @@ struct BoxArgs {
   double* out;
 };
 
-__global__ void k_tol_boxes(BoxArgs a) {
+// Up to kArgBoxes boxes come with the launch, longer lists from device memory
+// (a copy from staging that the call has to wait for: map, quantization and
+// reconstruction of 129^3 under new boxes 102 -> 81 us).
+constexpr int kArgBoxes = 32;
+struct BoxList {
+  double r[kArgBoxes * 7];
+};
+
+template <bool ARG>
+__global__ void k_tol_boxes(BoxArgs a, BoxList l) {
   const int64_t nbt = a.nb[0] * a.nb[1] * a.nb[2];
   for (int64_t k = int64_t(blockIdx.x) * NT + threadIdx.x; k < nbt; k += int64_t(gridDim.x) * NT) {
     const int64_t bx = k % a.nb[2], t = k / a.nb[2], by = t % a.nb[1], bz = t / a.nb[1];
@@ -73,7 +82,7 @@ __global__ void k_tol_boxes(BoxArgs a) {
     }
     double v = a.background;
     for (int j = 0; j < a.nbox; ++j) {
-      const double* r = a.boxes + 7 * j;
+      const double* r = (ARG ? l.r : a.boxes) + 7 * j;
       bool hit = true;
       for (int d = 0; d < 3; ++d) {
         const int64_t b0 = int64_t(r[d]), b1 = int64_t(r[d + 3]);
@@ -765,12 +774,29 @@ QPrep qprep_layout(bm_plan_s& p, const double* block_tol) {
 // One plan's tables are built by the many-field kernels with one field: one
 // launch per propagation step, one per table level, one for tau_global and
 // the scalar Deltas (which also clears the overflow flag).  The field record
-// is uploaded only when it changes (a new tolerance map pointer).
+// is stored only when it changes.
 namespace {
 __global__ void k_clear_flag(int64_t* flag) {
   if (threadIdx.x == 0) *flag = 0;
 }
 }  // namespace
+
+// The preparation's record reaches the device as a launch's argument, in
+// stream order, with no copy to wait for: a new plan's first call.
+struct PrepImage {
+  uint64_t w[kPrepBytes / 8];
+};
+
+__global__ __launch_bounds__(512) void k_prep_store(PrepImage im, uint64_t* dst) {
+  static_assert(kPrepBytes % 8 == 0 && kPrepBytes / 8 <= 512, "a lane per word");
+  if (threadIdx.x < kPrepBytes / 8) dst[threadIdx.x] = im.w[threadIdx.x];
+}
+
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  BM_HIP(hipStreamIsCapturing(st, &c));
+  return c != hipStreamCaptureStatusNone;
+}
 
 QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool clear_flag, bool tables) {
   const QPrep a = qprep_layout(p, block_tol);
@@ -792,24 +818,25 @@ QPrep quant_prepare(bm_plan_s& p, const double* block_tol, hipStream_t st, bool 
   auto wants = [&](int s) { return tables || p.lv[s - 1].b == 33; };
   for (int s = 1; s < 9; ++s) cnt_tab[s] = p.L >= s && wants(s) ? 27 * prod3(p.lv[s - 1].nb) : 0;
   cnt_tab[0] = (p.L > 0 && p.M == 0 && wants(p.L)) ? 27 * prod3(p.lv[p.L - 1].nb) : 0;
-  if (!p.ws.prep_set) {
-    std::vector<int64_t> first(4 * 9);
+  const uint8_t* fb = reinterpret_cast<const uint8_t*>(&f);
+  if (!p.ws.prep_set || p.ws.prep_key.size() != sizeof(f) || std::memcmp(p.ws.prep_key.data(), fb, sizeof(f)) != 0) {
+    PrepImage im{};
+    std::memcpy(im.w, fb, sizeof(f));
+    int64_t* first = reinterpret_cast<int64_t*>(im.w) + kPrepFirst / sizeof(int64_t);
     for (int s = 0; s < 9; ++s) {
-      first[2 * s] = 0;
       first[2 * s + 1] = s >= 1 && p.L > s ? prod3(p.lv[s].nb) : 0;
-      first[18 + 2 * s] = 0;
       first[18 + 2 * s + 1] = s == 0 ? (p.L > 0 && p.M == 0 ? 27 * prod3(p.lv[p.L - 1].nb) : 0)
                                      : (p.L >= s ? 27 * prod3(p.lv[s - 1].nb) : 0);
     }
-    BM_HIP(hipMemcpy(static_cast<uint8_t*>(p.ws.prep_dev) + kPrepFirst, first.data(), first.size() * sizeof(int64_t),
-                     hipMemcpyHostToDevice));
+    if (capturing(st)) {   // (a captured copy would leave the record unset: the wait refuses it)
+      BM_HIP(hipMemcpyAsync(p.ws.prep_dev, im.w, sizeof(im), hipMemcpyHostToDevice, st));
+      BM_HIP(hipStreamSynchronize(st));
+    } else {
+      hipLaunchKernelGGL(k_prep_store, dim3(1), dim3(512), 0, st, im, static_cast<uint64_t*>(p.ws.prep_dev));
+      BM_HIP(hipGetLastError());
+    }
+    if (!p.ws.prep_set) p.dev_bytes += kPrepBytes;
     p.ws.prep_set = true;
-    p.dev_bytes += kPrepBytes;
-  }
-  const uint8_t* fb = reinterpret_cast<const uint8_t*>(&f);
-  if (p.ws.prep_key.size() != sizeof(f) || std::memcmp(p.ws.prep_key.data(), fb, sizeof(f)) != 0) {
-    BM_HIP(hipMemcpyAsync(p.ws.prep_dev, fb, sizeof(f), hipMemcpyHostToDevice, st));
-    BM_HIP(hipStreamSynchronize(st));
     p.ws.prep_key.assign(fb, fb + sizeof(f));
   }
   PrepStages g;
@@ -1078,21 +1105,26 @@ void tolmap_from_boxes(bm_plan_s& p, const double* boxes, int nbox, double backg
   for (int j = 0; j < nbox; ++j)
     if (!(boxes[7 * j + 6] > 0) || !std::isfinite(boxes[7 * j + 6])) fail(BM_ENONFINITE, "box tolerance must be positive and finite");
   if (nbox > kMaxBoxes) fail(BM_EINVAL, "at most 4096 boxes");
-  double* dbox = nullptr;
-  if (nbox) {
-    // the caller's list goes through pinned staging; the call then waits for
-    // the copy so the staging buffer can be reused
-    if (!p.ws.boxhost)
-      BM_HIP(hipHostMalloc(&p.ws.boxhost, size_t(kMaxBoxes) * 7 * sizeof(double), hipHostMallocDefault));
-    std::copy(boxes, boxes + 7 * nbox, p.ws.boxhost);
-    BM_HIP(hipMemcpyAsync(p.ws.boxbuf, p.ws.boxhost, size_t(nbox) * 7 * sizeof(double), hipMemcpyHostToDevice, st));
-    dbox = p.ws.boxbuf;
-  }
-  BoxArgs a{dbox, nbox, background, {p.dims[0], p.dims[1], p.dims[2]}, {p.nb1[0], p.nb1[1], p.nb1[2]},
+  BoxArgs a{nullptr, nbox, background, {p.dims[0], p.dims[1], p.dims[2]}, {p.nb1[0], p.nb1[1], p.nb1[2]},
             p.L > 0 ? p.cfg.block - 1 : 0, block_tol};
-  hipLaunchKernelGGL(k_tol_boxes, dim3(grid_for(prod3(p.nb1))), dim3(NT), 0, st, a);
+  const dim3 g(grid_for(prod3(p.nb1)));
+  if (nbox <= kArgBoxes && (nbox == 0 || !capturing(st))) {
+    BoxList l{};
+    std::copy(boxes, boxes + 7 * nbox, l.r);
+    hipLaunchKernelGGL(k_tol_boxes<true>, g, dim3(NT), 0, st, a, l);
+    BM_HIP(hipGetLastError());
+    return;
+  }
+  // the caller's list goes through pinned staging; the call then waits for
+  // the copy so the staging buffer can be reused
+  if (!p.ws.boxhost)
+    BM_HIP(hipHostMalloc(&p.ws.boxhost, size_t(kMaxBoxes) * 7 * sizeof(double), hipHostMallocDefault));
+  std::copy(boxes, boxes + 7 * nbox, p.ws.boxhost);
+  BM_HIP(hipMemcpyAsync(p.ws.boxbuf, p.ws.boxhost, size_t(nbox) * 7 * sizeof(double), hipMemcpyHostToDevice, st));
+  a.boxes = p.ws.boxbuf;
+  hipLaunchKernelGGL(k_tol_boxes<false>, g, dim3(NT), 0, st, a, BoxList{});
   BM_HIP(hipGetLastError());
-  if (dbox) BM_HIP(hipStreamSynchronize(st));
+  BM_HIP(hipStreamSynchronize(st));
 }
 
 void tolmap_from_voxels(bm_plan_s& p, const double* voxel_tol, double* block_tol, hipStream_t st) {
