@@ -785,7 +785,7 @@ void launch_dec(const bm_plan_s& p, int s, const View3& src, bool first, void* c
 
 template <typename T, int B>
 RecArgs<T> rec_args(const bm_plan_s& p, int s, const void* coeff, const void* cin, void* out, bool last,
-                    const int32_t* codes, const QPrep* q) {
+                    const int32_t* codes, const QPrep* q, bool crop = true) {
   using G = Geo<B, sizeof(T), false>;
   const Level& L = p.lv[s - 1];
   RecArgs<T> a{};
@@ -807,7 +807,12 @@ RecArgs<T> rec_args(const bm_plan_s& p, int s, const void* coeff, const void* ci
   a.os[1] = on[2];
   a.os[2] = 1;
   a.os0 = column_stride(a.os[0], B);
-  a.nblocks = L.nb[0] * L.nb[1] * L.nb[2];
+  // planes of blocks that start past the (cropped) output have nothing to
+  // write: 98 x 1200 x 1200 with two block levels is padded to 129 planes of
+  // nodes, and its last plane of blocks out of eight is left out (level 1 396
+  // -> 367 us; left out inside the kernel it idled one XCD and gained nothing)
+  const int64_t nbz = crop ? std::min(L.nb[0], (on[0] + B - 2) / (B - 1)) : L.nb[0];
+  a.nblocks = nbz * L.nb[1] * L.nb[2];
   if (a.nblocks >= (int64_t(1) << 32)) fail(BM_EUNSUPPORTED, "too many blocks");
   a.fnb2 = FastDiv(uint32_t(L.nb[2]));
   a.fnb1 = FastDiv(uint32_t(L.nb[1]));
@@ -915,8 +920,8 @@ template <typename T>
 void launch_rec_nest(const bm_plan_s& p, int s, const void* coeff, const void* cin, void* out, bool last,
                      const int32_t* codes, const QPrep* q, hipStream_t st) {
   using G = Geo<17, sizeof(T), false>;
-  const RecArgs<T> a1 = rec_args<T, 17>(p, s, coeff, nullptr, out, last, codes, q);
-  const RecArgs<T> a2 = rec_args<T, 9>(p, s + 1, coeff, cin, nullptr, false, codes, q);
+  const RecArgs<T> a1 = rec_args<T, 17>(p, s, coeff, nullptr, out, last, codes, q, false);
+  const RecArgs<T> a2 = rec_args<T, 9>(p, s + 1, coeff, cin, nullptr, false, codes, q, false);
   if (a1.fuse || a1.coarsest_here || a2.nblocks != a1.nblocks) fail(BM_EINVAL, "nested pair: inconsistent levels");
   if (q)
     hipLaunchKernelGGL((k_local_recompose_nest<T, true>), dim3(unsigned(8 * a1.per)), dim3(G::NT), 0, st, a2, a1);
@@ -1056,8 +1061,8 @@ void nest_dec_pair(const bm_plan_s& p, const View3& src, int32_t* codes, const Q
 
 template <typename T>
 void nest_rec_pair(const bm_plan_s& p, void* x, const int32_t* codes, const QPrep* q, void* out1, void* out2) {
-  const RecArgs<T> a1 = rec_args<T, 17>(p, 1, nullptr, nullptr, x, true, codes, q);
-  const RecArgs<T> a2 = rec_args<T, 9>(p, 2, nullptr, p.ws.grid[2], nullptr, false, codes, q);
+  const RecArgs<T> a1 = rec_args<T, 17>(p, 1, nullptr, nullptr, x, true, codes, q, false);
+  const RecArgs<T> a2 = rec_args<T, 9>(p, 2, nullptr, p.ws.grid[2], nullptr, false, codes, q, false);
   if (a1.fuse || a1.coarsest_here || a2.nblocks != a1.nblocks) fail(BM_EINVAL, "nested pair: inconsistent levels");
   std::memcpy(out1, &a1, sizeof(a1));
   std::memcpy(out2, &a2, sizeof(a2));

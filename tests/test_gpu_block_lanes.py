@@ -37,6 +37,29 @@ def test_block_groups(shape, b, M, dt):
     assert float(np.abs(p.recompose(c).double().cpu().numpy() - back).max()) <= TOL[dt] * sc
 
 
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["float32", "float64"])
+@pytest.mark.parametrize("nested", [False, True], ids=["plain", "nested"])
+@pytest.mark.parametrize("shape,b", [((20, 37, 70), 9), ((33, 33, 70), 9), ((40, 70, 33), 17), ((98, 33, 40), 17)],
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_blocks_in_the_padding(shape, b, nested, dt):
+    """Two block levels pad to whole level-2 blocks: level-1 blocks past the
+    logical dims along one axis or several write nothing."""
+    from paper_2609_00205_amd import Plan
+    if nested and b == 9:
+        pytest.skip("the nested pair starts with 17-node blocks")
+    print("case", shape, b, nested, dt, flush=True)
+    x = synth.gaussian_random_field(shape, 3.0, seed=6, dtype=np.float64)
+    x = x.astype(np.float32 if dt == torch.float32 else np.float64)
+    p = Plan(shape, dtype=dt, block=b, L=2, M=0, nested=nested)
+    guard = torch.full((x.size + 64,), 7.0, dtype=dt, device="cuda")
+    out = guard[:x.size].view(shape)
+    c = p.decompose(torch.from_numpy(x).cuda())
+    p.recompose(c, out=out)
+    sc = float(np.abs(x).max())
+    assert float(np.abs(out.double().cpu().numpy() - x).max()) <= 4 * TOL[dt] * sc   # (both directions, two levels)
+    assert torch.all(guard[x.size:] == 7.0)
+
+
 NODES = [(0, 0, 0), (16, 16, 16), (32, 32, 32), (2, 2, 2), (1, 2, 2), (2, 3, 4), (5, 7, 9), (31, 16, 5), (16, 3, 32),
          (32, 2, 2)]
 
