@@ -645,6 +645,8 @@ bm_status bm_p8_compress(bm_p8 plan, const void* x_dev, const double* block_tol_
  *   slot 2(s-1)   decomposition level s (s = 1..L+M; one kernel for a block level)
  *   slot 2(s-1)+1 recomposition level s
  *   slot 2(L+M)   quantize, slot 2(L+M)+1 dequantize.
+ * (a level that ran in another level's launch, a nested pair's second or one of the
+ * last small global levels, shows none of its own)
  * *n receives the number of slots, 2(L+M)+2.  Synchronous. */
 bm_status bm_timing(bm_plan plan, int enable);
 bm_status bm_timing_get(bm_plan plan, double* ms, int64_t* calls, int cap, int* n);
