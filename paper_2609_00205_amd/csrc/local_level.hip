@@ -199,7 +199,11 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
   constexpr int POFF = SRC_LDS ? nest_offset<T, B>(PCC) : 0;
   static_assert(!SRC_LDS || POFF + G::DEC_LDS <= PREG, "nested level must fit in its parent's LDS region");
   const int tid = threadIdx.x;
-  const ColumnLane<B, NB> at(tid);
+  // (a pair of FP32 17^3 blocks makes rows of 34 lanes, which do as well or
+  // better here than groups of 16: coefficients / codes 313 / 351 against 325 /
+  // 349 us at 512^3 without global levels, 425 / 453 against 438 / 458 at 98 x
+  // 1200 x 1200)
+  const ColumnLane<B, NB, sizeof(T) == 4 && B == 17> at(tid);
   const int bl = at.bl, y = at.y, x = at.x, tb = y * B + x;
   const int64_t blk = g * NB + bl;
   const bool act = bl < NB && blk < a.nblocks;
