@@ -274,11 +274,14 @@ bm_status bm_dequantize_recompose(bm_plan plan, const int32_t* codes, const doub
  * (bm_quantize_roi, bm_dequantize, bm_decompose_quantize,
  * bm_dequantize_recompose, bm_compress) builds these tables from its map
  * first, a few launches (about 20 us at 512^3); after this call, calls
- * given the same block_tol pointer use the kept tables instead.  The map's
+ * given the same block_tol pointer use the kept tables instead; the fused
+ * calls form the classes of 9- and 17-node blocks from the taus (level 1:
+ * the map itself) in each block.  The map must stay allocated and its
  * contents must not change while it is kept (call again after changing
  * them), and later calls on another stream must be ordered after this one.
- * A call with another map builds its own tables over the kept ones and
- * drops them; block_tol = NULL drops them.  Stream-ordered. */
+ * A call with another map, of this plan or of the batch that owns it, builds
+ * its own tables over the kept ones and drops them; block_tol = NULL drops
+ * them.  Stream-ordered. */
 bm_status bm_quant_prepare(bm_plan plan, const double* block_tol, hipStream_t stream);
 
 /* ---- lossless stage (Sec. IV-B lossless stages) ----------------------- */

@@ -274,6 +274,9 @@ class Plan:
         if block_tol is not None:
             _need(block_tol, torch.float64, self.block_grid, "block_tol")
         call("bm_quant_prepare", self._h, _ptr(block_tol) if block_tol is not None else None, _stream(stream))
+        # (the library knows the kept map by its address, which no other map
+        # may take while it is kept)
+        self._kept_tol = block_tol
 
     def dequantize_recompose(self, codes: torch.Tensor, block_tol: torch.Tensor, out: Optional[torch.Tensor] = None,
                              stream=None) -> torch.Tensor:

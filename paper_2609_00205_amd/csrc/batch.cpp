@@ -255,6 +255,10 @@ void enqueue(bm_batch_s& b, Bound& B, bool dec, hipStream_t st) {
 
 void run(bm_batch_s& b, Bound& B, bool dec, bool graph, hipStream_t st) {
   if (graph && st == nullptr) fail(BM_EINVAL, "graph capture needs a stream other than the null stream");
+  // either direction writes its maps' propagated taus and scalar Deltas over
+  // those of a map that a field's plan keeps, also from a replayed graph
+  for (size_t f = 0; f < b.plans.size(); ++f)
+    if (b.plans[f]->ws.kept_tol != B.tol[f]) b.plans[f]->ws.kept_tol = nullptr;
   if (!graph) {
     enqueue(b, B, dec, st);
     return;
