@@ -141,7 +141,10 @@ bm_status bm_coeff_shape(bm_plan plan, int64_t padded_dims[3]);
  * calls add on first use and keep until bm_plan_destroy: the padded code
  * array of bm_compress / bm_compress_plan / bm_decompress and the batch
  * (padded nodes x 4), the padded coefficient array of bm_qoi_deltas and the
- * adjoint's padded gradient (padded nodes x sizeof dtype each), and the
+ * adjoint's padded gradient (padded nodes x sizeof dtype each), the scratch
+ * of the block levels' transposes (bm_decompose_adjoint, bm_recompose_adjoint,
+ * bm_qoi_deltas: block^3 values per block of the largest level, at most 128
+ * MiB, 256 MiB for 33-node blocks), and the
  * quantizer's task table.  The plan
  * owns all of it; a caller cannot supply its own.  Host memory (pinned
  * staging of the box list) is not counted.  Errors: BM_EINVAL (null). */
@@ -174,14 +177,15 @@ bm_status bm_recompose(bm_plan plan, const void* coeff, void* x, hipStream_t str
  * padded dims, in-place layout as bm_decompose writes it; gx: device, logical
  * dims, dtype of the plan (overwritten).  Padded nodes' gradients are added
  * into the nodes their clamped value came from (dropped under zero fill).
- * Uses the plan's grid buffers (and, on a padded grid with block levels, one
- * padded-size buffer allocated on first use).  Asynchronous on stream. */
+ * Uses the plan's grid buffers (and, with block levels, a bounded scratch
+ * and on a padded grid one padded-size buffer, allocated on first use:
+ * bm_workspace_size).  Asynchronous on stream. */
 bm_status bm_decompose_adjoint(bm_plan plan, const void* gcoeff, void* gx, hipStream_t stream);
 
 /* gcoeff = R^T(gx): gradient of <R(coeff), gx> with respect to coeff, e.g. the
  * sensitivities of a linear quantity of interest of the reconstruction.
  * gx: device, logical dims; gcoeff: device, padded dims, in-place layout
- * (overwritten).  Asynchronous on stream. */
+ * (overwritten).  Uses the same scratch.  Asynchronous on stream. */
 bm_status bm_recompose_adjoint(bm_plan plan, const void* gx, void* gcoeff, hipStream_t stream);
 
 /* ---- ROI tolerance maps (Sec. IV-C) ------------------------------------- */

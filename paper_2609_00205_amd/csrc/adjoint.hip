@@ -21,10 +21,11 @@
 // every node it covers, shared faces included.  The order in which the up to
 // eight contributions of a shared node are summed is fixed: by the parity
 // class of the contributing block, even before odd, z slowest.  The blocks of
-// a slab (a few layers along z) leave their contributions, b^3 values each,
-// in a scratch array; a second launch sums them node by node in that order.
-// HBM traffic is what bounds a level, and a slab's scratch is kept small
-// enough to stay in the 256 MB Infinity Cache between its two launches.
+// a slab (a few layers along z, of a strip along y and x where a layer is too
+// large) leave their contributions, b^3 values each, in a scratch array; a
+// second launch sums them node by node in that order.  HBM traffic is what
+// bounds a level, and a slab's scratch is kept small enough to stay in the
+// 256 MB Infinity Cache between its two launches.
 // (As 8 launches, one per parity class, that added into the grid in place,
 // every line was fetched and written several times: 384 x 384 x 256 FP32
 // 0.324 ms, now 0.18 ms.)  The transpose of the clamp padding adds the
@@ -32,6 +33,7 @@
 
 #include <algorithm>
 
+#include "adjoint_slab.h"
 #include "block.h"
 #include "internal.h"
 #include "line_solve.h"
@@ -152,17 +154,27 @@ __device__ inline T gather_yx(const T* R, int j, int y, int x) {
   return acc + T(0.5) * side + T(0.25) * corner;
 }
 
-// One slab of block layers [k0, k1) of a level and its scratch: block
-// (bz, by, bx) leaves its B^3 contributions in slot (bz mod ring, by, bx).
+// One slab of a level's blocks, from block o on, s per axis, and its scratch:
+// block (bz, by, bx) leaves its B^3 contributions in slot (bz mod ring, by,
+// bx) of rows of s[2] and layers of s[1] rows: the kernels' pointer to the
+// scratch lies where block (., 0, 0) would be.
 struct Slab {
   int64_t nb[3];          // blocks per axis of the level
-  int64_t k0, nblocks;    // first layer, blocks of the slab
+  int64_t o[3], s[3];     // first block of the slab, blocks per axis
+  int64_t nblocks;
   int64_t nwg, per;
   uint32_t ring;
-  FastDiv fnb2, fnb1, fring;
+  FastDiv fs2, fs1, fring;
   __device__ inline int64_t slot(int64_t bz, int64_t by, int64_t bx) const {
     const uint32_t r = uint32_t(bz) - fring.div(uint32_t(bz)) * ring;
-    return (int64_t(r) * nb[1] + by) * nb[2] + bx;
+    return (int64_t(r) * s[1] + by) * s[2] + bx;
+  }
+  // block k of the slab
+  __device__ inline void block(int64_t k, int64_t& bz, int64_t& by, int64_t& bx) const {
+    block_coords(uint32_t(k), fs2, fs1, s, bz, by, bx);
+    bz += o[0];
+    by += o[1];
+    bx += o[2];
   }
 };
 
@@ -203,8 +215,7 @@ struct BlockLane {
     tb = tid - bl * BB;
     act = NB == 1 ? tid < BB : bl < NB && g * NB + bl < sl.nblocks;
     const int64_t blk = NB == 1 || act ? g * NB + bl : 0;
-    block_coords(uint32_t(blk), sl.fnb2, sl.fnb1, sl.nb, bz, by, bx);
-    bz += sl.k0;
+    sl.block(blk, bz, by, bx);
     if (NB > 1 && bl >= NB) bl = 0;
     y = tb / B;
     x = tb - (tb / B) * B;
@@ -350,8 +361,11 @@ struct SumArgs {
   const T* part;
   Slab sl;
   NodeOut<T> out;
-  uint32_t z0;            // first plane of the slab
-  uint32_t n1, n2;        // rows per plane, nodes per row
+  // first node of the slab's own; y0 in groups of kSumR rows: that y is a
+  // multiple of kSumR there settles at compile time which rows can lie on a
+  // face (0.254 against 0.236 ms for 384 x 384 x 256 FP32)
+  uint32_t z0, y0, x0;
+  uint32_t n1, n2;        // rows and columns end here
   uint32_t ntask;         // wavefront tasks: kSumR rows of one plane, 64 nodes of each
   Unflat32 uf;            // task -> (plane, group of rows, 64 nodes)
 };
@@ -397,17 +411,17 @@ __global__ __launch_bounds__(NT) void k_block_sum(SumArgs<T> a) {
   uint32_t z, yg, seg;
   a.uf(w, z, yg, seg);
   z += a.z0;
-  const uint32_t x = seg * 64 + (threadIdx.x & 63);
+  const uint32_t x = a.x0 + seg * 64 + (threadIdx.x & 63);
   const bool in = x < a.n2;
   int bx[2], lx[2], by[2], ly[2], bz[2], lz[2];
-  const bool two = cover<B>(in ? x : 0, a.sl.nb[2], bx, lx) > 1;
+  const bool two = cover<B>(in ? x : a.x0, a.sl.nb[2], bx, lx) > 1;
   const int64_t o0 = bx[0] * B3 + lx[0], o1 = bx[1] * B3 + lx[1];
   const int nz = cover<B>(z, a.sl.nb[0], bz, lz);
   // a row of a block row's contributions at node (0, iz-th z, iy-th y)
   auto row = [&](int iz, int iy) {
     return a.part + a.sl.slot(bz[iz], by[iy], 0) * B3 + (lz[iz] * B + ly[iy]) * B;
   };
-  const uint32_t y0 = yg * kSumR;
+  const uint32_t y0 = (a.y0 + yg) * kSumR;
   T acc[kSumR], v1[kSumR];
 #pragma unroll
   for (int r = 0; r < kSumR; ++r) {
@@ -451,69 +465,58 @@ __global__ __launch_bounds__(NT) void k_block_sum(SumArgs<T> a) {
   }
 }
 
-// Bytes of scratch per slab: half the Infinity Cache, so that the second
-// launch finds it there (and the plan's memory does not grow with the grid).
-constexpr size_t kSlabBytes = size_t(128) << 20;
-
-// Layers per slab and layers in the scratch (one more than a slab, for the
-// last plane of the slab before, unless one slab takes the whole level).
-void slab_layers(const Level& L, size_t esize, int64_t& layers, int64_t& ring) {
-  const size_t layer = size_t(L.nb[1]) * L.nb[2] * L.b * L.b * L.b * esize;
-  int64_t fit = int64_t(kSlabBytes / layer);
-  if (fit >= L.nb[0]) {
-    layers = ring = L.nb[0];
-    return;
-  }
-  fit = std::max<int64_t>(fit - 1, 1);
-  const int64_t slabs = (L.nb[0] + fit - 1) / fit;
-  layers = (L.nb[0] + slabs - 1) / slabs;
-  ring = layers + 1;
-}
-
-// Runs a level slab by slab: blocks(slab) launches what leaves the
+// Runs a level slab by slab (slab_cut): blocks(slab) launches what leaves the
 // contributions of the slab's blocks in the plan's scratch (kept; sized for
-// the largest level on first use), then its nodes are summed.
+// the largest level on first use), then the slab's own nodes are summed.
 template <typename T, int B, bool REC, typename F>
 void run_slabs(bm_plan_s& p, int s, const NodeOut<T>& out, int per_wg, hipStream_t st, F blocks) {
   const Level& L = p.lv[s - 1];
   if (!p.ws.contrib) {
     size_t need = 0;
     for (const Level& l : p.lv)
-      if (l.local) {
-        int64_t n, r;
-        slab_layers(l, p.esize, n, r);
-        need = std::max(need, size_t(r) * l.nb[1] * l.nb[2] * l.b * l.b * l.b * p.esize);
-      }
+      if (l.local)
+        need = std::max(need, size_t(slab_cut(l.nb, l.b, p.esize).blocks()) * l.b * l.b * l.b * p.esize);
     plan_alloc_late(p, &p.ws.contrib, need);
   }
-  T* part = static_cast<T*>(p.ws.contrib);
-  int64_t layers, ring;
-  slab_layers(L, p.esize, layers, ring);
-  if (ring * L.nb[1] * L.nb[2] >= (int64_t(1) << 31)) fail(BM_EUNSUPPORTED, "too many blocks");
-  for (int64_t k0 = 0; k0 < L.nb[0]; k0 += layers) {
-    const int64_t k1 = std::min(L.nb[0], k0 + layers);
-    Slab sl{};
-    for (int k = 0; k < 3; ++k) sl.nb[k] = L.nb[k];
-    sl.k0 = k0;
-    sl.nblocks = (k1 - k0) * L.nb[1] * L.nb[2];
-    sl.nwg = (sl.nblocks + per_wg - 1) / per_wg;
-    sl.per = (sl.nwg + 7) / 8;
-    sl.ring = uint32_t(ring);
-    sl.fring = FastDiv(uint32_t(ring));
-    sl.fnb2 = FastDiv(uint32_t(L.nb[2]));
-    sl.fnb1 = FastDiv(uint32_t(L.nb[1]));
-    blocks(sl, part);
-    BM_HIP(hipGetLastError());
-    // planes of the slab; the far face goes with the last one
-    const int64_t z0 = k0 * (B - 1), z1 = k1 == L.nb[0] ? L.n[0] : k1 * (B - 1);
-    const int64_t ngy = (L.n[1] + kSumR - 1) / kSumR, nseg = (L.n[2] + 63) / 64, ntask = (z1 - z0) * ngy * nseg;
-    if (ntask >= (int64_t(1) << 31)) fail(BM_EUNSUPPORTED, "grid planes too large");
-    SumArgs<T> a{part, sl, out, uint32_t(z0), uint32_t(L.n[1]), uint32_t(L.n[2]), uint32_t(ntask),
-                 Unflat32(ngy, nseg)};
-    const int64_t nwg = (ntask + NT / 64 - 1) / (NT / 64);
-    hipLaunchKernelGGL((k_block_sum<T, B, REC>), dim3(unsigned((nwg + 7) / 8 * 8)), dim3(NT), 0, st, a);
-    BM_HIP(hipGetLastError());
-  }
+  const SlabCut c = slab_cut(L.nb, B, p.esize);
+  // nodes of blocks [lo, hi): up to the next one's first, the far face with the last
+  auto first = [](int64_t lo) { return uint32_t(lo * (B - 1)); };
+  auto end = [&](int a, int64_t hi) { return hi == L.nb[a] ? L.n[a] : hi * (B - 1); };
+  for (int64_t ky = 0; ky * c.cut[0] < L.nb[1]; ++ky)
+    for (int64_t kx = 0; kx * c.cut[1] < L.nb[2]; ++kx) {
+      const BlockRange y = strip(L.nb[1], c.cut[0], ky), x = strip(L.nb[2], c.cut[1], kx);
+      for (int64_t k0 = 0; k0 < L.nb[0]; k0 += c.layers) {
+        const int64_t k1 = std::min(L.nb[0], k0 + c.layers);
+        Slab sl{};
+        for (int k = 0; k < 3; ++k) sl.nb[k] = L.nb[k];
+        sl.o[0] = k0;
+        sl.o[1] = y.run;
+        sl.o[2] = x.run;
+        sl.s[0] = k1 - k0;
+        sl.s[1] = y.hi - y.run;
+        sl.s[2] = x.hi - x.run;
+        sl.nblocks = sl.s[0] * sl.s[1] * sl.s[2];
+        sl.nwg = (sl.nblocks + per_wg - 1) / per_wg;
+        sl.per = (sl.nwg + 7) / 8;
+        sl.ring = uint32_t(c.ring);
+        sl.fring = FastDiv(uint32_t(c.ring));
+        sl.fs2 = FastDiv(uint32_t(sl.s[2]));
+        sl.fs1 = FastDiv(uint32_t(sl.s[1]));
+        T* const part = reinterpret_cast<T*>(reinterpret_cast<intptr_t>(p.ws.contrib) -
+                                             (sl.o[1] * sl.s[2] + sl.o[2]) * int64_t(B) * B * B * int64_t(sizeof(T)));
+        blocks(sl, part);
+        BM_HIP(hipGetLastError());
+        const int64_t z1 = end(0, k1), n1 = end(1, y.hi), n2 = end(2, x.hi);
+        static_assert((B - 1) % kSumR == 0, "a strip's rows start a group");
+        SumArgs<T> a{part, sl, out, first(k0), first(y.lo) / kSumR, first(x.lo), uint32_t(n1), uint32_t(n2), 0, {}};
+        const int64_t ngy = (n1 + kSumR - 1) / kSumR - a.y0, nseg = (n2 - a.x0 + 63) / 64;
+        a.ntask = uint32_t((z1 - a.z0) * ngy * nseg);   // (of a scratch full of blocks: below 2^32)
+        a.uf = Unflat32(ngy, nseg);
+        const unsigned nwg = (a.ntask + NT / 64 - 1) / (NT / 64);
+        hipLaunchKernelGGL((k_block_sum<T, B, REC>), dim3((nwg + 7) / 8 * 8), dim3(NT), 0, st, a);
+        BM_HIP(hipGetLastError());
+      }
+    }
 }
 
 // the outputs of a recomposition level's transpose
@@ -594,13 +597,6 @@ struct W33Args {
   Slab sl;
 };
 
-// block (bz, by, bx) of index k in the slab
-template <typename T>
-__device__ inline void slab_block(const W33Args<T>& a, int64_t k, int64_t& bz, int64_t& by, int64_t& bx) {
-  block_coords(uint32_t(k), a.sl.fnb2, a.sl.fnb1, a.nb, bz, by, bx);
-  bz += a.sl.k0;
-}
-
 // z part of P3^T at the even planes of a column of 33 values
 template <typename T>
 __device__ inline T restrict_z33(const T (&v)[w33::B], int j) {
@@ -640,8 +636,16 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_w33_spread_x(W33Args<T> a, int from_zs) {
   using namespace w33;
   __shared__ T Z[ZB];
-  const int64_t blk = blockIdx.x + (from_zs ? a.sl.k0 * a.nb[1] * a.nb[2] : 0);   // zs: the slab's blocks
-  const int64_t bx = blk % a.nb[2], t = blk / a.nb[2], by = t % a.nb[1], bz = t / a.nb[1];
+  int64_t bz, by, bx;                    // zs: the slab's blocks
+  if (from_zs) {
+    a.sl.block(blockIdx.x, bz, by, bx);
+  } else {
+    bx = blockIdx.x % a.nb[2];
+    const int64_t t = blockIdx.x / a.nb[2];
+    by = t % a.nb[1];
+    bz = t / a.nb[1];
+  }
+  const int64_t blk = (bz * a.nb[1] + by) * a.nb[2] + bx;
   const int64_t c0 = bz * (MC - 1), c1 = by * (MC - 1), c2 = bx * (MC - 1), cpl = a.cn[1] * a.cn[2];
   for (int i = threadIdx.x; i < ZB; i += 256) {
     const int J = i / (MI * MI), r = i - J * MI * MI, I = r / MI, K = r - I * MI;
@@ -686,7 +690,7 @@ __global__ __launch_bounds__(w33::NT) void k_w33_dec_T(W33Args<T> a) {
   if (g >= 2 * a.sl.nblocks) return;
   const int h = int(g & 1);
   int64_t bz, by, bx;
-  slab_block(a, g >> 1, bz, by, bx);
+  a.sl.block(g >> 1, bz, by, bx);
   const int64_t blk = (bz * a.nb[1] + by) * a.nb[2] + bx;
   w33_spread_y(a, blk, h, lds);
   __syncthreads();
@@ -760,7 +764,7 @@ __global__ __launch_bounds__(w33::NT) void k_w33_rec_T_coarse(W33Args<T> a) {
   if (g >= 2 * a.sl.nblocks) return;
   const int h = int(g & 1);
   int64_t bz, by, bx;
-  slab_block(a, g >> 1, bz, by, bx);
+  a.sl.block(g >> 1, bz, by, bx);
   const int64_t blk = (bz * a.nb[1] + by) * a.nb[2] + bx;
   const int tid = threadIdx.x;
   const bool act = tid < NCOL;
@@ -795,7 +799,7 @@ __global__ __launch_bounds__(w33::NT) void k_w33_rec_T_fine(W33Args<T> a) {
   if (g >= 2 * a.sl.nblocks) return;
   const int h = int(g & 1);
   int64_t bz, by, bx;
-  slab_block(a, g >> 1, bz, by, bx);
+  a.sl.block(g >> 1, bz, by, bx);
   const int64_t blk = (bz * a.nb[1] + by) * a.nb[2] + bx;
   w33_spread_y(a, blk, h, T1);
   __syncthreads();
