@@ -195,11 +195,13 @@ struct BlockTArgs {
 
 // The element `lane` past a base that all lanes of a workgroup share: the
 // base stays in scalar registers and every access of a column takes the same
-// 32-bit lane offset, where a pointer per lane and plane costs two vector
-// registers each.
+// lane offset, where a pointer per lane and plane costs two vector registers
+// each.  64 bits: from 2^25 doubles or 2^26 floats a row on, the byte offset
+// of a block's last row does not fit in 32 (which take the same registers and
+// time).
 template <typename T>
-__device__ inline T* lane_at(T* base, uint32_t lane) {
-  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(base) + lane * uint32_t(sizeof(T)));
+__device__ inline T* lane_at(T* base, uint64_t lane) {
+  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(base) + lane * sizeof(T));
 }
 
 // A workgroup's block for this lane (several 9^3 blocks share a workgroup).
@@ -246,8 +248,8 @@ __global__ __launch_bounds__(BlockLane<B>::NT) void k_local_decompose_T(BlockTAr
     const int64_t cpl = a.cn[1] * a.cn[2];
     const T* col = a.gc + oz * a.cs[0] + oy * a.cs[1] + ox * a.cs[2];
     const T* ccol = a.gcur + (oz >> 1) * cpl + (oy >> 1) * a.cn[2] + (ox >> 1);
-    const uint32_t l = uint32_t(y * a.cs[1]) + uint32_t(x * a.cs[2]);
-    const uint32_t cl = uint32_t((y >> 1) * a.cn[2]) + uint32_t(x >> 1);
+    const uint64_t l = y * a.cs[1] + x * a.cs[2];
+    const uint64_t cl = (y >> 1) * a.cn[2] + (x >> 1);
 #pragma unroll
     for (int z = 0; z < B; ++z) {
       T w = T(0);
@@ -310,7 +312,7 @@ __global__ __launch_bounds__(BlockLane<B>::NT) void k_local_recompose_T(BlockTAr
     const bool lastz = k.bz == a.sl.nb[0] - 1;
     const int64_t pl = a.in[1] * a.in[2];
     const T* col = a.gin + oz * pl + oy * a.in[2] + ox;
-    const uint32_t l = uint32_t(y * a.in[2]) + uint32_t(x);
+    const uint64_t l = y * a.in[2] + x;
 #pragma unroll
     for (int z = 0; z < B; ++z)
       gv[z] = (own_yx && (z < B - 1 || lastz) && oz + z < a.lim[0]) ? *lane_at(col + z * pl, l) : T(0);
