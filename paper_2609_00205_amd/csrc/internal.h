@@ -397,7 +397,12 @@ PrepField prep_field(bm_plan_s& p, const double* block_tol, const QPrep& q);
 // s; only where a field has more blocks than one workgroup propagates),
 // tables of level s (index s; index 0: coarsest values), each a device prefix
 // array over the fields (first[nf] = total tasks)
-constexpr int64_t kPropOneGroup = 4096;   // level-2 blocks that one workgroup propagates
+// Level-2 blocks that one workgroup propagates, beside tau_global and the
+// flag in its launch; for more, a launch of many workgroups per level.  The
+// preparation in a fused call, one workgroup against launches, us: 216 blocks
+// 4.5 / 5 (two levels), 6.7 / 8.3 (three), 512 blocks 6.4 / 5.4 and 7.5 / 8,
+// 1000 blocks 11.5 / 7.3 and 13.5 / 9, 4096 blocks 33 / 8 and 37 / 12.
+constexpr int64_t kPropOneGroup = 512;
 struct PrepStages {
   const int64_t* prop_first[9] = {};
   int64_t prop_n[9] = {};
