@@ -637,8 +637,12 @@ __global__ __launch_bounds__((Geo<17, sizeof(T)>::NT)) __attribute__((amdgpu_wav
   decompose_group<T, 9, Q, NB, true>(a2, g, lds, cls);
 }
 
+// (waves: two levels' arguments take more scalar registers than eight waves a
+// SIMD leave, and with seven a third workgroup of 640 lanes does not fit a CU;
+// 30 scalars spilled to vector lanes cost less: 512^3 FP32 codes 464 -> 440 us
+// a restore with two global levels)
 template <typename T, bool Q>
-__global__ __launch_bounds__((Geo<17, sizeof(T), false>::NT)) void k_local_recompose_nest(RecArgs<T> a2, RecArgs<T> a1) {
+__global__ __launch_bounds__((Geo<17, sizeof(T), false>::NT)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_local_recompose_nest(RecArgs<T> a2, RecArgs<T> a1) {
   constexpr int NB = Geo<17, sizeof(T), false>::NB;
   __shared__ __attribute__((aligned(16))) T lds[NB * Geo<17>::REC_LDS];
   __shared__ double cls[Q ? 2 : 1][NB * 27];   // Delta classes of the blocks
