@@ -177,7 +177,7 @@ struct PoolMem {
   int device = -1;
 };
 PoolMem pool_take(size_t bytes, bool host);
-void pool_put(const PoolMem& m);
+void pool_put(const PoolMem& m) noexcept;
 void pool_release();
 
 template <typename T, bool HOST>

@@ -42,17 +42,21 @@ Pool& pool() {
   return *p;
 }
 
+void free_block(void* p, int device) {
+  if (device < 0)
+    (void)hipHostFree(p);
+  else
+    (void)hipFree(p);
+}
+
 void give_back(const std::vector<Block>& blocks) {
-  for (const Block& b : blocks) {
-    if (b.device < 0)
-      (void)hipHostFree(b.p);
-    else
-      (void)hipFree(b.p);
-  }
+  for (const Block& b : blocks) free_block(b.p, b.device);
 }
 
 // Moves the blocks that nothing took for kPoolIdle, and the oldest ones of a
-// kind over its bound, from the pool to `out`.  The caller holds the mutex.
+// kind over its bound, from the pool to `out`, which has room for every block
+// (a failure half way would leave a block with two owners or none).  The
+// caller holds the mutex.
 void expire(Pool& P, std::vector<Block>& out) {
   const auto old = clk::now() - kPoolIdle;
   for (size_t i = 0; i < P.idle.size();) {
@@ -93,6 +97,7 @@ PoolMem pool_take(size_t bytes, bool host) {
   {
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
+    out.reserve(P.idle.size());
     size_t best = P.idle.size();
     for (size_t i = 0; i < P.idle.size(); ++i) {
       const Block& b = P.idle[i];
@@ -111,17 +116,20 @@ PoolMem pool_take(size_t bytes, bool host) {
   return m;
 }
 
-void pool_put(const PoolMem& m) {
+void pool_put(const PoolMem& m) noexcept {
   if (!m.p) return;
   std::vector<Block> out;
+  bool kept = false;
   try {
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
+    out.reserve(P.idle.size() + 1);
     P.idle.push_back({m.p, m.bytes, m.device, clk::now()});
+    kept = true;
     expire(P, out);
-  } catch (...) {   // (no room for the list)
-    if (out.empty()) out.push_back({m.p, m.bytes, m.device, {}});
+  } catch (...) {   // (no room for the lists: the block was not taken in)
   }
+  if (!kept) free_block(m.p, m.device);
   give_back(out);
 }
 
