@@ -421,8 +421,9 @@ bm_status bm_decompress(const void* in, size_t in_bytes, void* x, hipStream_t st
  * bm_huffman_*) keep for the next such call: at most 2 GiB of device memory
  * per GPU and 64 MiB of pinned host memory per process, none of it in use
  * between calls.  Such a call also gives back by itself what none took for
- * five seconds, and an allocation of theirs that fails gives back everything
- * first.  Any thread may call this at any time. */
+ * five seconds, and an allocation of the library's that finds no memory left
+ * gives back everything and is tried again (other allocators in the process
+ * cannot: call this first).  Any thread may call this at any time. */
 bm_status bm_release_memory(void);
 
 /* ---- many fields (the paper's batched multi-field workloads, Sec. V) ------- */

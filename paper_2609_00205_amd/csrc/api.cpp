@@ -962,7 +962,7 @@ bm_status bm_decompress(const void* in, size_t in_bytes, void* x, hipStream_t st
       bm::p8_block_grid(*q, nb);
       const int64_t ntol = nb[0] * nb[1] * nb[2];
       if (h.ntol != ntol || h.payload < uint64_t(ntol) * 8) bm::fail(BM_ECORRUPT, "tolerance map size mismatch");
-      BM_HIP(hipMalloc(&g8.d, size_t(ntol) * sizeof(double)));
+      bm::dev_malloc(&g8.d, size_t(ntol) * sizeof(double));
       BM_HIP(hipMemcpyAsync(g8.d, pl, size_t(ntol) * 8, hipMemcpyHostToDevice, st));
       int32_t* codes = bm::p8_codes(*q);
       dec->decode(codes, bm::p8_coeff_size(*q));

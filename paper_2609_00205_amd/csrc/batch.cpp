@@ -202,7 +202,7 @@ void bind(bm_batch_s& b, Bound& B, bool dec, const void* const* x, const double*
     off_nfirst = im.put(first.data(), first.size() * sizeof(int64_t));
   }
   B.arena_bytes = im.bytes.size();
-  BM_HIP(hipMalloc(&B.arena, B.arena_bytes));
+  dev_malloc(&B.arena, B.arena_bytes);
   BM_HIP(hipMemcpyAsync(B.arena, im.bytes.data(), B.arena_bytes, hipMemcpyHostToDevice, st));
   BM_HIP(hipStreamSynchronize(st));
   auto at = [&](size_t off) { return static_cast<const void*>(static_cast<const uint8_t*>(B.arena) + off); };

@@ -179,6 +179,13 @@ struct PoolMem {
 PoolMem pool_take(size_t bytes, bool host);
 void pool_put(const PoolMem& m) noexcept;
 void pool_release();
+// hipMalloc of everything else the library allocates: tried again without the
+// pool's idle blocks when the device has no memory left
+void dev_malloc_bytes(void** p, size_t bytes);
+template <typename P>
+void dev_malloc(P** p, size_t bytes) {
+  dev_malloc_bytes(reinterpret_cast<void**>(p), bytes);
+}
 
 template <typename T, bool HOST>
 struct PoolBuf {
@@ -269,7 +276,7 @@ namespace bm {
 // Device memory owned by a plan, counted for bm_workspace_size.
 template <typename P>
 void plan_alloc(bm_plan_s& p, P** ptr, size_t bytes) {
-  BM_HIP(hipMalloc(reinterpret_cast<void**>(ptr), bytes));
+  dev_malloc(ptr, bytes);
   p.dev_bytes += bytes;
 }
 
@@ -278,12 +285,12 @@ void plan_alloc(bm_plan_s& p, P** ptr, size_t bytes) {
 // runs in the relaxed capture mode.
 template <typename P>
 void plan_alloc_late(bm_plan_s& p, P** ptr, size_t bytes) {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  BM_HIP(hipThreadExchangeStreamCaptureMode(&mode));
-  const hipError_t e = hipMalloc(reinterpret_cast<void**>(ptr), bytes);
-  BM_HIP(hipThreadExchangeStreamCaptureMode(&mode));
-  BM_HIP(e);
-  p.dev_bytes += bytes;
+  struct Mode {
+    hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
+    Mode() { BM_HIP(hipThreadExchangeStreamCaptureMode(&m)); }
+    ~Mode() { (void)hipThreadExchangeStreamCaptureMode(&m); }
+  } relaxed;
+  plan_alloc(p, ptr, bytes);
 }
 
 // Workgroups of a persistent launch over ntasks tasks: as many as stay

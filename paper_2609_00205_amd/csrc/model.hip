@@ -116,9 +116,9 @@ Run time_plan(int dtype, int b, int L, int M, int64_t n, int reps, hipStream_t s
   const size_t es = dtype == BM_F32 ? 4 : 8;
   const int64_t nlog = n * n * n, npad = p.pdims[0] * p.pdims[1] * p.pdims[2];
   const int64_t ntol = p.nb1[0] * p.nb1[1] * p.nb1[2];
-  BM_HIP(hipMalloc(&g.x, size_t(nlog) * es));
-  BM_HIP(hipMalloc(&g.codes, size_t(npad) * 4));
-  BM_HIP(hipMalloc(&g.tol, size_t(ntol) * 8));
+  dev_malloc(&g.x, size_t(nlog) * es);
+  dev_malloc(&g.codes, size_t(npad) * 4);
+  dev_malloc(&g.tol, size_t(ntol) * 8);
   const unsigned grid = unsigned(std::min<int64_t>(4096, (nlog + 255) / 256));
   if (dtype == BM_F32)
     hipLaunchKernelGGL(k_synth<float>, dim3(grid), dim3(256), 0, st, static_cast<float*>(g.x), n, n, n, 12345u);
@@ -234,7 +234,7 @@ void model_calibrate(int dtype, int b, bm_model& m, hipStream_t st) {
   // lossless: one line per Huffman stage, on code arrays of 2^16 .. 2^26
   int32_t* q = nullptr;
   const int64_t qmax = int64_t(1) << 26;
-  BM_HIP(hipMalloc(&q, size_t(qmax) * 4));
+  dev_malloc(&q, size_t(qmax) * 4);
   struct QG {
     int32_t* q;
     ~QG() { (void)hipFree(q); }

@@ -603,11 +603,11 @@ bm_p8_s* p8_create(const int64_t dims[3], int dtype, int L, int M) {
     p->tau.assign(L, nullptr);
     for (int s = 1; s < L; ++s) {
       const size_t bytes = size_t(p->n[s][0] * p->n[s][1] * p->n[s][2]) * p->esize;
-      BM_HIP(hipMalloc(&p->grid[s], bytes));
+      dev_malloc(&p->grid[s], bytes);
       BM_HIP(hipMemset(p->grid[s], 0, bytes));   // the zero fill beyond the assembled values
-      BM_HIP(hipMalloc(&p->tau[s], size_t(p->n[s][0] / 8) * (p->n[s][1] / 8) * (p->n[s][2] / 8) * sizeof(double)));
+      dev_malloc(&p->tau[s], size_t(p->n[s][0] / 8) * (p->n[s][1] / 8) * (p->n[s][2] / 8) * sizeof(double));
     }
-    BM_HIP(hipMalloc(&p->flag, sizeof(int64_t)));
+    dev_malloc(&p->flag, sizeof(int64_t));
     if (M > 0) {
       // the global levels: a plan of their own over the coarsest grid (clamp
       // extension to the lengths they halve, natural ends)
@@ -626,7 +626,7 @@ bm_p8_s* p8_create(const int64_t dims[3], int dtype, int L, int M) {
       // the last block level writes its assembled values straight into the
       // global plan's padded level-1 grid, and reads them back from there
       p->gin = level1_grid(*p->glob);
-      BM_HIP(hipMalloc(&p->tg, 2 * sizeof(double)));
+      dev_malloc(&p->tg, 2 * sizeof(double));
     }
   } catch (...) {
     for (void* g : p->grid)
@@ -657,7 +657,7 @@ void p8_free(bm_p8_s* p) {
 }
 
 int32_t* p8_codes(bm_p8_s& p) {
-  if (!p.codes) BM_HIP(hipMalloc(&p.codes, size_t(p8_coeff_size(p)) * sizeof(int32_t)));
+  if (!p.codes) dev_malloc(&p.codes, size_t(p8_coeff_size(p)) * sizeof(int32_t));
   return p.codes;
 }
 

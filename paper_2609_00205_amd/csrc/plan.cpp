@@ -428,7 +428,7 @@ bm_plan_s* bm_plan_build(const bm_config* c, bool pooled) {
     if (pooled) {
       p->slab = pool_take(total, false);
     } else {
-      BM_HIP(hipMalloc(&p->slab.p, total));
+      dev_malloc(&p->slab.p, total);
       p->slab.bytes = total;
     }
     p->dev_bytes = total - (kPrepBytes + 255) / 256 * 256;   // (the quantizer counts its task table once it is set up)

@@ -8,7 +8,8 @@
 // any stream may take it next.  The pool holds at most kPoolDevice bytes on a
 // GPU (less than 1% of its memory) and kPoolHost of pinned memory, gives back
 // what no call took for kPoolIdle when a later call looks, everything when
-// an allocation fails, and all of it on request (bm_release_memory).
+// an allocation of the library fails (which is then tried again), and all of
+// it on request (bm_release_memory).
 
 #include <chrono>
 #include <mutex>
@@ -74,17 +75,31 @@ void expire(Pool& P, std::vector<Block>& out) {
 
 void* fresh(size_t bytes, bool host) {
   void* p = nullptr;
-  hipError_t e = host ? hipHostMalloc(&p, bytes, hipHostMallocDefault) : hipMalloc(&p, bytes);
-  if (e != hipSuccess) {
+  if (!host) {
+    dev_malloc_bytes(&p, bytes);
+    return p;
+  }
+  hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocDefault);
+  if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     pool_release();
-    e = host ? hipHostMalloc(&p, bytes, hipHostMallocDefault) : hipMalloc(&p, bytes);
+    e = hipHostMalloc(&p, bytes, hipHostMallocDefault);
   }
-  check_hip(e, host ? "hipHostMalloc" : "hipMalloc");
+  check_hip(e, "hipHostMalloc");
   return p;
 }
 
 }  // namespace
+
+void dev_malloc_bytes(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    pool_release();
+    e = hipMalloc(p, bytes);
+  }
+  check_hip(e, "hipMalloc");
+}
 
 PoolMem pool_take(size_t bytes, bool host) {
   int device = -1;

@@ -143,6 +143,13 @@ static void retry() {
   CHECK(b.p && held[0] == 4 * GB);
   bm::pool_put(b);
   CHECK(held[0] == 0);
+  // what the rest of the library allocates, too; and nothing but a lack of memory is tried again
+  PoolMem c = bm::pool_take(GB, false);
+  bm::pool_put(c);
+  fail_hip = 1;
+  double* plan = nullptr;
+  bm::dev_malloc(&plan, 8 * GB);
+  CHECK(plan && held[0] == 8 * GB);
   fail_hip = 2;
   bool threw = false;
   try {
