@@ -4,6 +4,7 @@ PyTorch; every step of the computation runs in the library's HIP kernels.
 from __future__ import annotations
 
 import ctypes as C
+import threading
 from typing import Optional, Sequence, Tuple
 
 import torch
@@ -661,6 +662,21 @@ class Paper8Plan:
         return _take(buf, got.value)
 
 
+_side = threading.local()
+
+
+def _side_stream() -> torch.cuda.Stream:
+    """The calling thread's side stream on the current device.  The first use
+    of a stream costs 0.15 to 0.5 ms (its queue is set up then), so the
+    thread's batches share one: all of them come from and go back to the null
+    stream, which orders them anyway."""
+    streams = _side.__dict__.setdefault("streams", {})
+    dev = torch.cuda.current_device()
+    if dev not in streams:
+        streams[dev] = torch.cuda.Stream()
+    return streams[dev]
+
+
 class Batch:
     """Many fields of one dtype and block size through the fused pipeline in
     few launches (one launch per block level for all fields; for
@@ -698,7 +714,6 @@ class Batch:
             resolved = BMConfig()
             call("bm_plan_config", ph, C.byref(resolved))
             self.plans.append(Plan._borrow(ph, resolved, self.device))
-        self._graph_stream = None
 
     def __len__(self):
         return len(self.plans)
@@ -722,9 +737,7 @@ class Batch:
         cur = stream if stream is not None else torch.cuda.current_stream()
         if not use_graph or cur.cuda_stream != 0:
             return fn(C.c_void_p(cur.cuda_stream))
-        if self._graph_stream is None:
-            self._graph_stream = torch.cuda.Stream()
-        side = self._graph_stream
+        side = _side_stream()
         side.wait_stream(cur)
         r = fn(C.c_void_p(side.cuda_stream))
         cur.wait_stream(side)
