@@ -440,7 +440,7 @@ __global__ __launch_bounds__(NT) void k_line_pass(PassArgs<T> a) {
       }
     }
   };
-  // the pivots (m <= 3 NT) are fetched with the first batch
+  // the pivots (m <= 64 kLineQ) are fetched with the first batch
   constexpr int NP = (64 * kLineQ + NT - 1) / NT;   // pivots per thread
   double pv[NP];
 #pragma unroll
@@ -870,7 +870,7 @@ bool launch_plane(const bm_plan_s& p, int s, const View3& in, bool mask, void* o
 // levels, of which the last four (17^3 down to 3^3) run here: 24 launches of
 // 3 to 5 us -> two of 24 us, the fused step 161 -> 112 us.
 constexpr int kTailLevels = 8;         // levels a launch can hold
-constexpr int kTailNodes = 5000;       // nodes of its first level (see tail_first)
+constexpr int64_t kTailBytes = 32 << 10;   // grid of its first level (see tail_first)
 constexpr int kTailM = 16 * 3;         // coarse nodes per line (Q = 3)
 
 struct TailLevel {
@@ -1194,11 +1194,14 @@ void launch_interp(const bm_plan_s& p, int s, const void* coeff, const int32_t* 
 }
 
 // The first of the last levels that run in one tail launch (nlev + 1: none):
-// global levels that are not fused with a block level, of at most kTailNodes
-// nodes, whose lines take the 3-unknown row solves and whose grids fit a
-// workgroup's LDS.  A 17^3 level takes 7 us more here than a 9^3 one and 14 us
-// as launches of its own; twice its nodes would take as long on the one CU as
-// spread over the chip, and 33^3 does not fit.
+// global levels that are not fused with a block level, whose grid has at most
+// kTailBytes, whose lines take the 3-unknown row solves and whose grids fit a
+// workgroup's LDS.  Beyond, one CU takes longer than three launches: two
+// levels from the first on, decomposition / recomposition in us, first level
+// here / as launches: FP32 17 x 17 x 25 (29 KB) 16.3 / 18.3 against 17.6 /
+// 19.7, 17 x 17 x 33 (38 KB) 19.8 / 22.4 against 17.2 / 20.8; FP64 13 x 17 x 17
+// (30 KB) 14.7 / 16.8 against 15.9 / 19.4, 17^3 (39 KB) 17.2 / 19.2 against
+// 16.3 / 19.9 (33^3 with codes 26.4 / 29.4 against 22.6 / 26.3).
 int64_t tail_half(const Level& L) {   // the first pass's result (no pass: nothing)
   if (L.coarsen[2]) return L.n[0] * L.n[1] * L.m[2];
   return L.coarsen[1] ? L.n[0] * L.m[1] * L.n[2] : 0;
@@ -1216,10 +1219,10 @@ int tail_first(const bm_plan_s& p) {
     for (int k = 0; k < 3; ++k) {
       n *= L.n[k];
       m *= L.m[k];
-      ok = ok && L.n[k] <= kTailNodes;
+      ok = ok && n * int64_t(p.esize) <= kTailBytes;
       if (L.coarsen[k]) ok = ok && L.n[k] >= 3 && L.m[k] == (L.n[k] + 1) / 2 && L.m[k] <= kTailM;
     }
-    if (!ok || n > kTailNodes) break;
+    if (!ok) break;
     const int64_t half = tail_half(L);
     const int64_t piv = int64_t(p.nlev - s + 1) * 3 * kTailM;
     if ((piv + n + m + half) * int64_t(p.esize) + n * int64_t(std::max<size_t>(p.esize, 4)) > kPlaneLds) break;
