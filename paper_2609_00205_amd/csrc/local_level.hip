@@ -431,17 +431,17 @@ __device__ __attribute__((always_inline)) inline void decompose_group(const DecA
 // (FP64 rows of 17 values are 128 bytes wide in any case and read best as
 // rows: 512^3 FP64 446 / 453 us against 463 / 465 in groups of 16 lanes, where
 // the decomposition has 602 / 555 against 574 / 524.)
-template <typename T, int B, bool Q, int NBG = Geo<B, sizeof(T), false>::NB, int MODE = 0>
+template <typename T, int B, bool Q, int NBG = Geo<B, sizeof(T), false>::NB, int MODE = 0, bool ROWS = sizeof(T) == 8>
 __device__ __attribute__((always_inline)) inline void recompose_group(const RecArgs<T>& a, int64_t g, T* lds,
                                                                         double (*cls)[NBG * 27]) {
   using G = Geo<B, sizeof(T), false>;
   constexpr int BB = G::BB, MC = G::MC, MI = G::MI, NB = NBG;
   constexpr int PREG = MODE == 1 ? Geo<2 * B - 1>::REC_LDS : G::REC_LDS;   // LDS elements per block
   constexpr int POFF = MODE == 1 ? nest_offset<T, B>(0) : 0;
-  constexpr int NT = MODE == 1 ? Geo<2 * B - 1, sizeof(T), false>::NT : G::NT;   // lanes of the workgroup
+  constexpr int BL = MODE == 1 ? 2 * B - 1 : B, NT = (NBG * BL * BL + 63) / 64 * 64;   // lanes of the workgroup
   static_assert(MODE != 1 || POFF + G::REC_LDS <= PREG, "nested level must fit in its parent's LDS region");
   const int tid = threadIdx.x;
-  const ColumnLane<B, NB, sizeof(T) == 8> at(tid);
+  const ColumnLane<B, NB, ROWS> at(tid);
   const int bl = at.bl, y = at.y, x = at.x, tb = y * B + x;
   const int64_t blk = g * NB + bl;
   const bool act = bl < NB && blk < a.nblocks;
@@ -641,16 +641,15 @@ __global__ __launch_bounds__((Geo<17, sizeof(T)>::NT)) __attribute__((amdgpu_wav
 // SIMD leave, and with seven a third workgroup of 640 lanes does not fit a CU;
 // 30 scalars spilled to vector lanes cost less: 512^3 FP32 codes 464 -> 440 us
 // a restore with two global levels)
-template <typename T, bool Q>
-__global__ __launch_bounds__((Geo<17, sizeof(T), false>::NT)) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_local_recompose_nest(RecArgs<T> a2, RecArgs<T> a1) {
-  constexpr int NB = Geo<17, sizeof(T), false>::NB;
+template <typename T, bool Q, int NB, bool ROWS>
+__global__ __launch_bounds__((NB * 289 + 63) / 64 * 64) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<T>))) void k_local_recompose_nest(RecArgs<T> a2, RecArgs<T> a1) {
   __shared__ __attribute__((aligned(16))) T lds[NB * Geo<17>::REC_LDS];
   __shared__ double cls[Q ? 2 : 1][NB * 27];   // Delta classes of the blocks
   const int64_t g = xcd_group(blockIdx.x, a1.per);
   if (g >= a1.nwg) return;
-  recompose_group<T, 9, Q, NB, 1>(a2, g, lds, cls);
+  recompose_group<T, 9, Q, NB, 1, ROWS>(a2, g, lds, cls);
   __syncthreads();
-  recompose_group<T, 17, Q, NB, 2>(a1, g, lds, cls);
+  recompose_group<T, 17, Q, NB, 2, ROWS>(a1, g, lds, cls);
 }
 
 // Many fields in one launch: workgroup k takes task k, block group
@@ -793,7 +792,7 @@ void launch_dec(const bm_plan_s& p, int s, const View3& src, bool first, void* c
 
 template <typename T, int B>
 RecArgs<T> rec_args(const bm_plan_s& p, int s, const void* coeff, const void* cin, void* out, bool last,
-                    const int32_t* codes, const QPrep* q, bool crop = true) {
+                    const int32_t* codes, const QPrep* q, bool crop = true, int nb = Geo<B, sizeof(T), false>::NB) {
   using G = Geo<B, sizeof(T), false>;
   const Level& L = p.lv[s - 1];
   RecArgs<T> a{};
@@ -824,7 +823,7 @@ RecArgs<T> rec_args(const bm_plan_s& p, int s, const void* coeff, const void* ci
   if (a.nblocks >= (int64_t(1) << 32)) fail(BM_EUNSUPPORTED, "too many blocks");
   a.fnb2 = FastDiv(uint32_t(L.nb[2]));
   a.fnb1 = FastDiv(uint32_t(L.nb[1]));
-  a.nwg = (a.nblocks + G::NB - 1) / G::NB;
+  a.nwg = (a.nblocks + nb - 1) / nb;
   a.per = (a.nwg + 7) / 8;
   if (q) {
     a.codes = codes;
@@ -924,18 +923,46 @@ void launch_dec_nest(const bm_plan_s& p, int s, const View3& src, bool first, vo
   BM_HIP(hipGetLastError());
 }
 
+template <typename T, int NB, bool ROWS>
+void launch_rec_pairs(const bm_plan_s& p, int s, const void* coeff, const void* cin, void* out, bool last,
+                      const int32_t* codes, const QPrep* q, hipStream_t st) {
+  const RecArgs<T> a1 = rec_args<T, 17>(p, s, coeff, nullptr, out, last, codes, q, false, NB);
+  const RecArgs<T> a2 = rec_args<T, 9>(p, s + 1, coeff, cin, nullptr, false, codes, q, false);
+  if (a1.fuse || a1.coarsest_here || a2.nblocks != a1.nblocks) fail(BM_EINVAL, "nested pair: inconsistent levels");
+  auto* const k = q ? k_local_recompose_nest<T, true, NB, ROWS> : k_local_recompose_nest<T, false, NB, ROWS>;
+  hipLaunchKernelGGL(k, dim3(unsigned(8 * a1.per)), dim3((NB * 289 + 63) / 64 * 64), 0, st, a2, a1);
+  BM_HIP(hipGetLastError());
+}
+
+// FP32 pairs: two blocks a workgroup share the lines between them, which pays
+// where many workgroups write most of what they span; with few blocks, or an
+// output cropped to a part of them, workgroups of one block start and end
+// sooner; under codes and a global level, whose coarse values come from one
+// more grid, one block in plain rows.  us, one block in groups of 16 / one in
+// rows / two, without codes; with:
+//   257^3, M = 0        34 / 37 / 38;      32 / 33 / 38
+//   513^3, M = 0        429 / 393 / 362;   410 / 377 / 362
+//   513^3, M = 1        439 / 403 / 377;   435 / 405 / 409
+//   98 x 1200^2, M = 1  465 / 449 / 443;   475 / 463 / 487
+//   1 x 4096^2, M = 0   471 / 456 / 523;   473 / 475 / 565
+//   1 x 4096^2, M = 1   543 / 533 / 620;   600 / 604 / 698
 template <typename T>
 void launch_rec_nest(const bm_plan_s& p, int s, const void* coeff, const void* cin, void* out, bool last,
                      const int32_t* codes, const QPrep* q, hipStream_t st) {
-  using G = Geo<17, sizeof(T), false>;
-  const RecArgs<T> a1 = rec_args<T, 17>(p, s, coeff, nullptr, out, last, codes, q, false);
-  const RecArgs<T> a2 = rec_args<T, 9>(p, s + 1, coeff, cin, nullptr, false, codes, q, false);
-  if (a1.fuse || a1.coarsest_here || a2.nblocks != a1.nblocks) fail(BM_EINVAL, "nested pair: inconsistent levels");
-  if (q)
-    hipLaunchKernelGGL((k_local_recompose_nest<T, true>), dim3(unsigned(8 * a1.per)), dim3(G::NT), 0, st, a2, a1);
-  else
-    hipLaunchKernelGGL((k_local_recompose_nest<T, false>), dim3(unsigned(8 * a1.per)), dim3(G::NT), 0, st, a2, a1);
-  BM_HIP(hipGetLastError());
+  if constexpr (sizeof(T) == 8) {
+    launch_rec_pairs<T, 1, true>(p, s, coeff, cin, out, last, codes, q, st);
+  } else {
+    const Level& L = p.lv[s - 1];
+    double whole = 1.0;                  // share of the blocks' nodes in the output
+    for (int k = 0; k < 3; ++k) whole *= last ? double(p.dims[k]) / double(L.n[k]) : 1.0;
+    const bool fused = p.fuse_next && s + 1 == p.L;
+    if (L.nb[0] * L.nb[1] * L.nb[2] < 8192 || whole < 0.75)
+      launch_rec_pairs<T, 1, false>(p, s, coeff, cin, out, last, codes, q, st);
+    else if (q && fused)
+      launch_rec_pairs<T, 1, true>(p, s, coeff, cin, out, last, codes, q, st);
+    else
+      launch_rec_pairs<T, 2, false>(p, s, coeff, cin, out, last, codes, q, st);
+  }
 }
 
 }  // namespace
