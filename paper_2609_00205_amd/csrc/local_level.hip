@@ -610,13 +610,13 @@ __global__ __launch_bounds__((Geo<B, sizeof(T)>::NT)) __attribute__((amdgpu_wave
   decompose_group<T, B, Q>(a, g, lds, cls);
 }
 
-template <typename T, int B, bool Q>
-__global__ __launch_bounds__((Geo<B, sizeof(T), false>::NT)) void k_local_recompose(RecArgs<T> a) {
-  __shared__ T lds[Geo<B, sizeof(T), false>::NB * Geo<B>::REC_LDS];
-  __shared__ double cls[Q ? 2 : 1][Geo<B, sizeof(T), false>::NB * 27];   // Delta classes of the blocks
+template <typename T, int B, bool Q, int NB>
+__global__ __launch_bounds__((NB * B * B + 63) / 64 * 64) void k_local_recompose(RecArgs<T> a) {
+  __shared__ T lds[NB * Geo<B>::REC_LDS];
+  __shared__ double cls[Q ? 2 : 1][NB * 27];   // Delta classes of the blocks
   const int64_t g = xcd_group(blockIdx.x, a.per);
   if (g >= a.nwg) return;
-  recompose_group<T, B, Q>(a, g, lds, cls);
+  recompose_group<T, B, Q, NB>(a, g, lds, cls);
 }
 
 // Nested schedule: block levels of 17- and 9-node blocks over the same
@@ -841,16 +841,26 @@ RecArgs<T> rec_args(const bm_plan_s& p, int s, const void* coeff, const void* ci
   return a;
 }
 
+template <typename T, int B, int NB>
+void launch_rec_nb(const bm_plan_s& p, int s, const void* coeff, const void* cin, void* out, bool last,
+                   const int32_t* codes, const QPrep* q, hipStream_t st) {
+  const RecArgs<T> a = rec_args<T, B>(p, s, coeff, cin, out, last, codes, q, true, NB);
+  auto* const k = q ? k_local_recompose<T, B, true, NB> : k_local_recompose<T, B, false, NB>;
+  hipLaunchKernelGGL(k, dim3(unsigned(8 * a.per)), dim3((NB * B * B + 63) / 64 * 64), 0, st, a);
+  BM_HIP(hipGetLastError());
+}
+
+// (two FP32 blocks a workgroup share lines along x; where a row has one block
+// there is none to share: 2200 x 2200 x 1 one level 130 -> 115 us, with codes
+// 101 -> 87)
 template <typename T, int B>
 void launch_rec(const bm_plan_s& p, int s, const void* coeff, const void* cin, void* out, bool last,
                 const int32_t* codes, const QPrep* q, hipStream_t st) {
-  using G = Geo<B, sizeof(T), false>;
-  const RecArgs<T> a = rec_args<T, B>(p, s, coeff, cin, out, last, codes, q);
-  if (q)
-    hipLaunchKernelGGL((k_local_recompose<T, B, true>), dim3(unsigned(8 * a.per)), dim3(G::NT), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_local_recompose<T, B, false>), dim3(unsigned(8 * a.per)), dim3(G::NT), 0, st, a);
-  BM_HIP(hipGetLastError());
+  constexpr int NB = Geo<B, sizeof(T), false>::NB;
+  if constexpr (B == 17 && NB > 1)
+    if (p.lv[s - 1].nb[2] == 1)
+      return launch_rec_nb<T, B, 1>(p, s, coeff, cin, out, last, codes, q, st);
+  launch_rec_nb<T, B, NB>(p, s, coeff, cin, out, last, codes, q, st);
 }
 
 
@@ -934,6 +944,13 @@ void launch_rec_pairs(const bm_plan_s& p, int s, const void* coeff, const void* 
   BM_HIP(hipGetLastError());
 }
 
+// share of a recomposition level's nodes (whole blocks) in its output
+inline double whole(const bm_plan_s& p, int s, bool last) {
+  double w = 1.0;
+  for (int k = 0; k < 3; ++k) w *= last ? double(p.dims[k]) / double(p.lv[s - 1].n[k]) : 1.0;
+  return w;
+}
+
 // FP32 pairs: two blocks a workgroup share the lines between them, which pays
 // where many workgroups write most of what they span; with few blocks, or an
 // output cropped to a part of them, workgroups of one block start and end
@@ -953,10 +970,8 @@ void launch_rec_nest(const bm_plan_s& p, int s, const void* coeff, const void* c
     launch_rec_pairs<T, 1, true>(p, s, coeff, cin, out, last, codes, q, st);
   } else {
     const Level& L = p.lv[s - 1];
-    double whole = 1.0;                  // share of the blocks' nodes in the output
-    for (int k = 0; k < 3; ++k) whole *= last ? double(p.dims[k]) / double(L.n[k]) : 1.0;
     const bool fused = p.fuse_next && s + 1 == p.L;
-    if (L.nb[0] * L.nb[1] * L.nb[2] < 8192 || whole < 0.75)
+    if (L.nb[0] * L.nb[1] * L.nb[2] < 8192 || whole(p, s, last) < 0.75)
       launch_rec_pairs<T, 1, false>(p, s, coeff, cin, out, last, codes, q, st);
     else if (q && fused)
       launch_rec_pairs<T, 1, true>(p, s, coeff, cin, out, last, codes, q, st);

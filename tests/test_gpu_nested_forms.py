@@ -38,3 +38,22 @@ def test_fused_equals_unfused(shape, M):
     p.dequantize_recompose(codes, bt, out=out)
     assert torch.equal(out, ref)
     assert bool((guard[x.numel():] == 7.0).all())
+
+
+@pytest.mark.parametrize("shape,M", [((90, 70, 1), 1), ((40, 33, 17), 0), ((40, 33, 18), 0), ((17, 300, 9), 2)], ids=str)
+def test_rows_of_one_block(shape, M):
+    """The plain schedule where a row has one block and where it has two."""
+    from paper_2609_00205_amd import Plan
+    gen = torch.Generator(device="cuda").manual_seed(32)
+    p = Plan(shape, block=17, L=1, M=M)
+    print("case", shape, M, p.block_grid, flush=True)
+    x = torch.randn(shape, device="cuda", generator=gen)
+    guard = torch.full((x.numel() + 64,), 7.0, device="cuda")
+    out = guard[:x.numel()].view(shape)
+    p.recompose(p.decompose(x), out=out)
+    assert float((out - x).abs().max()) <= 4e-6 * float(x.abs().max())
+    bt = 10.0 ** (torch.rand(p.block_grid, dtype=torch.float64, device="cuda", generator=gen) * 3 - 4)
+    codes = p.decompose_quantize(x, bt)
+    p.dequantize_recompose(codes, bt, out=out)
+    assert torch.equal(out, p.recompose(p.dequantize(codes, bt)))
+    assert bool((guard[x.numel():] == 7.0).all())
