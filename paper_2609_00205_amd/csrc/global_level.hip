@@ -639,8 +639,10 @@ void launch_pass(const bm_plan_s& p, int s, int axis, const View3& in, const int
   // 512 lanes for tiles of 32 and more lines: a tile's LDS leaves four
   // workgroups per CU, which with 256 lanes is half the wavefronts (y pass at
   // 257 x 257 x 129 FP32: 0.0271 -> 0.0225 ms; tiles of 16 lines have no work
-  // for eight wavefronts: 0.0227 -> 0.0257 ms at 321 x 161 x 161)
-  const bool wide = a.W >= 32;
+  // for eight wavefronts: 0.0227 -> 0.0257 ms at 321 x 161 x 161; nor have lines
+  // of a flat field: one level of 3 x 1100 x 1100 FP32 93 us with 256 lanes, 101
+  // with 512, 33 x 1100 x 1100 410 / 420, 65 x 700 x 700 304 / 304, FP64 492 / 488)
+  const bool wide = a.W >= 32 && a.nl >= 64;
   auto go = [&](auto q) {
     constexpr int Q = decltype(q)::value;
     if (wide)
