@@ -676,12 +676,6 @@ void launch_pass(const bm_plan_s& p, int s, int axis, const View3& in, const int
 constexpr int kPlaneNT = 1024;
 constexpr int kPlaneLds = 152 * 1024;
 
-// A level of up to this many cells has its details written by the plane pass's
-// launch (129^3 FP32 into 512^3 codes 20.2 + 13.9 -> 26.4 us, 65^3 4.6 + 7.1
-// -> 7.8); beyond it the workgroups of 152 KB LDS would hold back what k_details
-// keeps in flight.
-constexpr int64_t kDetCells = int64_t(1) << 19;
-
 template <typename T>
 struct PlaneArgs {
   const T* in;
@@ -718,6 +712,8 @@ __device__ inline T restrict_row(int J, int nl, int m, V v) {
 
 // DET: the workgroups past the planes (a.planes) write the level's details, which need
 // the same grid: a launch less, and cells run on the CUs that have no plane.
+// In us, apart / here: 65^3 FP32 18.5 / 15.7, 145^3 33.5 / 28.0, 513 x 129 x 129
+// (1.1 M cells) 75.8 / 68.6, 1025 x 145 x 145 (2.7 M) 133 / 126.
 template <typename T, int Q, bool DET>
 __global__ __launch_bounds__(kPlaneNT) void k_plane_pass(PlaneArgs<T> a, DetArgs<T> det) {
   __shared__ __align__(16) unsigned char smem[kPlaneLds];
@@ -1175,7 +1171,7 @@ bool launch_details(const bm_plan_s& p, int s, const void* u, void* coeff, int32
   DetArgs<T> a{static_cast<const T*>(u), {L.n[0], L.n[1], L.n[2]}, {L.m[0], L.m[1], L.m[2]}, L.coarsen[0],
                L.coarsen[1], L.coarsen[2], static_cast<T*>(coeff), {cv.s[0], cv.s[1], cv.s[2]}, codes, qinv, flag};
   const int64_t cells = L.m[0] * L.m[1] * L.m[2];
-  if (L.coarsen[0] && cells <= kDetCells &&
+  if (L.coarsen[0] &&
       launch_plane<T>(p, s, dense_view(const_cast<void*>(u), L.n), false, p.ws.t1, nullptr, nullptr, st, false, &a))
     return true;
   hipLaunchKernelGGL(k_details<T>, dim3(grid_for(cells)), dim3(NT), 0, st, a);

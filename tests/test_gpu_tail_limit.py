@@ -49,3 +49,21 @@ def test_either_side_of_the_limit(shape, dt, L, M):
     q = a.decompose_quantize(x, tol)
     assert torch.equal(q, z.decompose_quantize(x, tol))
     assert torch.equal(a.dequantize_recompose(q, tol), z.dequantize_recompose(q, tol))
+
+
+@pytest.mark.parametrize("shape,dt,M", [((515, 131, 129), F32, 1), ((1025, 145, 145), F32, 2), ((700, 97, 95), F64, 1)],
+                         ids=str)
+def test_details_of_many_planes(shape, dt, M):
+    """Details written by the plane pass's launch on grids of more than 2^19 coarse cells."""
+    from paper_2609_00205_amd import Plan
+    print("case", shape, dt, M, flush=True)
+    kw = dict(dtype=dt, block=17, L=0, M=M)
+    a, z = Plan(shape, **kw), _single(shape, **kw)
+    x = torch.randn(shape, dtype=dt, device="cuda", generator=torch.Generator(device="cuda").manual_seed(33))
+    c = a.decompose(x)
+    assert torch.equal(c, z.decompose(x))
+    assert torch.equal(a.recompose(c), z.recompose(c))
+    tol = a.tolmap_from_boxes([], 1e-2)
+    q = a.decompose_quantize(x, tol)
+    assert torch.equal(q, z.decompose_quantize(x, tol))
+    assert torch.equal(a.dequantize_recompose(q, tol), z.dequantize_recompose(q, tol))
