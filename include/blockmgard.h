@@ -363,8 +363,9 @@ bm_status bm_huffman_code_lengths(const uint64_t* hist, uint8_t* len);
  * enc_copy (the stream's words and outliers to the host), enc_crc (the
  * container's CRC-32 from those block CRCs and the host's bytes; 0 outside
  * bm_compress).  Decode:
- * dec_parse (header checks and decode tables, host), dec_upload (tables,
- * offsets, words and outliers to the device), dec_decode (device).  enc_n
+ * dec_parse (header checks and decode tables, host), dec_upload (words and
+ * outliers to the device while the host parses, then tables and offsets: the
+ * copies, not the wait between them), dec_decode (device).  enc_n
  * and dec_n: symbols of those calls (0: none yet).  Never fails. */
 typedef struct {
   double enc_hist_ms, enc_table_ms, enc_sizes_ms, enc_encode_ms, enc_copy_ms, enc_crc_ms;
