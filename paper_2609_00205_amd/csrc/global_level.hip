@@ -868,7 +868,7 @@ bool launch_plane(const bm_plan_s& p, int s, const View3& in, bool mask, void* o
 // levels, of which the last four (17^3 down to 3^3) run here: 24 launches of
 // 3 to 5 us -> two of 24 us, the fused step 161 -> 112 us.
 constexpr int kTailLevels = 8;         // levels a launch can hold
-constexpr int64_t kTailBytes = 32 << 10;   // grid of its first level (see tail_first)
+constexpr int64_t kTailBytes = 27 << 10;   // grid of its first level (see tail_first)
 constexpr int kTailM = 16 * 3;         // coarse nodes per line (Q = 3)
 
 struct TailLevel {
@@ -1194,12 +1194,13 @@ void launch_interp(const bm_plan_s& p, int s, const void* coeff, const int32_t* 
 // The first of the last levels that run in one tail launch (nlev + 1: none):
 // global levels that are not fused with a block level, whose grid has at most
 // kTailBytes, whose lines take the 3-unknown row solves and whose grids fit a
-// workgroup's LDS.  Beyond, one CU takes longer than three launches: two
-// levels from the first on, decomposition / recomposition in us, first level
-// here / as launches: FP32 17 x 17 x 25 (29 KB) 16.3 / 18.3 against 17.6 /
-// 19.7, 17 x 17 x 33 (38 KB) 19.8 / 22.4 against 17.2 / 20.8; FP64 13 x 17 x 17
-// (30 KB) 14.7 / 16.8 against 15.9 / 19.4, 17^3 (39 KB) 17.2 / 19.2 against
-// 16.3 / 19.9 (33^3 with codes 26.4 / 29.4 against 22.6 / 26.3).
+// workgroup's LDS.  Beyond, one CU takes longer than three launches.  One
+// level in us, here / as launches, decompose, recompose, the same with codes:
+//   FP32 17 x 17 x 19 (22 KB)  10.7 / 12.8, 12.1 / 15.8, 12.9 / 13.5, 12.4 / 13.5
+//   FP32 19^3 (27 KB)          12.3 / 13.1, 14.0 / 15.9, 14.5 / 13.5, 14.4 / 13.6
+//   FP32 17 x 25 x 19 (32 KB)  13.3 / 13.0, 15.9 / 15.4, 15.5 / 13.4, 16.2 / 13.5
+//   FP64 15^3 (27 KB)          10.6 / 12.0, 12.2 / 14.4, 12.6 / 12.3, 12.3 / 12.3
+//   FP64 17^3 (39 KB)          12.7 / 12.6, 14.8 / 15.5, 14.8 / 13.9, 15.0 / 13.3
 int64_t tail_half(const Level& L) {   // the first pass's result (no pass: nothing)
   if (L.coarsen[2]) return L.n[0] * L.n[1] * L.m[2];
   return L.coarsen[1] ? L.n[0] * L.m[1] * L.n[2] : 0;
@@ -1399,7 +1400,7 @@ void launch_pad_extend(const bm_plan_s& p, void* g, bool zero, hipStream_t st) {
 }
 
 // Whether the caller's array itself can be the level-1 grid: nothing padded,
-// and no byte shared with the coefficients or codes (na, nb: bytes).
+// and no byte shared with the coefficients or codes (osize: bytes of one).
 static bool direct(const bm_plan_s& p, const void* x, const void* other, size_t osize) {
   const int64_t n = p.pdims[0] * p.pdims[1] * p.pdims[2];
   for (int k = 0; k < 3; ++k)

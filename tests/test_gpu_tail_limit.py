@@ -1,5 +1,5 @@
-"""The first level of the tail launch on either side of its size limit (32 KiB
-of grid: 8192 nodes FP32, 4096 FP64), against a plan created with
+"""The first level of the tail launch on either side of its size limit (27 KiB
+of grid: 6912 nodes FP32, 3456 FP64), against a plan created with
 BM_PLANE_PASS=0, which runs every level by itself.  The same operations in
 the same order: equal bit for bit.
 """
@@ -30,7 +30,8 @@ def _single(*args, **kw):
 
 
 @pytest.mark.parametrize("shape,dt,L,M", [
-    ((17, 17, 25), F32, 0, 2), ((1, 89, 89), F32, 0, 2), ((3, 29, 93), F32, 0, 3), ((93, 1, 88), F32, 0, 1),
+    ((19, 19, 19), F32, 0, 2), ((17, 17, 23), F32, 0, 1), ((1, 83, 83), F32, 0, 3), ((15, 15, 15), F64, 0, 2),
+    ((3, 33, 33), F64, 0, 2), ((17, 17, 25), F32, 0, 2), ((1, 89, 89), F32, 0, 2), ((3, 29, 93), F32, 0, 3), ((93, 1, 88), F32, 0, 1),
     ((17, 17, 33), F32, 0, 2), ((2, 64, 64), F32, 0, 3),
     ((13, 17, 17), F64, 0, 2), ((17, 17, 13), F64, 0, 3), ((1, 64, 64), F64, 0, 2), ((17, 17, 17), F64, 0, 3),
     ((65, 65, 65), F64, 1, 3),
