@@ -523,7 +523,9 @@ bm_status bm_autotune_budget(const bm_config* in, const void* x, const double* v
  * Quantization, fitted apart for the local and the global quantizer as
  * Sec. IV-B does: max(q_slope_ms N_s, q_lat_ms) for each block level s (its
  * per-block tables; N_s its grid's nodes), max(gq_slope_ms N, gq_lat_ms)
- * for an all-global hierarchy (N its padded nodes).  Lossless: stage k of the Huffman coder (0
+ * for an all-global hierarchy (N its padded nodes; with the copy of the field
+ * into the padded grid, so that a field that needs none is predicted on the
+ * high side).  Lossless: stage k of the Huffman coder (0
  * histogram, 1 code table, 2 chunk sizes and encode, 3 copy-out and CRC)
  * takes huf_a_ms[k] + huf_b_ms[k] N for N codes. */
 typedef struct {
